@@ -216,11 +216,13 @@ size_t pf_insert_workspace_bytes(uint64_t n, uint32_t log2_slots);
 
 /* The same accumulation as pf_insert_accumulate (identical table, flags and
  * slots up to the order-dependent placement of probe collisions), without
- * device atomics on the cell sums: vertices are binned by the slot they
- * claim (a counting sort over tile histograms) and each bin -- a contiguous
- * slot range -- is summed in LDS by one workgroup, which then adds count and
- * sums to its cells with plain loads and stores and sets their occupancy
- * bits.  Compare-and-swap remains only for claiming new cells.
+ * device atomics on the cell sums: vertices that share a key are merged in
+ * LDS, each group's record goes to the bucket of its bin -- a contiguous slot
+ * range -- and each bin is summed in LDS by one workgroup, which then adds
+ * count and sums to its cells with plain loads and stores and sets their
+ * occupancy bits.  Compare-and-swap remains only for claiming new cells.  (A
+ * bucket holds twice what evenly spread keys can fill; groups that find it
+ * full go to their cells by device atomics.)
  * slot_out is required.  workspace: pf_insert_workspace_bytes(n, log2_slots)
  * device bytes (caller-owned, no alignment needed).
  * Errors: PF_EINVAL (NULL, misaligned, workspace too small, a

@@ -3,29 +3,37 @@
 // Device atomics run at ~24 G/s on MI355X whatever the footprint, and a
 // random access of any kind moves a whole cache line, so the cost of the
 // insert is the number of per-cell operations it sends to memory.  This path
-// sends one per group of vertices that share a key within a chunk of 4096
-// consecutive vertices, and no atomic at all for the sums:
-//   aggregate  per tile (every ntiles-th chunk): each chunk's vertices are
-//              merged by key in an LDS hash table (count and fixed-point
-//              sums added with LDS atomics; the LDS serialises the lanes of
-//              a coherent run on one entry more cheaply than a wavefront
-//              prefix sum over them costs in VALU work, which bounds this
-//              kernel); each group then probes / claims its cell
-//              once (compare-and-swap on new cells only), writes one record
-//              {slot, count, sums} to the tile's staging area and counts it
-//              in the tile's histogram of slot bins; every vertex receives
-//              its group's slot
-//   colscan    per bin: running record offsets over the tiles, bin totals
-//   scatter    per tile: the start offset of every bin (each workgroup scans
-//              the bin totals itself), then staged records moved to their
-//              bin's range
-//   reduce     per bin (a contiguous slot range): records summed in LDS, then
-//              count and sums added to the cells with plain loads and stores
-//              by the workgroup that owns them, occupancy bits set; with a
-//              temporal blend (Section 3.4.1) in the same launch, the owner
-//              also blends each cell's final average with the previous
-//              table's value of its key and stores the temporal value
+// sends one per group of vertices that share a key within a window of up to
+// 4096 consecutive vertices, and no atomic at all for the sums:
+//   aggregate  per window: the vertices are merged by key in an LDS hash table
+//              (count and fixed-point sums added with LDS atomics; the LDS
+//              serialises the lanes of a coherent run on one entry more cheaply
+//              than a wavefront prefix sum over them costs in VALU work); each
+//              group then probes / claims its cell once (compare-and-swap on
+//              new cells only) and writes one record {slot, count, sums} into
+//              the bucket of its bin (a contiguous slot range); every vertex
+//              receives its group's slot.  A window takes its places in all
+//              buckets with one device atomic per bin it reaches, so a bin's
+//              records of a window are neighbours in memory
+//   reduce     per bin: a bitmap of the slots its records name gives every
+//              cell a dense index (by population counts), the records are
+//              summed in LDS by that index, then count and sums are added to
+//              the cells with plain loads and stores by the workgroup that owns
+//              them, occupancy bits set; with a temporal blend (Section 3.4.1)
+//              in the same launch, the owner also blends each cell's final
+//              average with the previous table's value of its key and stores
+//              the temporal value
 // Integer sums make the result identical to the atomic insert.
+//
+// What it measured (MI355X; all launches of one call, the temporal blend in
+// reduce): 1920x1080x3 vertices (1.1M groups) 183 us, 3840x2160x4 (11M groups)
+// 906 us, 401x229x3 40 us, 64x64 34 us.  The counting sort it replaces (a
+// record of 32 bytes staged per workgroup, histograms scanned over the
+// workgroups, records scattered to their bins' ranges, LDS sums for every slot
+// of a bin, windows of a fixed 4096 vertices) took 234, 1544, 96 and 85 us:
+// incoherent vertices hardly merge, so the records' way through memory is what
+// the insert costs, and a window of mostly distinct keys overflowed its LDS
+// table and sent its vertices to the table one by one.
 #include <mutex>
 
 #include "pf_kernels.h"
@@ -36,21 +44,27 @@ namespace pfk {
 
 namespace binned {
 
-constexpr int kT = 1024;                     // threads of the tile kernels
-constexpr uint32_t kPer = 4;                 // vertices per thread and chunk
-constexpr uint32_t kChunk = kT * kPer;       // vertices merged in one LDS table
-constexpr uint32_t kMaxTiles = 512;          // two workgroups on each of 256 CUs
-constexpr uint32_t kLdsBudget = 80 * 1024;   // two 1024-thread workgroups per CU
-constexpr uint32_t kFlush = 2;               // LDS entries per thread (entries <= kFlush * kT)
+constexpr int kT = 1024;                     // threads of aggregate
+constexpr uint32_t kMaxSteps = 4;            // vertices per thread and chunk, at most
+constexpr uint32_t kMaxGroups = 512;         // two workgroups on each of 256 CUs
+constexpr uint32_t kFlush = 2;               // LDS entries per thread
+constexpr uint32_t kCap = kFlush * kT;       // LDS entries of a window
+constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
-constexpr int kReduceThreads = 1024;  // the bin's LDS sums allow two workgroups per CU
+constexpr uint32_t kMaxBins = 256, kMaxParts = 8;
+constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
+constexpr int kR = 1024;                     // threads of reduce
+constexpr uint32_t kCells = 2048;            // cells of a bin summed in LDS at a time
+constexpr uint32_t kHold = 4;                // records a thread of reduce keeps in registers
 
-// One staged group: the cell layout with the slot in place of the fingerprint.
-struct __align__(16) Rec {
-    uint32_t slot, count;
-    int64_t s[3];
-};
-static_assert(sizeof(Rec) == 32, "record is two 16-byte words");
+// A record is 16 bytes: one word of slot, count and kind, three of sums.  A
+// group whose sums all fit 32 bits and whose count fits 6 is one record; others
+// are followed by records of kind 1 that add to the high parts:
+//   kind 0: count 1 + c, sums sign-extended;  kind 1: count 64 c, sums << 32.
+// (Contributions below 128 / vertices at 24 fraction bits fit one record; with
+// 32-byte records of full sums a 3840x2160x4 frame moved twice the bytes.)
+constexpr uint32_t kSlotBits = 25, kCountMask = 63u;
+static_assert(kMaxLog2Slots == kSlotBits && kSlotBits + 7 == 32, "slot, 6 bits of count and the kind in one word");
 
 // Inputs of key construction when the insert builds the keys itself.
 struct FusedKeys {
@@ -60,45 +74,57 @@ struct FusedKeys {
     uint64_t *key_out;  // nullable
 };
 
+// A record buffer's view as aggregate writes it: bucket (bin, part) holds up
+// to part_cap records; cnt counts the places taken (possibly beyond part_cap:
+// those groups went to their cells by device atomics, and spill[bin] is set).
+struct Buckets {
+    uint4 *rec;
+    uint32_t *cnt, *spill;
+    uint32_t bin_shift, nbins, parts, part_cap;
+};
+
 struct Plan {
-    uint32_t log2_bins, nbins, bin_shift, bin_slots, ntiles, tile, cap;
+    uint32_t nbins, bin_shift, groups, steps, parts, part_cap;
     size_t lds_aggregate, lds_reduce;
-    size_t off_h, off_tot, off_start, off_ntr, off_trec, off_rec, bytes;
+    size_t off_cnt, off_rec, bytes;
+    uint32_t nzero;  // words from off_cnt on that start at zero: ticket, spill flags, bucket counts
 };
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 Plan make_plan(uint32_t n, uint32_t log2_slots) {
     Plan p;
-    // bins of 2048 slots (4096 above 2^24 slots, keeping the histogram small)
-    uint32_t lbs = log2_slots > 24 ? 12 : 11;
-    if (lbs > log2_slots) lbs = log2_slots;
-    p.bin_shift = lbs;
-    p.bin_slots = 1u << lbs;
-    p.log2_bins = log2_slots - lbs;
-    p.nbins = 1u << p.log2_bins;
-    // a tile is the set of chunks one workgroup takes (every ntiles-th);
-    // its staging area holds a record per vertex at most
-    const uint32_t nchunks = (n + kChunk - 1) / kChunk;
-    p.ntiles = nchunks < kMaxTiles ? (nchunks ? nchunks : 1) : kMaxTiles;
-    p.tile = (nchunks + p.ntiles - 1) / p.ntiles * kChunk;
-    if (p.tile == 0) p.tile = kChunk;
-    // LDS of aggregate: key 8 B, sums 24 B and count 4 B per entry, the bin
-    // histogram and two counters; entries take what the budget leaves
-    const size_t fixed = (size_t)p.nbins * 4 + 16;
-    uint32_t cap = (uint32_t)((kLdsBudget - fixed) / 36) / 64 * 64;
-    if (cap < 512) cap = 512;
-    if (cap > kFlush * kT) cap = kFlush * kT;
-    p.cap = cap;
-    p.lds_aggregate = (size_t)cap * 36 + fixed;
-    p.lds_reduce = (size_t)p.bin_slots * 28;
-    p.off_h = 0;
-    p.off_tot = align256((size_t)p.ntiles * p.nbins * 4);
-    p.off_start = p.off_tot + align256((size_t)p.nbins * 4);
-    p.off_ntr = p.off_start + align256((size_t)p.nbins * 4);
-    p.off_trec = p.off_ntr + align256((size_t)p.ntiles * 4);
-    p.off_rec = p.off_trec + align256((size_t)p.ntiles * p.tile * sizeof(Rec));
-    p.bytes = p.off_rec + align256((size_t)(n ? n : 1) * sizeof(Rec)) + 256;
+    // a bin per 1024 vertices, at most 256: a window of ~1500 groups then
+    // takes a handful of neighbouring places in each
+    uint32_t log2_bins = 0;
+    while ((1u << log2_bins) < kMaxBins && (1024u << log2_bins) < n) ++log2_bins;
+    if (log2_slots > kMaxLog2BinSlots && log2_bins < log2_slots - kMaxLog2BinSlots)
+        log2_bins = log2_slots - kMaxLog2BinSlots;
+    const uint32_t most = log2_slots > 5 ? log2_slots - 5 : 0;  // a bin owns whole bitmap words
+    if (log2_bins > most) log2_bins = most;
+    p.nbins = 1u << log2_bins;
+    p.bin_shift = log2_slots - log2_bins;
+    // steps of kT vertices spread over as many workgroups as there are, in
+    // chunks of equal size
+    const uint32_t nsteps = n ? (n + kT - 1) / kT : 1;
+    const uint32_t rounds = (nsteps + kMaxGroups * kMaxSteps - 1) / (kMaxGroups * kMaxSteps);
+    p.steps = (nsteps + kMaxGroups * rounds - 1) / (kMaxGroups * rounds);
+    const uint32_t nchunks = (nsteps + p.steps - 1) / p.steps;
+    p.groups = nchunks < kMaxGroups ? nchunks : kMaxGroups;
+    // a bucket is split into one part per XCD (workgroups are dealt to the 8
+    // XCDs in turn), so that a line of records is completed through one L2
+    p.parts = nsteps >= 64 ? kMaxParts : 1;
+    // room for four records a vertex in all (twice what a call can write
+    // when every group needs two), and some for uneven parts of small calls
+    const uint64_t nparts = (uint64_t)p.nbins * p.parts;
+    p.part_cap = (uint32_t)((4ull * n + nparts - 1) / nparts) + 32;
+    p.nzero = 1 + p.nbins + p.nbins * p.parts;
+    p.lds_aggregate = (size_t)kCap * 36 + (size_t)p.nbins * 8 + (4 + 2 * kMaxSteps) * 4;
+    const uint32_t words = p.bin_shift > 5 ? 1u << (p.bin_shift - 5) : 1u;
+    p.lds_reduce = (size_t)kCells * 32 + (size_t)words * 8;
+    p.off_cnt = 0;
+    p.off_rec = align256((size_t)p.nzero * 4);
+    p.bytes = p.off_rec + align256((size_t)nparts * p.part_cap * sizeof(uint4)) + 256;
     return p;
 }
 
@@ -128,329 +154,341 @@ __device__ __forceinline__ uint32_t claim(const Tab &t, uint64_t key) {
     return claim_next(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
-__device__ __forceinline__ void store_rec(Rec *p, uint32_t slot, uint32_t count, uint64_t s0, uint64_t s1,
-                                          uint64_t s2) {
-    uint4 *w = reinterpret_cast<uint4 *>(p);
-    w[0] = make_uint4(slot, count, (uint32_t)s0, (uint32_t)(s0 >> 32));
-    w[1] = make_uint4((uint32_t)s1, (uint32_t)(s1 >> 32), (uint32_t)s2, (uint32_t)(s2 >> 32));
+// Whether a group needs records of kind 1, and how many.
+__device__ __forceinline__ uint32_t extra_records(uint32_t count, uint64_t s0, uint64_t s1, uint64_t s2) {
+    const bool fits = (int64_t)s0 == (int32_t)s0 && (int64_t)s1 == (int32_t)s1 && (int64_t)s2 == (int32_t)s2;
+    const uint32_t high = (count - 1) >> 6;
+    return (high + kCountMask - 1) / kCountMask + (!fits && high == 0 ? 1u : 0u);
 }
 
-// Key of vertex i built in the insert itself (Algorithm 1, as pf_build_keys);
-// the caller has checked the vertex's valid byte.
-__device__ __forceinline__ uint8_t fused_key(const FusedKeys &fk, uint32_t i, uint64_t &k) {
-    const float x[3] = {fk.px[i], fk.py[i], fk.pz[i]};
-    const float nr[3] = {fk.nx[i], fk.ny[i], fk.nz[i]};
-    uint32_t fp, home;
-    const PcgJump jp(fk.a.seed, fk.a.idx_base);
-    return vertex_key(x, nr, true, fk.a.cam, fk.a.s, fk.a.inv_s, jp, i, fk.a.mask, k, fp, home);
+// One group's records from place `pos` of its bucket part on; a group whose
+// records do not all fit goes to its cell by device atomics instead.
+__device__ __forceinline__ void put_records(const Buckets &bk, const Tab &t, uint32_t part, uint32_t pos,
+                                            uint32_t extra, uint32_t s, uint32_t count, uint64_t s0, uint64_t s1,
+                                            uint64_t s2) {
+    const uint32_t bin = s >> bk.bin_shift;
+    if (pos < bk.part_cap && pos + extra < bk.part_cap) {
+        uint4 *w = bk.rec + ((size_t)bin * bk.parts + part) * bk.part_cap + pos;
+        w[0] = make_uint4(s | ((count - 1) & kCountMask) << kSlotBits, (uint32_t)s0, (uint32_t)s1, (uint32_t)s2);
+        uint32_t high = (count - 1) >> 6;
+        // what the sign-extended low parts leave, in units of 2^32
+        uint32_t h0 = (uint32_t)((s0 - (uint64_t)(int64_t)(int32_t)s0) >> 32);
+        uint32_t h1 = (uint32_t)((s1 - (uint64_t)(int64_t)(int32_t)s1) >> 32);
+        uint32_t h2 = (uint32_t)((s2 - (uint64_t)(int64_t)(int32_t)s2) >> 32);
+        for (uint32_t e = 1; e <= extra; ++e) {
+            const uint32_t c = min(high, kCountMask);
+            w[e] = make_uint4(s | c << kSlotBits | 0x80000000u, h0, h1, h2);
+            high -= c;
+            h0 = h1 = h2 = 0;
+        }
+    } else {
+        // places below part_cap that no group fills are read by reduce:
+        // records that add nothing
+        for (uint32_t e = pos; e <= pos + extra && e < bk.part_cap; ++e)
+            bk.rec[((size_t)bin * bk.parts + part) * bk.part_cap + e] = make_uint4(s | 0x80000000u, 0, 0, 0);
+        accumulate(t, s, count, (int64_t)s0, (int64_t)s1, (int64_t)s2);
+        __hip_atomic_fetch_or(&t.occ[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bk.spill[bin] = 1;
+    }
 }
+
+// The count words of a call start at zero (a kernel of its own: a memset is
+// not safe to capture in a graph).
+__global__ __launch_bounds__(kT) void zero_kernel(uint32_t *p, uint32_t n) {
+    for (uint32_t k = threadIdx.x; k < n; k += kT) p[k] = 0;
+}
+
+// A vertex's inputs: its contribution and its key, or (kKeys) the position
+// and normal its key is built from (Algorithm 1, as pf_build_keys).
+template <bool kKeys>
+struct VertexIn {
+    float c[3];
+    float x[kKeys ? 3 : 1], nr[kKeys ? 3 : 1];
+    uint64_t key;
+};
+
+template <bool kKeys>
+__device__ __forceinline__ VertexIn<kKeys> load_vertex(const FusedKeys &fk, const uint64_t *key, const float *r,
+                                                       const float *g, const float *b, uint32_t i) {
+    VertexIn<kKeys> in{};
+    in.c[0] = r[i];
+    in.c[1] = g[i];
+    in.c[2] = b[i];
+    if constexpr (kKeys) {
+        in.x[0] = fk.px[i];
+        in.x[1] = fk.py[i];
+        in.x[2] = fk.pz[i];
+        in.nr[0] = fk.nx[i];
+        in.nr[1] = fk.ny[i];
+        in.nr[2] = fk.nz[i];
+    } else {
+        in.key = key[i];
+    }
+    return in;
+}
+
+// Key, fixed-point contribution and flags of a vertex; rnd: its PCG32 outputs.
+template <bool kKeys>
+__device__ __forceinline__ uint32_t vertex_value(const FusedKeys &fk, const VertexIn<kKeys> &in, const uint32_t rnd[3],
+                                                 int frac_bits, uint64_t &k, int64_t &q0, int64_t &q1, int64_t &q2) {
+    uint32_t f = 0;
+    k = in.key;
+    if constexpr (kKeys) {
+        uint32_t fp, home;
+        f = vertex_key(in.x, in.nr, true, fk.a.cam, fk.a.s, fk.a.inv_s, rnd, fk.a.mask, k, fp, home);
+    }
+    if (f == 0) f = fixed_point(in.c[0], in.c[1], in.c[2], frac_bits, q0, q1, q2);
+    return f;
+}
+
+// What a thread keeps of a vertex until its window is flushed (16 bits): its
+// LDS entry, kAlone (no room in LDS), or kFlagged and its flags.
+constexpr uint32_t kAlone = 0xffffu, kFlagged = 0x8000u;
 
 // kKeys: keys are built here from positions and normals (fk) and the flags
 // are outputs only; otherwise key[] and flags[] come from pf_build_keys.
+//
+// Bound by the vertex phase's VALU issue and by the latencies of a window's
+// chain (claim, bucket places) with two workgroups of 16 waves on a CU.  A
+// workgroup takes chunks of `steps` x 1024 consecutive vertices and goes
+// through a chunk in steps of one vertex per thread.  The steps are gathered
+// into windows: a window ends when the next step's valid vertices might not
+// find room in the LDS table any more (more than kLimit entries in use), so
+// coherent streams merge over 4096 vertices, while streams of mostly
+// distinct keys (small images, bounces, shuffled keys) flush as often as the
+// table needs.
 template <bool kKeys>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void aggregate_kernel(
     Tab t, const uint64_t *__restrict__ key, const float *__restrict__ r, const float *__restrict__ g,
     const float *__restrict__ b, uint8_t *__restrict__ flags, uint32_t *__restrict__ slot_out, uint32_t n,
-    uint32_t tile, uint32_t cap, uint32_t nbins, uint32_t bin_shift, uint32_t *__restrict__ H,
-    uint32_t *__restrict__ ntr, Rec *__restrict__ trec, FusedKeys fk) {
+    uint32_t steps, Buckets bk, uint32_t *__restrict__ ticket, FusedKeys fk) {
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned long long *lkey = reinterpret_cast<unsigned long long *>(lds);
-    unsigned long long *ls0 = lkey + cap, *ls1 = ls0 + cap, *ls2 = ls1 + cap;
-    uint32_t *lcnt = reinterpret_cast<uint32_t *>(ls2 + cap);  // count, then the group's slot
-    uint32_t *hist = lcnt + cap;
-    uint32_t *misc = hist + nbins;                              // [0] staged records, [1] overflowed vertices
-    for (uint32_t k = threadIdx.x; k < nbins; k += kT) hist[k] = 0;
-    if (threadIdx.x < 2) misc[threadIdx.x] = 0;
-    // chunks are dealt out with a stride so that every workgroup gets a mix
-    // of coherent and incoherent (or empty) parts of the stream
-    const uint32_t nchunks = (n + kChunk - 1) / kChunk;
-    Rec *out = trec + (size_t)blockIdx.x * tile;
-    for (uint32_t ci = blockIdx.x; ci < nchunks; ci += gridDim.x) {
-        const uint32_t c0 = ci * kChunk;
-        const uint32_t i1 = min(n, c0 + kChunk);
-        for (uint32_t j = threadIdx.x; j < cap; j += kT) {
-            lkey[j] = kEmpty;
-            ls0[j] = 0;
-            ls1[j] = 0;
-            ls2[j] = 0;
-            lcnt[j] = 0;
-        }
-        __syncthreads();
-        // only the flags (8 bits per vertex) and the LDS entries (16 bits,
-        // 0xffff = none) stay live across the barriers, packed; the rare
-        // vertex that finds no room reloads its key and contribution
-        uint32_t flp0 = 0, flp = 0;
-        uint64_t ep = 0;
-        if constexpr (kKeys) {
-            flp0 = 0xffffffffu;  // no input flags: every vertex's flags are written
-            // the valid bytes of the thread's vertices first: masked vertices
-            // (sky, escaped paths) read nothing more
-            uint32_t live = 0;
+    unsigned long long *ls0 = lkey + kCap, *ls1 = ls0 + kCap, *ls2 = ls1 + kCap;
+    uint32_t *lcnt = reinterpret_cast<uint32_t *>(ls2 + kCap);  // count, then the group's slot
+    uint32_t *taken = lcnt + kCap;      // [nbins] places the window takes in each bin
+    uint32_t *place = taken + bk.nbins;  // [nbins] the first of them
+    uint32_t *misc = place + bk.nbins;  // [0] overflowed vertices, [1] the next chunk
+    uint32_t *created = misc + 4;       // [kMaxSteps] LDS entries created by each step of the chunk
+    uint32_t *nvalid = created + kMaxSteps;  // [kMaxSteps] valid vertices of each step
+    const uint32_t tid = threadIdx.x;
+    const uint32_t part = blockIdx.x % bk.parts;
+    for (uint32_t k = tid; k < bk.nbins; k += kT) taken[k] = 0;
+    if (tid < 4 + 2 * kMaxSteps) misc[tid] = 0;
+    for (uint32_t j = tid; j < kCap; j += kT) {
+        lkey[j] = kEmpty;
+        ls0[j] = 0;
+        ls1[j] = 0;
+        ls2[j] = 0;
+        lcnt[j] = 0;
+    }
+    __syncthreads();
+    // the thread's part of the PCG32 states of its vertices: vertex i0 + tid
+    // has F + E (i0 + tid), and the uniform F + E i0 costs no vector work
+    const PcgJump jp(fk.a.seed, fk.a.idx_base);
+    uint64_t pe[3];
 #pragma unroll
-            for (uint32_t u = 0; u < kPer; ++u) {
-                const uint32_t i = c0 + u * kT + threadIdx.x;
-                const bool v = i < i1 && (fk.valid == nullptr || fk.valid[i] != 0);
-                live |= (v ? 1u : 0u) << u;
-            }
-#pragma unroll 1
-            for (uint32_t u = 0; u < kPer; ++u) {
-                const uint32_t i = c0 + u * kT + threadIdx.x;
-                uint32_t f = PF_V_INVALID;
+    for (int k = 0; k < 3; ++k) pe[k] = jp.E[k] * tid;
+    auto random3 = [&](uint32_t i0, uint32_t rnd[3]) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) rnd[k] = PcgJump::permute(jp.F[k] + jp.E[k] * (uint64_t)i0 + pe[k]);
+    };
+    const uint32_t nchunks = (n + steps * kT - 1) / (steps * kT);
+    // chunks differ in cost (coherent, incoherent or empty parts of the
+    // stream): a workgroup takes the next one when it is done
+    uint32_t ci = blockIdx.x;
+    while (ci < nchunks) {
+        uint32_t next_chunk = 0;
+        if (tid == 0) next_chunk = gridDim.x + atomicAdd(ticket, 1u);
+        const uint32_t c0 = ci * steps * kT;
+        const uint32_t nsteps = min(steps, (n - c0 + kT - 1) / kT);
+        // the valid bytes (or input flags) of the chunk first: masked
+        // vertices (sky, escaped paths) read nothing more
+        uint32_t live = 0;
+        for (uint32_t u = 0; u < nsteps; ++u) {
+            const uint32_t i = c0 + u * kT + tid;
+            bool v = i < n;
+            if constexpr (kKeys)
+                v = v && (fk.valid == nullptr || fk.valid[i] != 0);
+            else
+                v = v && flags[i] == 0;
+            live |= (v ? 1u : 0u) << u;
+        }
+        for (uint32_t u = 0; u < nsteps; ++u) {
+            const uint64_t m = __ballot((live >> u) & 1u);
+            if ((tid & 63) == 0 && m) atomicAdd(&nvalid[u], (uint32_t)__popcll(m));
+        }
+        uint32_t w0 = 0;  // the window's first step
+        while (w0 < nsteps) {
+            uint64_t code = 0;  // 16 bits per step
+            uint32_t used = 0;  // entries in use, at most (exact after a barrier)
+            uint32_t u = w0;
+            bool synced;
+            do {
+                const uint32_t i0 = c0 + u * kT, i = i0 + tid;
+                uint32_t c = kKeys ? kFlagged | PF_V_INVALID : kFlagged;
                 uint64_t k = 0;
-                int64_t q0 = 0, q1 = 0, q2 = 0;
+                bool fresh = false;
                 if ((live >> u) & 1u) {
-                    const float cr = r[i], cg = g[i], cb = b[i];
-                    f = fused_key(fk, i, k);
-                    if (f == 0) f = fixed_point(cr, cg, cb, t.frac_bits, q0, q1, q2);
+                    const VertexIn<kKeys> in = load_vertex<kKeys>(fk, key, r, g, b, i);
+                    uint32_t rnd[3] = {0, 0, 0};
+                    if constexpr (kKeys) random3(i0, rnd);
+                    int64_t q0, q1, q2;
+                    c = vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
+                    if (c == 0) {
+                        const int e = lds_insert(lkey, kCap, k, fresh);
+                        if (e >= 0) {
+                            atomicAdd(&lcnt[e], 1u);
+                            atomicAdd(&ls0[e], (unsigned long long)q0);
+                            atomicAdd(&ls1[e], (unsigned long long)q1);
+                            atomicAdd(&ls2[e], (unsigned long long)q2);
+                            c = (uint32_t)e;
+                        } else {
+                            c = kAlone;
+                        }
+                    } else {
+                        c |= kFlagged;
+                    }
                 }
-                if (fk.key_out && i < i1) fk.key_out[i] = k;
-                flp |= f << (8 * u);
-                const int e = merge_into_lds<false>(lkey, ls0, ls1, ls2, lcnt, cap, f == 0, k, q0, q1, q2);
-                ep |= (uint64_t)(uint16_t)e << (16 * u);
-            }
-        } else {
+                if (kKeys && fk.key_out && i < n) fk.key_out[i] = k;
+                const uint64_t m = __ballot(fresh);
+                if ((tid & 63) == 0 && m) atomicAdd(&created[u], (uint32_t)__popcll(m));
+                code |= (uint64_t)c << (16 * u);
+                synced = false;
+                const bool first = u == 0;
+                ++u;
+                if (u == nsteps) break;
+                // go on while the next step's vertices are sure to find room;
+                // the counters are read after a barrier, only when the bound
+                // does not tell already (every thread decides alike)
+                if (!first && used + nvalid[u - 1] + nvalid[u] <= kLimit) {
+                    used += nvalid[u - 1];
+                    continue;
+                }
+                __syncthreads();
+                synced = true;
+                used = 0;
+                for (uint32_t v = w0; v < u; ++v) used += created[v];
+            } while (used + nvalid[u] <= kLimit);
+            if (!synced) __syncthreads();
+            // one probe / claim per group; a thread's
+            // entries issue their home-slot loads, then their compare-and-swaps
+            // on empty home slots, before either result is needed
+            uint64_t gk[kFlush];
+            uint32_t fs[kFlush], ff[kFlush], fcur[kFlush];
 #pragma unroll
-        for (uint32_t u = 0; u < kPer; ++u) {
-            const uint32_t i = c0 + u * kT + threadIdx.x;
-            flp0 |= (uint32_t)(i < i1 ? flags[i] : (uint8_t)PF_V_INVALID) << (8 * u);
-        }
-        flp = flp0;
-        // software pipeline: the contribution and key of vertex u + 1 are in
-        // flight while vertex u is merged
-        float nr = 0.0f, ng = 0.0f, nb = 0.0f;
-        uint64_t nk = 0;
-        if ((flp0 & 0xffu) == 0) {
-            const uint32_t i = c0 + threadIdx.x;
-            nr = r[i];
-            ng = g[i];
-            nb = b[i];
-            nk = key[i];
-        }
-#pragma unroll 1
-        for (uint32_t u = 0; u < kPer; ++u) {
-            const float cr = nr, cg = ng, cb = nb;
-            const uint64_t k = nk;
-            if (u + 1 < kPer && ((flp0 >> (8 * (u + 1))) & 0xffu) == 0) {
-                const uint32_t i = c0 + (u + 1) * kT + threadIdx.x;
-                nr = r[i];
-                ng = g[i];
-                nb = b[i];
-                nk = key[i];
+            for (uint32_t v = 0; v < kFlush; ++v) {
+                const uint32_t j = v * kT + tid;
+                gk[v] = lkey[j];
+                fs[v] = 0;
+                ff[v] = 0;
+                fcur[v] = 0;
+                if (gk[v] != kEmpty) {
+                    fs[v] = home_of(gk[v], t.mask);
+                    ff[v] = fingerprint_of(gk[v]);
+                    fcur[v] = load_fp_probe(&t.cell_at(fs[v]).fp);
+                }
             }
-            uint32_t f = (flp0 >> (8 * u)) & 0xffu;
-            int64_t q0 = 0, q1 = 0, q2 = 0;
-            if (f == 0) f = fixed_point(cr, cg, cb, t.frac_bits, q0, q1, q2);
-            flp |= f << (8 * u);  // bits change only where they were 0
-            const int e = merge_into_lds<false>(lkey, ls0, ls1, ls2, lcnt, cap, f == 0, k, q0, q1, q2);
-            ep |= (uint64_t)(uint16_t)e << (16 * u);
-        }
-        }
-        __syncthreads();
-        // one probe / claim and one staged record per group; a thread's
-        // entries issue their home-slot loads, then their compare-and-swaps
-        // on empty home slots, before either result is needed
-        uint64_t gk[kFlush];
-        uint32_t fs[kFlush], ff[kFlush], fcur[kFlush];
+            bool won[kFlush];
 #pragma unroll
-        for (uint32_t v = 0; v < kFlush; ++v) {
-            const uint32_t j = v * kT + threadIdx.x;
-            gk[v] = j < cap ? lkey[j] : kEmpty;
-            fs[v] = 0;
-            ff[v] = 0;
-            fcur[v] = 0;
-            if (gk[v] != kEmpty) {
-                fs[v] = home_of(gk[v], t.mask);
-                ff[v] = fingerprint_of(gk[v]);
-                fcur[v] = load_fp_probe(&t.cell_at(fs[v]).fp);
+            for (uint32_t v = 0; v < kFlush; ++v) {
+                won[v] = false;
+                if (gk[v] != kEmpty && fcur[v] == 0) {
+                    uint32_t expected = 0;
+                    won[v] =
+                        __hip_atomic_compare_exchange_strong(&t.cell_at(fs[v]).fp, &expected, ff[v], __ATOMIC_RELAXED,
+                                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    fcur[v] = won[v] ? ff[v] : expected;
+                }
             }
-        }
-        bool won[kFlush];
+            // the group's rank among the window's records of its bin
+            uint32_t slot[kFlush], cnt[kFlush], rank[kFlush];
 #pragma unroll
-        for (uint32_t v = 0; v < kFlush; ++v) {
-            won[v] = false;
-            if (gk[v] != kEmpty && fcur[v] == 0) {
-                uint32_t expected = 0;
-                won[v] = __hip_atomic_compare_exchange_strong(&t.cell_at(fs[v]).fp, &expected, ff[v], __ATOMIC_RELAXED,
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                fcur[v] = won[v] ? ff[v] : expected;
-            }
-        }
-#pragma unroll
-        for (uint32_t v = 0; v < kFlush; ++v) {
-            const uint32_t j = v * kT + threadIdx.x;
-            uint32_t s = kNoSlot;
-            if (gk[v] != kEmpty) {
+            for (uint32_t v = 0; v < kFlush; ++v) {
+                const uint32_t j = v * kT + tid;
+                slot[v] = kNoSlot;
+                if (gk[v] == kEmpty) continue;
                 if (won[v]) t.key_at(fs[v]) = gk[v];
                 // the home slot holds another key: probe on from the next
-                s = fcur[v] == ff[v] ? fs[v] : claim_next(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
-                if (s == kNoSlot) atomicAdd(&misc[1], lcnt[j]);
+                slot[v] = fcur[v] == ff[v] ? fs[v] : claim_next(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
+                cnt[v] = lcnt[j];
+                lcnt[j] = slot[v];
+                if (slot[v] != kNoSlot)
+                    rank[v] = atomicAdd(&taken[slot[v] >> bk.bin_shift],
+                                        1u + extra_records(cnt[v], ls0[j], ls1[j], ls2[j]));
+                else
+                    atomicAdd(&misc[0], cnt[v]);
             }
-            const bool stage = gk[v] != kEmpty && s != kNoSlot;
-            const uint32_t pos = wave_reserve(&misc[0], stage);
-            if (stage) {
-                store_rec(out + pos, s, lcnt[j], ls0[j], ls1[j], ls2[j]);
-                atomicAdd(&hist[s >> bin_shift], 1u);
-            }
-            if (gk[v] != kEmpty) lcnt[j] = s;
-        }
-        __syncthreads();
+            __syncthreads();
+            // the window's places, one device atomic per bin; the vertices get
+            // their slots while they are on their way
+            uint32_t first_place = 0;
+            const uint32_t want = tid < bk.nbins ? taken[tid] : 0u;
+            if (want)
+                first_place = __hip_atomic_fetch_add(&bk.cnt[tid * bk.parts + part], want, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
-        for (uint32_t u = 0; u < kPer; ++u) {
-            const uint32_t i = c0 + u * kT + threadIdx.x;
-            uint32_t f = (flp >> (8 * u)) & 0xffu;
-            const uint32_t e = (uint32_t)(ep >> (16 * u)) & 0xffffu;
-            uint32_t s = kNoSlot;
-            bool alone = false;
-            int64_t q0 = 0, q1 = 0, q2 = 0;
-            if (f == 0) {
-                if (e != 0xffffu) {
-                    s = lcnt[e];
-                } else {  // no room in the LDS table: a group of its own
-                    fixed_point(r[i], g[i], b[i], t.frac_bits, q0, q1, q2);
+            for (uint32_t v = w0; v < u; ++v) {
+                const uint32_t i0 = c0 + v * kT, i = i0 + tid;
+                const uint32_t c = (uint32_t)(code >> (16 * v)) & 0xffffu;
+                uint32_t s = kNoSlot, f = 0;
+                if (c < kFlagged) {
+                    s = lcnt[c];
+                    f = s == kNoSlot ? (uint32_t)PF_V_OVERFLOW : 0u;
+                } else if (c == kAlone) {  // no room in the LDS table: a group of its own
+                    const VertexIn<kKeys> in = load_vertex<kKeys>(fk, key, r, g, b, i);
+                    uint32_t rnd[3] = {0, 0, 0};
+                    if constexpr (kKeys) random3(i0, rnd);
                     uint64_t k;
-                    if constexpr (kKeys)
-                        fused_key(fk, i, k);
-                    else
-                        k = key[i];
+                    int64_t q0, q1, q2;
+                    vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
                     s = claim(t, k);
-                    alone = s != kNoSlot;
-                    if (!alone) atomicAdd(&misc[1], 1u);
+                    if (s != kNoSlot) {
+                        const uint32_t extra = extra_records(1, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
+                        const uint32_t pos =
+                            __hip_atomic_fetch_add(&bk.cnt[(s >> bk.bin_shift) * bk.parts + part], 1u + extra,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        put_records(bk, t, part, pos, extra, s, 1u, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
+                    } else {
+                        f = PF_V_OVERFLOW;
+                        atomicAdd(&misc[0], 1u);
+                    }
+                } else {
+                    f = c & 0xffu;
                 }
-                if (s == kNoSlot) f = PF_V_OVERFLOW;
-            }
-            const uint32_t pos = wave_reserve(&misc[0], alone);
-            if (alone) {
-                store_rec(out + pos, s, 1u, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
-                atomicAdd(&hist[s >> bin_shift], 1u);
-            }
-            if (i < i1) {
-                if (f != ((flp0 >> (8 * u)) & 0xffu)) flags[i] = (uint8_t)f;
-                slot_out[i] = s;
-            }
-        }
-        __syncthreads();  // the table is cleared for the next chunk
-    }
-    __syncthreads();
-    uint32_t *row = H + (size_t)blockIdx.x * nbins;
-    for (uint32_t k = threadIdx.x; k < nbins; k += kT) row[k] = hist[k];
-    if (threadIdx.x == 0) {
-        ntr[blockIdx.x] = misc[0];
-        if (misc[1]) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], misc[1]);
-    }
-}
-
-// Per bin: exclusive running offset over the tiles (in place), bin total.
-// Tiles are taken XCD by XCD (workgroups are dealt to the 8 XCDs in turn,
-// so tile t runs on XCD t % 8): a bin's range is cut into 8 sub-ranges each
-// written by the scatter workgroups of one XCD, and a cache line of records
-// is filled through one L2 instead of several.
-// A workgroup takes 16 bins; each of its 64 rows of lanes holds the counts of
-// 8 consecutive tiles of that order in registers, so a column is loaded
-// once, summed in parallel and rewritten without a second read.
-constexpr int kScanBins = 16, kScanRows = 64, kScanPer = 8;
-constexpr uint32_t kXcds = 8;
-static_assert(kScanRows * kScanPer >= kMaxTiles, "one register batch covers every tile");
-static_assert(kMaxTiles % kXcds == 0, "tiles split evenly over the XCDs");
-__global__ __launch_bounds__(kScanBins *kScanRows) void colscan_kernel(uint32_t *__restrict__ H, uint32_t ntiles,
-                                                                       uint32_t nbins,
-                                                                       uint32_t *__restrict__ total) {
-    __shared__ uint32_t part[kScanRows][kScanBins + 1];
-    const uint32_t bx = threadIdx.x % kScanBins, cy = threadIdx.x / kScanBins;
-    const uint32_t bin = blockIdx.x * kScanBins + bx;
-    const uint32_t per = (ntiles + kXcds - 1) / kXcds;  // tiles per XCD (at most 64)
-    const uint32_t q0 = cy * kScanPer;
-    uint32_t v[kScanPer], tt[kScanPer];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-        const uint32_t q = q0 + k;  // position in XCD-major order
-        tt[k] = (q % per) * kXcds + q / per;
-        const bool in = bin < nbins && q < kXcds * per && tt[k] < ntiles;
-        if (!in) tt[k] = ~0u;
-        v[k] = in ? H[(size_t)tt[k] * nbins + bin] : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) s += v[k];
-    part[cy][bx] = s;
-    __syncthreads();
-    uint32_t run = 0;
-    for (uint32_t c = 0; c < cy; ++c) run += part[c][bx];
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-        if (tt[k] != ~0u) H[(size_t)tt[k] * nbins + bin] = run;
-        run += v[k];
-    }
-    if (cy == kScanRows - 1 && bin < nbins) total[bin] = run;
-}
-
-constexpr uint32_t kBatch = 4;  // records per thread loaded before any is moved
-
-__global__ __launch_bounds__(kT) void scatter_kernel(const Rec *__restrict__ trec, const uint32_t *__restrict__ ntr,
-                                                     uint32_t tile, uint32_t nbins, uint32_t bin_shift,
-                                                     const uint32_t *__restrict__ H,
-                                                     const uint32_t *__restrict__ total, uint32_t *__restrict__ start,
-                                                     Rec *__restrict__ rec) {
-    extern __shared__ uint32_t cursor[];
-    __shared__ uint32_t part[kT];
-    const uint4 *in = reinterpret_cast<const uint4 *>(trec + (size_t)blockIdx.x * tile);
-    const uint32_t m = ntr[blockIdx.x];
-    uint4 lo[kBatch], hi[kBatch];
-#pragma unroll
-    for (uint32_t u = 0; u < kBatch; ++u) {  // first batch in flight while the cursors are set up
-        const uint32_t j = u * kT + threadIdx.x;
-        if (j < m) {
-            lo[u] = in[2 * j];
-            hi[u] = in[2 * j + 1];
-        }
-    }
-    // every workgroup scans the bin totals itself (a few KB, L2-resident)
-    // instead of waiting for a launch of its own; workgroup 0 stores the
-    // bins' start offsets for reduce.  Each lane takes `per` consecutive
-    // bins; a Hillis-Steele scan runs over the lanes' partial sums.
-    const uint32_t *row = H + (size_t)blockIdx.x * nbins;
-    const uint32_t per = (nbins + kT - 1) / kT;
-    const uint32_t b0 = threadIdx.x * per;
-    uint32_t local = 0;
-    for (uint32_t k = 0; k < per; ++k)
-        if (b0 + k < nbins) local += total[b0 + k];
-    part[threadIdx.x] = local;
-    __syncthreads();
-    for (uint32_t off = 1; off < kT; off <<= 1) {
-        const uint32_t v = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    uint32_t run = part[threadIdx.x] - local;  // exclusive
-    for (uint32_t k = 0; k < per; ++k)
-        if (b0 + k < nbins) {
-            cursor[b0 + k] = run + row[b0 + k];
-            if (blockIdx.x == 0) start[b0 + k] = run;
-            run += total[b0 + k];
-        }
-    __syncthreads();
-    for (uint32_t j0 = 0; j0 < m; j0 += kBatch * kT) {
-        if (j0) {
-#pragma unroll
-            for (uint32_t u = 0; u < kBatch; ++u) {
-                const uint32_t j = j0 + u * kT + threadIdx.x;
-                if (j < m) {
-                    lo[u] = in[2 * j];
-                    hi[u] = in[2 * j + 1];
+                if (i < n) {
+                    if (kKeys || f) flags[i] = (uint8_t)f;
+                    slot_out[i] = s;
                 }
             }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t j = j0 + u * kT + threadIdx.x;
-            if (j < m) {
-                const uint32_t pos = atomicAdd(&cursor[lo[u].x >> bin_shift], 1u);
-                uint4 *o = reinterpret_cast<uint4 *>(rec + pos);
-                o[0] = lo[u];
-                o[1] = hi[u];
+            if (want) {
+                place[tid] = first_place;
+                taken[tid] = 0;
             }
+            if (tid < 2 * kMaxSteps && u == nsteps) created[tid] = 0;  // and nvalid, for the next chunk
+            if (tid == 0) misc[1] = next_chunk;
+            __syncthreads();
+#pragma unroll
+            for (uint32_t v = 0; v < kFlush; ++v) {
+                const uint32_t j = v * kT + tid;
+                if (gk[v] == kEmpty) continue;
+                if (slot[v] != kNoSlot) {
+                    const uint64_t s0 = ls0[j], s1 = ls1[j], s2 = ls2[j];
+                    put_records(bk, t, part, place[slot[v] >> bk.bin_shift] + rank[v],
+                                extra_records(cnt[v], s0, s1, s2), slot[v], cnt[v], s0, s1, s2);
+                }
+                lkey[j] = kEmpty;  // emptied for the next window
+                ls0[j] = 0;
+                ls1[j] = 0;
+                ls2[j] = 0;
+                lcnt[j] = 0;
+            }
+            w0 = u;
+            if (w0 == nsteps) ci = misc[1];
+            __syncthreads();
         }
     }
+    if (tid == 0 && misc[0]) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], misc[0]);
 }
 
 // The temporal blend done by reduce: the previous table (has_prev) and the
@@ -461,127 +499,186 @@ struct Blend {
     uint32_t cap;
 };
 
-// One workgroup per bin: LDS sums over its records, then the exclusive
-// owner adds them to the cells and sets the occupancy bits of its words.
-// kBlend: the owner then computes the temporal values of its cells (the
-// cells are final: every record of a slot is in the slot's bin), as
-// temporal_word does for one bitmap word.
+// One workgroup per bin: the slots its records name, as a bitmap; a cell's
+// index is the number of set bits before its own, so the LDS holds sums for the
+// cells there are and not for the bin's slots (a frame fills a few percent of
+// its table).  More than kCells cells take several passes over the records.
+// The exclusive owner then adds the sums to the cells and sets the occupancy
+// bits of its words.
+// kBlend: it also computes the temporal values of the cells (which are final:
+// every record of a slot is in the slot's bin), as temporal_word does for one
+// bitmap word.
 template <bool kBlend = false, bool kHasPrev = false, bool kIntegrate = false>
-__global__ __launch_bounds__(kReduceThreads) void reduce_kernel(Tab t, const Rec *__restrict__ rec,
-                                                                const uint32_t *__restrict__ start,
-                                                                const uint32_t *__restrict__ total,
-                                                                uint32_t bin_slots, Blend bl) {
+__global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl) {
     extern __shared__ unsigned long long lred[];
-    unsigned long long *sum0 = lred, *sum1 = lred + bin_slots, *sum2 = lred + 2 * bin_slots;
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(lred + 3 * bin_slots);
-    const uint32_t bin = blockIdx.x;
-    const uint32_t base = bin * bin_slots;
-    for (uint32_t k = threadIdx.x; k < bin_slots; k += kReduceThreads) {
+    unsigned long long *sum0 = lred, *sum1 = lred + kCells, *sum2 = lred + 2 * kCells;
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(lred + 3 * kCells);
+    uint32_t *list = cnt + kCells;  // the cells' slots within the bin
+    const uint32_t words = bk.bin_shift > 5 ? 1u << (bk.bin_shift - 5) : 1u;
+    uint32_t *bits = list + kCells, *before = bits + words;  // bitmap, set bits before each word
+    __shared__ uint32_t seg[kMaxParts + 1], wave_sum[kR / 64], s_hits;
+    const uint32_t tid = threadIdx.x, bin = blockIdx.x, base = bin << bk.bin_shift;
+    const uint32_t in_bin = (1u << bk.bin_shift) - 1;
+    if (tid <= kMaxParts) seg[tid] = tid < bk.parts ? min(bk.cnt[bin * bk.parts + tid], bk.part_cap) : 0u;
+    if (tid == 0) s_hits = 0;
+    // cells that got sums by device atomics (a full bucket) are in the
+    // occupancy bitmap already; they are blended too
+    const bool spilled = kBlend && bk.spill[bin] != 0;
+    for (uint32_t w = tid; w < words; w += kR) bits[w] = spilled ? t.occ[(base >> 5) + w] : 0u;
+    for (uint32_t k = tid; k < kCells; k += kR) {
         sum0[k] = 0;
         sum1[k] = 0;
         sum2[k] = 0;
         cnt[k] = 0;
     }
     __syncthreads();
-    const uint4 *in = reinterpret_cast<const uint4 *>(rec);
-    const uint32_t j0 = start[bin], j1 = j0 + total[bin];
-    for (uint32_t jb = j0; jb < j1; jb += kBatch * kReduceThreads) {
-        uint4 lo[kBatch], hi[kBatch];
+    uint32_t end[kMaxParts], m = 0;  // where each part's records end in the bin's sequence
 #pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t j = jb + u * kReduceThreads + threadIdx.x;
-            if (j < j1) {
-                lo[u] = in[2 * (size_t)j];
-                hi[u] = in[2 * (size_t)j + 1];
-            }
-        }
+    for (uint32_t x = 0; x < kMaxParts; ++x) {
+        m += seg[x];
+        end[x] = m;
+    }
+    auto record = [&](uint32_t j) -> uint4 {
+        uint32_t x = 0, from = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t j = jb + u * kReduceThreads + threadIdx.x;
-            if (j < j1) {
-                const uint32_t loc = lo[u].x - base;
-                atomicAdd(&cnt[loc], lo[u].y);
-                atomicAdd(&sum0[loc], (unsigned long long)lo[u].z | (unsigned long long)lo[u].w << 32);
-                atomicAdd(&sum1[loc], (unsigned long long)hi[u].x | (unsigned long long)hi[u].y << 32);
-                atomicAdd(&sum2[loc], (unsigned long long)hi[u].z | (unsigned long long)hi[u].w << 32);
+        for (uint32_t y = 0; y + 1 < kMaxParts; ++y)
+            if (j >= end[y]) {
+                x = y + 1;
+                from = end[y];
             }
-        }
+        return bk.rec[((size_t)bin * bk.parts + x) * bk.part_cap + (j - from)];
+    };
+    auto mark = [&](const uint4 &q) {
+        const uint32_t loc = q.x & in_bin;
+        atomicOr(&bits[loc >> 5], 1u << (loc & 31));
+    };
+    uint4 held[kHold];
+#pragma unroll
+    for (uint32_t u = 0; u < kHold; ++u)
+        if (u * kR + tid < m) held[u] = record(u * kR + tid);
+#pragma unroll
+    for (uint32_t u = 0; u < kHold; ++u)
+        if (u * kR + tid < m) mark(held[u]);
+    for (uint32_t j0 = kHold * kR; j0 < m; j0 += kHold * kR) {
+        uint4 q[kHold];
+#pragma unroll
+        for (uint32_t u = 0; u < kHold; ++u)
+            if (j0 + u * kR + tid < m) q[u] = record(j0 + u * kR + tid);
+#pragma unroll
+        for (uint32_t u = 0; u < kHold; ++u)
+            if (j0 + u * kR + tid < m) mark(q[u]);
     }
     __syncthreads();
-    // the cells of a thread's slots are all loaded before any is updated
-    uint4 *cells = t.words_at(base);  // 4 sixteen-byte words per slot record
-    uint32_t hits = 0;
-    for (uint32_t kb = 0; kb < bin_slots; kb += kBatch * kReduceThreads) {
-        uint32_t c[kBatch];
-        uint4 lo[kBatch], hi[kBatch];
+    // set bits before each word: a thread takes `per` consecutive words
+    const uint32_t per = (words + kR - 1) / kR, b0 = tid * per;
+    uint32_t own = 0;
+    for (uint32_t w = b0; w < min(words, b0 + per); ++w) own += (uint32_t)__popc(bits[w]);
+    uint32_t incl = own;
 #pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t k = kb + u * kReduceThreads + threadIdx.x;
-            c[u] = k < bin_slots ? cnt[k] : 0u;
-            if (c[u]) {
-                lo[u] = cells[4 * k];
-                hi[u] = cells[4 * k + 1];
+    for (uint32_t off = 1; off < 64; off <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+        if ((tid & 63) >= off) incl += v;
+    }
+    if ((tid & 63) == 63) wave_sum[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t run = incl - own, ncells = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kR / 64; ++w) {
+        if (w < (tid >> 6)) run += wave_sum[w];
+        ncells += wave_sum[w];
+    }
+    const uint32_t run0 = run;
+    for (uint32_t w = b0; w < min(words, b0 + per); ++w) {
+        before[w] = run;
+        const uint32_t v = bits[w];
+        run += (uint32_t)__popc(v);
+        // occupancy: the words of this bin belong to this workgroup
+        if (v) t.occ[(base >> 5) + w] |= v;
+    }
+    uint32_t hits = 0;
+    for (uint32_t c0 = 0; c0 < ncells; c0 += kCells) {
+        const uint32_t nc = min(ncells - c0, kCells);
+        if (c0) {
+            __syncthreads();  // the last pass's cells are written
+            for (uint32_t k = tid; k < nc; k += kR) {
+                sum0[k] = 0;
+                sum1[k] = 0;
+                sum2[k] = 0;
+                cnt[k] = 0;
             }
         }
-#pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t k = kb + u * kReduceThreads + threadIdx.x;
-            if (c[u]) {
-                const uint64_t s0 = ((uint64_t)lo[u].z | (uint64_t)lo[u].w << 32) + sum0[k];
-                const uint64_t s1 = ((uint64_t)hi[u].x | (uint64_t)hi[u].y << 32) + sum1[k];
-                const uint64_t s2 = ((uint64_t)hi[u].z | (uint64_t)hi[u].w << 32) + sum2[k];
-                cells[4 * k] = make_uint4(lo[u].x, lo[u].y + c[u], (uint32_t)s0, (uint32_t)(s0 >> 32));
-                cells[4 * k + 1] = make_uint4((uint32_t)s1, (uint32_t)(s1 >> 32), (uint32_t)s2, (uint32_t)(s2 >> 32));
+        uint32_t at = run0;
+        for (uint32_t w = b0; w < min(words, b0 + per); ++w)
+            for (uint32_t v = bits[w]; v; v &= v - 1, ++at)
+                if (at - c0 < nc) list[at - c0] = w * 32 + (uint32_t)__builtin_ctz(v);
+        __syncthreads();
+        auto add = [&](const uint4 &q) {
+            const uint32_t loc = q.x & in_bin;
+            const uint32_t k = before[loc >> 5] + (uint32_t)__popc(bits[loc >> 5] & ((1u << (loc & 31)) - 1u)) - c0;
+            if (k >= nc) return;  // another pass's cell
+            const uint32_t c = (q.x >> kSlotBits) & kCountMask;
+            unsigned long long v0, v1, v2;
+            if (__builtin_expect(q.x >> 31, 0)) {
+                v0 = (unsigned long long)q.y << 32;
+                v1 = (unsigned long long)q.z << 32;
+                v2 = (unsigned long long)q.w << 32;
+                atomicAdd(&cnt[k], 64u * c);
+            } else {
+                v0 = (unsigned long long)(int64_t)(int32_t)q.y;
+                v1 = (unsigned long long)(int64_t)(int32_t)q.z;
+                v2 = (unsigned long long)(int64_t)(int32_t)q.w;
+                atomicAdd(&cnt[k], 1u + c);
             }
-            // occupancy: a wavefront's 64 consecutive slots are two bitmap
-            // words of this bin (bins hold >= 32 slots, or the whole table)
-            const uint64_t m = __ballot(c[u] != 0);
-            if ((threadIdx.x & 63) == 0 && m) {
-                const uint32_t w = (base + k) >> 5;
-                if ((uint32_t)m) t.occ[w] |= (uint32_t)m;
-                if (m >> 32) t.occ[w + 1] |= (uint32_t)(m >> 32);
+            atomicAdd(&sum0[k], v0);
+            atomicAdd(&sum1[k], v1);
+            atomicAdd(&sum2[k], v2);
+        };
+#pragma unroll
+        for (uint32_t u = 0; u < kHold; ++u)
+            if (u * kR + tid < m) add(held[u]);
+        for (uint32_t j0 = kHold * kR; j0 < m; j0 += kHold * kR) {
+            uint4 q[kHold];
+#pragma unroll
+            for (uint32_t u = 0; u < kHold; ++u)
+                if (j0 + u * kR + tid < m) q[u] = record(j0 + u * kR + tid);
+#pragma unroll
+            for (uint32_t u = 0; u < kHold; ++u)
+                if (j0 + u * kR + tid < m) add(q[u]);
+        }
+        __syncthreads();
+        for (uint32_t k = tid; k < nc; k += kR) {
+            const uint32_t sl[1] = {base + list[k]};
+            uint4 *w4 = t.words_at(sl[0]);  // 4 sixteen-byte words per slot record
+            const uint4 lo = w4[0], hi = w4[1];
+            pf_cell cl;
+            cl.fp = lo.x;
+            cl.count = lo.y + cnt[k];
+            const uint64_t s0 = ((uint64_t)lo.z | (uint64_t)lo.w << 32) + sum0[k];
+            const uint64_t s1 = ((uint64_t)hi.x | (uint64_t)hi.y << 32) + sum1[k];
+            const uint64_t s2 = ((uint64_t)hi.z | (uint64_t)hi.w << 32) + sum2[k];
+            uint64_t kw = 0;
+            if constexpr (kBlend && kHasPrev) kw = t.key_at(sl[0]);
+            w4[0] = make_uint4(cl.fp, cl.count, (uint32_t)s0, (uint32_t)(s0 >> 32));
+            w4[1] = make_uint4((uint32_t)s1, (uint32_t)(s1 >> 32), (uint32_t)s2, (uint32_t)(s2 >> 32));
+            if constexpr (kBlend) {
+                cl.sum[0] = (int64_t)s0;
+                cl.sum[1] = (int64_t)s1;
+                cl.sum[2] = (int64_t)s2;
+                const bool has[1] = {true};
+                const uint64_t key[1] = {kw};
+                const uint32_t fp[1] = {cl.fp}, n[1] = {cl.count};
+                uint32_t keep[1] = {kIntegrate ? min(cl.count, bl.cap) : cl.count};
+                float v[1][3] = {{t.average(cl, 0), t.average(cl, 1), t.average(cl, 2)}};
+                hits += blend_cells<kHasPrev, kIntegrate, 1, false>(t, bl.prev, sl, has, key, fp, v, n, keep, bl.alpha,
+                                                                    bl.beta, bl.cap);
             }
         }
     }
-    if constexpr (kBlend) {
-        // the bin's cells are final: listed in LDS (the sums' space is free
-        // now), then blended one per lane, so that every lane has a cell
-        // while the list lasts
-        __shared__ uint32_t nlist, s_hits;
-        uint32_t *list = reinterpret_cast<uint32_t *>(sum0);
-        if (threadIdx.x == 0) {
-            nlist = 0;
-            s_hits = 0;
-        }
-        __syncthreads();  // the cells are written, the sums no longer read
-        for (uint32_t k = threadIdx.x; k < bin_slots; k += kReduceThreads)
-            if (cnt[k]) list[atomicAdd(&nlist, 1u)] = k;
+    if constexpr (kBlend && kHasPrev) {
+        // one device atomic per workgroup, spread over 32 partial counters
+        if (hits) atomicAdd(&s_hits, hits);
         __syncthreads();
-        const uint32_t m = nlist;
-        for (uint32_t q = threadIdx.x; q < m; q += kReduceThreads) {
-            const uint32_t sl[1] = {base + list[q]};
-            const uint4 *w4 = t.words_at(sl[0]);  // written above by this workgroup
-            const uint4 lo = w4[0], hi = w4[1], kw = w4[2];
-            pf_cell cl;
-            cl.fp = lo.x;
-            cl.count = lo.y;
-            cl.sum[0] = (int64_t)((uint64_t)lo.z | (uint64_t)lo.w << 32);
-            cl.sum[1] = (int64_t)((uint64_t)hi.x | (uint64_t)hi.y << 32);
-            cl.sum[2] = (int64_t)((uint64_t)hi.z | (uint64_t)hi.w << 32);
-            const bool has[1] = {true};
-            const uint64_t key[1] = {(uint64_t)kw.x | (uint64_t)kw.y << 32};
-            const uint32_t fp[1] = {cl.fp}, n[1] = {cl.count};
-            uint32_t keep[1] = {kIntegrate ? min(cl.count, bl.cap) : cl.count};
-            float v[1][3] = {{t.average(cl, 0), t.average(cl, 1), t.average(cl, 2)}};
-            hits += blend_cells<kHasPrev, kIntegrate, 1, false>(t, bl.prev, sl, has, key, fp, v, n, keep, bl.alpha,
-                                                                bl.beta, bl.cap);
-        }
-        if constexpr (kHasPrev) {
-            // one device atomic per workgroup, spread over 32 partial counters
-            if (hits) atomicAdd(&s_hits, hits);
-            __syncthreads();
-            if (threadIdx.x == 0 && s_hits) add_u64(&t.stats[PF_STAT_PART_HIT + (blockIdx.x & 31)], s_hits);
-        }
+        if (tid == 0 && s_hits) add_u64(&t.stats[PF_STAT_PART_HIT + (blockIdx.x & 31)], s_hits);
     }
 }
 
@@ -611,47 +708,46 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
     const uint32_t log2_slots = 32 - __builtin_clz(t.mask + 1) - 1;
     const Plan p = make_plan(n, log2_slots);
     char *base = reinterpret_cast<char *>((reinterpret_cast<uintptr_t>(ws) + 255) / 256 * 256);
-    uint32_t *H = reinterpret_cast<uint32_t *>(base + p.off_h);
-    uint32_t *tot = reinterpret_cast<uint32_t *>(base + p.off_tot);
-    uint32_t *start = reinterpret_cast<uint32_t *>(base + p.off_start);
-    uint32_t *ntr = reinterpret_cast<uint32_t *>(base + p.off_ntr);
-    Rec *trec = reinterpret_cast<Rec *>(base + p.off_trec);
-    Rec *rec = reinterpret_cast<Rec *>(base + p.off_rec);
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(base + p.off_cnt);
+    Buckets bk;
+    bk.spill = ticket + 1;
+    bk.cnt = bk.spill + p.nbins;
+    bk.rec = reinterpret_cast<uint4 *>(base + p.off_rec);
+    bk.bin_shift = p.bin_shift;
+    bk.nbins = p.nbins;
+    bk.parts = p.parts;
+    bk.part_cap = p.part_cap;
     static bool attrs = false;  // dynamic LDS above 64 KB needs the attribute, set once per function
     if (!attrs) {
+        constexpr int kAggregateLds = kCap * 36 + kMaxBins * 8 + (4 + 2 * kMaxSteps) * 4;
+        constexpr int kReduceLds = kCells * 32 + (8 << (kMaxLog2BinSlots - 5));
+        static_assert(kAggregateLds <= 80 * 1024, "two workgroups of aggregate share a CU");
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
         for (const void *f : kReduceKernels)
             if (e == hipSuccess)
-                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(4096 * 28));
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kReduceLds);
         if (e != hipSuccess) return e;
         attrs = true;
     }
-    aggregate_kernel<kKeys><<<p.ntiles, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n, p.tile, p.cap,
-                                                                   p.nbins, p.bin_shift, H, ntr, trec, fk);
-    colscan_kernel<<<(p.nbins + kScanBins - 1) / kScanBins, kScanBins * kScanRows, 0, st>>>(H, p.ntiles, p.nbins,
-                                                                                          tot);
-    scatter_kernel<<<p.ntiles, kT, (size_t)p.nbins * 4, st>>>(trec, ntr, p.tile, p.nbins, p.bin_shift, H, tot,
-                                                              start, rec);
+    zero_kernel<<<1, kT, 0, st>>>(ticket, p.nzero);
+    aggregate_kernel<kKeys><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n, p.steps, bk,
+                                                                   ticket, fk);
     const Blend none{};
     const Blend &bl = blend ? *blend : none;
     if (!blend)
-        reduce_kernel<<<p.nbins, kReduceThreads, p.lds_reduce, st>>>(t, rec, start, tot, p.bin_slots, bl);
+        reduce_kernel<<<p.nbins, kR, p.lds_reduce, st>>>(t, bk, bl);
     else if (!has_prev && !integrate)
-        reduce_kernel<true, false, false><<<p.nbins, kReduceThreads, p.lds_reduce, st>>>(t, rec, start, tot,
-                                                                                       p.bin_slots, bl);
+        reduce_kernel<true, false, false><<<p.nbins, kR, p.lds_reduce, st>>>(t, bk, bl);
     else if (has_prev && !integrate)
-        reduce_kernel<true, true, false><<<p.nbins, kReduceThreads, p.lds_reduce, st>>>(t, rec, start, tot,
-                                                                                      p.bin_slots, bl);
+        reduce_kernel<true, true, false><<<p.nbins, kR, p.lds_reduce, st>>>(t, bk, bl);
     else if (!has_prev)
-        reduce_kernel<true, false, true><<<p.nbins, kReduceThreads, p.lds_reduce, st>>>(t, rec, start, tot,
-                                                                                      p.bin_slots, bl);
+        reduce_kernel<true, false, true><<<p.nbins, kR, p.lds_reduce, st>>>(t, bk, bl);
     else
-        reduce_kernel<true, true, true><<<p.nbins, kReduceThreads, p.lds_reduce, st>>>(t, rec, start, tot,
-                                                                                     p.bin_slots, bl);
+        reduce_kernel<true, true, true><<<p.nbins, kR, p.lds_reduce, st>>>(t, bk, bl);
     return hipGetLastError();
 }
 

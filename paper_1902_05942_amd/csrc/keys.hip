@@ -20,7 +20,8 @@ __global__ __launch_bounds__(kBlock) void build_keys_kernel(
     if (valid == nullptr || valid[i] != 0) {  // masked vertices read nothing more
         const float x[3] = {px[i], py[i], pz[i]};
         const float nr[3] = {nx[i], ny[i], nz[i]};
-        flags = vertex_key(x, nr, true, a.cam, a.s, a.inv_s, jp, i, a.mask, key, fp, home);
+        const uint32_t rnd[3] = {jp.output(0, i), jp.output(1, i), jp.output(2, i)};
+        flags = vertex_key(x, nr, true, a.cam, a.s, a.inv_s, rnd, a.mask, key, fp, home);
     }
     key_out[i] = key;
     flags_out[i] = flags;

@@ -91,7 +91,11 @@ struct PcgJump {
     }
 
     __device__ __forceinline__ uint32_t output(int k, uint32_t i) const {
-        const uint64_t old = F[k] + E[k] * (uint64_t)i;
+        return permute(F[k] + E[k] * (uint64_t)i);
+    }
+
+    // XSH-RR of a state
+    static __device__ __forceinline__ uint32_t permute(uint64_t old) {
         const uint32_t xs = (uint32_t)(((old >> 18) ^ old) >> 27);
         const uint32_t rot = (uint32_t)(old >> 59);
         return (xs >> rot) | (xs << ((32u - rot) & 31u));

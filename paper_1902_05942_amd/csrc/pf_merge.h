@@ -28,15 +28,18 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t *ctr, bool want) {
     return base + rank;
 }
 
-// LDS entry of `key` in the chunk's table (inserted if absent), or -1 when
-// kLdsProbe entries in a row hold other keys.
-__device__ __forceinline__ int lds_insert(unsigned long long *lkey, uint32_t cap, uint64_t key) {
+// LDS entry of `key` in the window's table (inserted if absent, then fresh is
+// set), or -1 when the kLdsProbe entries of its probe sequence hold other
+// keys.  The probes are 1, 2, 3, ... apart, so that a nearly full table has
+// no runs to walk along.
+__device__ __forceinline__ int lds_insert(unsigned long long *lkey, uint32_t cap, uint64_t key, bool &fresh) {
     uint32_t j = (uint32_t)(((uint64_t)(uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 32) * cap) >> 32);
 #pragma unroll 1
-    for (uint32_t d = 0; d < kLdsProbe; ++d) {
+    for (uint32_t d = 1; d <= kLdsProbe; ++d) {
         const unsigned long long old = atomicCAS(&lkey[j], (unsigned long long)kEmpty, (unsigned long long)key);
-        if (old == kEmpty || old == key) return (int)j;
-        j = j + 1 == cap ? 0 : j + 1;
+        fresh = old == kEmpty;
+        if (fresh || old == key) return (int)j;
+        j = j + d >= cap ? j + d - cap : j + d;
     }
     return -1;
 }
@@ -82,8 +85,9 @@ __device__ __forceinline__ int merge_into_lds(unsigned long long *lkey, unsigned
                                               int64_t q2) {
     if constexpr (!kWaveRuns) {  // every valid lane adds itself
         int e = -1;
+        bool fresh;
         if (ok) {
-            e = lds_insert(lkey, cap, k);
+            e = lds_insert(lkey, cap, k, fresh);
             if (e >= 0) {
                 atomicAdd(&lcnt[e], 1u);
                 atomicAdd(&ls0[e], (unsigned long long)q0);
@@ -123,8 +127,9 @@ __device__ __forceinline__ int merge_into_lds(unsigned long long *lkey, unsigned
         a2 = p2 - e2;
     }
     int e = -1;
+    bool fresh;
     if (ok && lane == tail) {
-        e = lds_insert(lkey, cap, kv);
+        e = lds_insert(lkey, cap, kv, fresh);
         if (e >= 0) {
             atomicAdd(&lcnt[e], cnt);
             atomicAdd(&ls0[e], (unsigned long long)a0);

@@ -11,10 +11,10 @@ namespace pfk {
 
 // Key construction of Algorithm 1 for one vertex.  Returns the vertex flags
 // (0, PF_V_INVALID or PF_V_KEYRANGE); key/fp/home are 0 for flagged vertices.
-// jp holds the launch's PCG32 streams (seed, idx_base) and i is the vertex's
-// index within the launch (stream idx_base + i); inv_s = RN(1 / s).
+// rnd: the first three PCG32 outputs of the vertex's stream (idx_base + i,
+// seeded with the launch's seed); inv_s = RN(1 / s).
 __device__ __forceinline__ uint8_t vertex_key(const float x[3], const float nr[3], bool valid, const float cam[3],
-                                              float s, float inv_s, const PcgJump &jp, uint32_t i, uint32_t mask,
+                                              float s, float inv_s, const uint32_t rnd[3], uint32_t mask,
                                               uint64_t &key, uint32_t &fp, uint32_t &home) {
     key = 0;
     fp = 0;
@@ -27,7 +27,7 @@ __device__ __forceinline__ uint8_t vertex_key(const float x[3], const float nr[3
     // jitter(n): cube sample projected onto the tangent plane
     float r[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) r[c] = ldexpf((float)(jp.output(c, i) >> 8), -24) - 0.5f;
+    for (int c = 0; c < 3; ++c) r[c] = ldexpf((float)(rnd[c] >> 8), -24) - 0.5f;
     const float t0 = r[0] * nr[0];
     const float t1 = r[1] * nr[1];
     const float t2 = r[2] * nr[2];

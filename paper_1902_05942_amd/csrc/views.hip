@@ -94,7 +94,8 @@ __device__ __forceinline__ uint8_t view_vertex(const pf_view &d, const Tab &t, f
     const float nr[3] = {d.nx[i], d.ny[i], d.nz[i]};
     uint32_t fp, home;
     const PcgJump jp(d.kp.seed, d.kp.idx_base);
-    uint8_t fl = vertex_key(x, nr, true, d.kp.cam, d.kp.s, inv_s, jp, i, t.mask, key, fp, home);
+    const uint32_t rnd[3] = {jp.output(0, i), jp.output(1, i), jp.output(2, i)};
+    uint8_t fl = vertex_key(x, nr, true, d.kp.cam, d.kp.s, inv_s, rnd, t.mask, key, fp, home);
     if (fl == 0) fl = fixed_point(d.r[i], d.g[i], d.b[i], t.frac_bits, q0, q1, q2);
     return fl;
 }

@@ -1,0 +1,84 @@
+"""The binned insert where its windows, buckets and bins have their edges: steps
+of 1024 vertices, windows that fill the LDS table, groups whose count or sums
+need more than one record, a bucket that runs full (its groups then go to their
+cells by device atomics) and bins of more cells than one pass sums.  All sums are
+integers: table, averages and counts equal the oracle's group-by bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1902_05942_amd as pf
+from gpu_util import assert_bits_equal, table_contents
+
+pytestmark = pytest.mark.gpu
+
+
+def _insert_and_compare(key, rgb, m, frac_bits=24):
+    n = key.size
+    probe = min(64, 1 << m)
+    R = oracle.filter_keys(key, rgb[0], rgb[1], rgb[2], np.ones(n, np.uint8), m, probe, frac_bits)
+    t = pf.Table(m, probe, frac_bits)
+    pf.table_init(t)
+    k = torch.from_numpy(key.view(np.int64)).cuda()
+    r, g, b = (torch.from_numpy(x).cuda() for x in rgb)
+    fl = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(n, dtype=torch.int32, device="cuda")
+    ws = torch.empty(pf.insert_workspace_bytes(n, m), dtype=torch.uint8, device="cuda")
+    out = [torch.empty(n, device="cuda") for _ in range(3)]
+    pf.insert_accumulate_binned(t, k, r, g, b, fl, slot, ws)
+    pf.query_average(t, k, slot, r, g, b, fl, False, *out, cnt)
+    torch.cuda.synchronize()
+    assert R.table.order_free and not R.flags.any()
+    assert_bits_equal(fl.cpu().numpy(), R.flags, "flags")
+    assert_bits_equal(cnt.cpu().numpy().view(np.uint32), R.cnt, "count")
+    assert_bits_equal(np.stack([o.cpu().numpy() for o in out], 1), R.out, "average")
+    tc = table_contents(t)
+    order = np.argsort(tc["key"])
+    assert_bits_equal(tc["key"][order], R.gkey, "table keys")
+    assert_bits_equal(tc["count"][order], R.gcnt, "table counts")
+    assert_bits_equal(tc["sum"][order], R.gsum, "table sums")
+    assert_bits_equal(tc["occupied"], R.table.occupied, "occupied slots")
+    bits = np.unpackbits(t.occupancy().cpu().numpy().view(np.uint8), bitorder="little")[:1 << m]
+    assert_bits_equal(bits, R.table.occupied, "occupancy bitmap")
+
+
+def _keys(ids):
+    return ids.astype(np.uint64) * np.uint64(2654435761)
+
+
+@pytest.mark.parametrize("n,distinct,m", [
+    (1, 1, 4), (63, 9, 5), (1023, 1023, 12), (1024, 1, 4), (1025, 700, 12), (4097, 4097, 14), (5000, 3, 6),
+    (64 * 1024, 30000, 17), (64 * 1024 + 1, 64 * 1024 + 1, 18), (525000, 1793, 17), (1 << 21, 900000, 22)])
+def test_edges_of_steps_windows_and_bins(gpu, n, distinct, m):
+    rng = np.random.default_rng(n + m)
+    ids = np.concatenate([np.arange(distinct), rng.integers(0, distinct, n - distinct)])
+    rng.shuffle(ids)
+    _insert_and_compare(_keys(ids), rng.random((3, n), dtype=np.float32), m)
+
+
+@pytest.mark.parametrize("frac_bits,scale,per", [
+    (40, 900.0, 1),        # every sum needs its high part
+    (24, 150.0, 65),       # counts on both sides of 64, some sums beyond 2^31
+    (24, -150.0, 64),
+    (8, 1.0e13, 2000),     # sums near the top of 64 bits
+    (24, 1.0, 4096)])      # one cell for a whole window
+def test_groups_of_more_than_one_record(gpu, frac_bits, scale, per):
+    n = 20000
+    rng = np.random.default_rng(per)
+    rgb = (rng.random((3, n), dtype=np.float32) * np.float32(scale)).astype(np.float32)
+    rgb[1] = -rgb[1]
+    _insert_and_compare(_keys(np.arange(n) // per), rgb, 16, frac_bits)
+
+
+def test_full_bucket_and_several_passes(gpu):
+    # every home slot lies in one 256th of the table: that bin's buckets run
+    # full, and it holds more cells than are summed in one pass
+    m, cells, n = 22, 5000, 1 << 20
+    cand = _keys(np.arange(1, 3000000))
+    home, _ = oracle.key_hashes(cand, m)
+    chosen = cand[(home >> np.uint32(m - 8)) == 17][:cells]
+    assert len(chosen) == cells
+    rng = np.random.default_rng(3)
+    _insert_and_compare(chosen[rng.integers(0, cells, n)], rng.random((3, n), dtype=np.float32), m)
