@@ -26,8 +26,8 @@
 // Integer sums make the result identical to the atomic insert.
 //
 // What it measured (MI355X; all launches of one call, the temporal blend in
-// reduce): 1920x1080x3 vertices (1.1M groups) 183 us, 3840x2160x4 (11M groups)
-// 906 us, 401x229x3 40 us, 64x64 34 us.  The counting sort it replaces (a
+// reduce): 1920x1080x3 vertices (1.1M groups) 161 us, 3840x2160x4 (11M groups)
+// 815 us, 401x229x3 40 us, 64x64 35 us.  The counting sort it replaces (a
 // record of 32 bytes staged per workgroup, histograms scanned over the
 // workgroups, records scattered to their bins' ranges, LDS sums for every slot
 // of a bin, windows of a fixed 4096 vertices) took 234, 1544, 96 and 85 us:
@@ -48,14 +48,16 @@ constexpr int kT = 1024;                     // threads of aggregate
 constexpr uint32_t kMaxSteps = 4;            // vertices per thread and chunk, at most
 constexpr uint32_t kMaxGroups = 512;         // two workgroups on each of 256 CUs
 constexpr uint32_t kFlush = 2;               // LDS entries per thread
-constexpr uint32_t kCap = kFlush * kT;       // LDS entries of a window
+constexpr uint32_t kCap = 1920;              // LDS entries of a window
 constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
-constexpr uint32_t kMaxBins = 256, kMaxParts = 8;
+constexpr uint32_t kMaxBins = 512, kMaxParts = 8;
 constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
-constexpr int kR = 1024;                     // threads of reduce
+constexpr int kR = 512;                      // threads of reduce: two workgroups on a CU, all bins at once
 constexpr uint32_t kCells = 2048;            // cells of a bin summed in LDS at a time
 constexpr uint32_t kHold = 4;                // records a thread of reduce keeps in registers
+constexpr uint32_t kMark = 16;               // records whose slots are read together after those
+constexpr int kPair = 2;                     // cells a thread of reduce updates together
 
 // A record is 16 bytes: one word of slot, count and kind, three of sums.  A
 // group whose sums all fit 32 bits and whose count fits 6 is one record; others
@@ -84,7 +86,7 @@ struct Buckets {
 };
 
 struct Plan {
-    uint32_t nbins, bin_shift, groups, steps, parts, part_cap;
+    uint32_t nbins, bin_shift, groups, chunk, parts, part_cap;
     size_t lds_aggregate, lds_reduce;
     size_t off_cnt, off_rec, bytes;
     uint32_t nzero;  // words from off_cnt on that start at zero: ticket, spill flags, bucket counts
@@ -94,10 +96,14 @@ static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 Plan make_plan(uint32_t n, uint32_t log2_slots) {
     Plan p;
-    // a bin per 1024 vertices, at most 256: a window of ~1500 groups then
-    // takes a handful of neighbouring places in each
+    // a bin per 1024 vertices up to 256 (a window of ~1500 groups then takes
+    // a handful of neighbouring places in each), 512 for more than 2^22
+    // vertices: reduce gains more than aggregate's places cost (8M incoherent
+    // keys: 206 -> 161 us against 450 -> 460; 3840x2160x4: 190 -> 149 against
+    // 657 -> 677; at 1920x1080x3 the two are even)
     uint32_t log2_bins = 0;
-    while ((1u << log2_bins) < kMaxBins && (1024u << log2_bins) < n) ++log2_bins;
+    while (log2_bins < 8 && (1024u << log2_bins) < n) ++log2_bins;
+    if (n > 1u << 22) log2_bins = 9;
     if (log2_slots > kMaxLog2BinSlots && log2_bins < log2_slots - kMaxLog2BinSlots)
         log2_bins = log2_slots - kMaxLog2BinSlots;
     const uint32_t most = log2_slots > 5 ? log2_slots - 5 : 0;  // a bin owns whole bitmap words
@@ -108,8 +114,9 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     // chunks of equal size
     const uint32_t nsteps = n ? (n + kT - 1) / kT : 1;
     const uint32_t rounds = (nsteps + kMaxGroups * kMaxSteps - 1) / (kMaxGroups * kMaxSteps);
-    p.steps = (nsteps + kMaxGroups * rounds - 1) / (kMaxGroups * rounds);
-    const uint32_t nchunks = (nsteps + p.steps - 1) / p.steps;
+    const uint32_t steps = (nsteps + kMaxGroups * rounds - 1) / (kMaxGroups * rounds);
+    p.chunk = steps * kT;
+    const uint32_t nchunks = (nsteps + steps - 1) / steps;
     p.groups = nchunks < kMaxGroups ? nchunks : kMaxGroups;
     // a bucket is split into one part per XCD (workgroups are dealt to the 8
     // XCDs in turn), so that a line of records is completed through one L2
@@ -119,7 +126,7 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     const uint64_t nparts = (uint64_t)p.nbins * p.parts;
     p.part_cap = (uint32_t)((4ull * n + nparts - 1) / nparts) + 32;
     p.nzero = 1 + p.nbins + p.nbins * p.parts;
-    p.lds_aggregate = (size_t)kCap * 36 + (size_t)p.nbins * 8 + (4 + 2 * kMaxSteps) * 4;
+    p.lds_aggregate = (size_t)kCap * 36 + (size_t)p.nbins * 8 + (4 + kMaxSteps) * 4 + (size_t)p.chunk * 2;
     const uint32_t words = p.bin_shift > 5 ? 1u << (p.bin_shift - 5) : 1u;
     p.lds_reduce = (size_t)kCells * 32 + (size_t)words * 8;
     p.off_cnt = 0;
@@ -248,33 +255,35 @@ constexpr uint32_t kAlone = 0xffffu, kFlagged = 0x8000u;
 // kKeys: keys are built here from positions and normals (fk) and the flags
 // are outputs only; otherwise key[] and flags[] come from pf_build_keys.
 //
-// Bound by the vertex phase's VALU issue and by the latencies of a window's
-// chain (claim, bucket places) with two workgroups of 16 waves on a CU.  A
-// workgroup takes chunks of `steps` x 1024 consecutive vertices and goes
-// through a chunk in steps of one vertex per thread.  The steps are gathered
-// into windows: a window ends when the next step's valid vertices might not
-// find room in the LDS table any more (more than kLimit entries in use), so
-// coherent streams merge over 4096 vertices, while streams of mostly
-// distinct keys (small images, bounces, shuffled keys) flush as often as the
-// table needs.
+// Bound by memory requests: the claims fetch a 128-byte line for each group's
+// 4-byte probe (without them 1920x1080x3 took 84 us of 118, 3840x2160x4 476 of
+// 655), the record writes cost 24 and 105 us, the key arithmetic nothing.  A
+// workgroup takes chunks of `chunk` consecutive vertices, lists a chunk's valid
+// ones in LDS (bounce segments keep one vertex in four; 138 -> 124 us and 711
+// -> 659 us at the two sizes above) and goes through the list in steps of one
+// vertex per thread.  The steps are gathered into windows: a window ends when
+// the next step's vertices might not find room in the LDS table any more (more
+// than kLimit entries in use), so coherent streams merge over 4096 vertices,
+// while streams of mostly distinct keys (small images, bounces, shuffled keys)
+// flush as often as the table needs.
 template <bool kKeys>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void aggregate_kernel(
     Tab t, const uint64_t *__restrict__ key, const float *__restrict__ r, const float *__restrict__ g,
     const float *__restrict__ b, uint8_t *__restrict__ flags, uint32_t *__restrict__ slot_out, uint32_t n,
-    uint32_t steps, Buckets bk, uint32_t *__restrict__ ticket, FusedKeys fk) {
+    uint32_t chunk, Buckets bk, uint32_t *__restrict__ ticket, FusedKeys fk) {
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned long long *lkey = reinterpret_cast<unsigned long long *>(lds);
     unsigned long long *ls0 = lkey + kCap, *ls1 = ls0 + kCap, *ls2 = ls1 + kCap;
     uint32_t *lcnt = reinterpret_cast<uint32_t *>(ls2 + kCap);  // count, then the group's slot
     uint32_t *taken = lcnt + kCap;      // [nbins] places the window takes in each bin
     uint32_t *place = taken + bk.nbins;  // [nbins] the first of them
-    uint32_t *misc = place + bk.nbins;  // [0] overflowed vertices, [1] the next chunk
+    uint32_t *misc = place + bk.nbins;  // [0] overflowed vertices, [1] the next chunk, [2] valid vertices
     uint32_t *created = misc + 4;       // [kMaxSteps] LDS entries created by each step of the chunk
-    uint32_t *nvalid = created + kMaxSteps;  // [kMaxSteps] valid vertices of each step
+    uint16_t *list = reinterpret_cast<uint16_t *>(created + kMaxSteps);  // the chunk's valid vertices
     const uint32_t tid = threadIdx.x;
     const uint32_t part = blockIdx.x % bk.parts;
     for (uint32_t k = tid; k < bk.nbins; k += kT) taken[k] = 0;
-    if (tid < 4 + 2 * kMaxSteps) misc[tid] = 0;
+    if (tid < 4 + kMaxSteps) misc[tid] = 0;
     for (uint32_t j = tid; j < kCap; j += kT) {
         lkey[j] = kEmpty;
         ls0[j] = 0;
@@ -283,58 +292,72 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
         lcnt[j] = 0;
     }
     __syncthreads();
-    // the thread's part of the PCG32 states of its vertices: vertex i0 + tid
-    // has F + E (i0 + tid), and the uniform F + E i0 costs no vector work
     const PcgJump jp(fk.a.seed, fk.a.idx_base);
-    uint64_t pe[3];
+    const uint32_t nchunks = (n + chunk - 1) / chunk;
+    // the valid bytes (or input flags) of a chunk's vertices, loaded ...
+    auto load_live = [&](uint32_t ci, uint32_t raw[kMaxSteps]) {
+        const uint32_t c0 = ci * chunk, i1 = ci < nchunks ? min(n, c0 + chunk) : 0u;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) pe[k] = jp.E[k] * tid;
-    auto random3 = [&](uint32_t i0, uint32_t rnd[3]) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) rnd[k] = PcgJump::permute(jp.F[k] + jp.E[k] * (uint64_t)i0 + pe[k]);
-    };
-    const uint32_t nchunks = (n + steps * kT - 1) / (steps * kT);
-    // chunks differ in cost (coherent, incoherent or empty parts of the
-    // stream): a workgroup takes the next one when it is done
-    uint32_t ci = blockIdx.x;
-    while (ci < nchunks) {
-        uint32_t next_chunk = 0;
-        if (tid == 0) next_chunk = gridDim.x + atomicAdd(ticket, 1u);
-        const uint32_t c0 = ci * steps * kT;
-        const uint32_t nsteps = min(steps, (n - c0 + kT - 1) / kT);
-        // the valid bytes (or input flags) of the chunk first: masked
-        // vertices (sky, escaped paths) read nothing more
-        uint32_t live = 0;
-        for (uint32_t u = 0; u < nsteps; ++u) {
+        for (uint32_t u = 0; u < kMaxSteps; ++u) {
             const uint32_t i = c0 + u * kT + tid;
-            bool v = i < n;
-            if constexpr (kKeys)
-                v = v && (fk.valid == nullptr || fk.valid[i] != 0);
-            else
-                v = v && flags[i] == 0;
-            live |= (v ? 1u : 0u) << u;
+            raw[u] = kKeys ? 0u : 1u;
+            if (i < i1) raw[u] = kKeys ? (fk.valid ? fk.valid[i] : 1u) : flags[i];
         }
-        for (uint32_t u = 0; u < nsteps; ++u) {
-            const uint64_t m = __ballot((live >> u) & 1u);
-            if ((tid & 63) == 0 && m) atomicAdd(&nvalid[u], (uint32_t)__popcll(m));
+    };
+    // ... and taken as one bit per step
+    auto live_bits = [&](const uint32_t raw[kMaxSteps]) -> uint32_t {
+        uint32_t m = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kMaxSteps; ++u) m |= ((raw[u] != 0) == kKeys ? 1u : 0u) << u;
+        return m;
+    };
+    // chunks differ in cost (coherent, incoherent or empty parts of the
+    // stream): after its first two a workgroup takes the next one there is.
+    // It draws a chunk's number while it works on the chunk before the last
+    // (drawn by every workgroup at the launch's start, the tickets' atomics on
+    // one address held all of them up for 6 us), and reads its valid bytes
+    // before the chunk before it ends.
+    uint32_t ci = blockIdx.x, next = blockIdx.x + gridDim.x, drawn = 0;
+    uint32_t raw[kMaxSteps];
+    load_live(ci, raw);
+    uint32_t live = live_bits(raw);
+    while (ci < nchunks) {
+        const uint32_t c0 = ci * chunk, i1 = min(n, c0 + chunk);
+        // masked vertices (sky, escaped paths) read nothing more and get
+        // their outputs here
+#pragma unroll
+        for (uint32_t u = 0; u < kMaxSteps; ++u) {
+            const uint32_t i = c0 + u * kT + tid;
+            const bool v = (live >> u) & 1u;
+            const uint32_t at = wave_reserve(&misc[2], v);
+            if (v) {
+                list[at] = (uint16_t)(u * kT + tid);
+            } else if (i < i1) {
+                if (kKeys) flags[i] = PF_V_INVALID;
+                if (kKeys && fk.key_out) fk.key_out[i] = 0;
+                slot_out[i] = kNoSlot;
+            }
         }
+        __syncthreads();
+        const uint32_t nlive = misc[2], nsteps = (nlive + kT - 1) / kT;
         uint32_t w0 = 0;  // the window's first step
-        while (w0 < nsteps) {
+        do {
             uint64_t code = 0;  // 16 bits per step
-            uint32_t used = 0;  // entries in use, at most (exact after a barrier)
             uint32_t u = w0;
-            bool synced;
-            do {
-                const uint32_t i0 = c0 + u * kT, i = i0 + tid;
-                uint32_t c = kKeys ? kFlagged | PF_V_INVALID : kFlagged;
-                uint64_t k = 0;
+            while (u < nsteps) {
+                const uint32_t l = u * kT + tid;
+                uint32_t c = kFlagged;
                 bool fresh = false;
-                if ((live >> u) & 1u) {
+                if (l < nlive) {
+                    const uint32_t i = c0 + list[l];
                     const VertexIn<kKeys> in = load_vertex<kKeys>(fk, key, r, g, b, i);
                     uint32_t rnd[3] = {0, 0, 0};
-                    if constexpr (kKeys) random3(i0, rnd);
+                    if constexpr (kKeys)
+                        for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
+                    uint64_t k;
                     int64_t q0, q1, q2;
                     c = vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
+                    if (kKeys && fk.key_out) fk.key_out[i] = k;
                     if (c == 0) {
                         const int e = lds_insert(lkey, kCap, k, fresh);
                         if (e >= 0) {
@@ -350,27 +373,20 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                         c |= kFlagged;
                     }
                 }
-                if (kKeys && fk.key_out && i < n) fk.key_out[i] = k;
                 const uint64_t m = __ballot(fresh);
                 if ((tid & 63) == 0 && m) atomicAdd(&created[u], (uint32_t)__popcll(m));
                 code |= (uint64_t)c << (16 * u);
-                synced = false;
-                const bool first = u == 0;
                 ++u;
                 if (u == nsteps) break;
-                // go on while the next step's vertices are sure to find room;
-                // the counters are read after a barrier, only when the bound
-                // does not tell already (every thread decides alike)
-                if (!first && used + nvalid[u - 1] + nvalid[u] <= kLimit) {
-                    used += nvalid[u - 1];
-                    continue;
-                }
+                // go on while the next step's vertices are sure to find room
+                const uint32_t next = min(nlive - u * kT, (uint32_t)kT);
+                if ((u - w0) * kT + next <= kLimit) continue;
                 __syncthreads();
-                synced = true;
-                used = 0;
+                uint32_t used = 0;
                 for (uint32_t v = w0; v < u; ++v) used += created[v];
-            } while (used + nvalid[u] <= kLimit);
-            if (!synced) __syncthreads();
+                if (used + next > kLimit) break;
+            }
+            __syncthreads();
             // one probe / claim per group; a thread's
             // entries issue their home-slot loads, then their compare-and-swaps
             // on empty home slots, before either result is needed
@@ -379,7 +395,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 #pragma unroll
             for (uint32_t v = 0; v < kFlush; ++v) {
                 const uint32_t j = v * kT + tid;
-                gk[v] = lkey[j];
+                gk[v] = j < kCap ? lkey[j] : kEmpty;
                 fs[v] = 0;
                 ff[v] = 0;
                 fcur[v] = 0;
@@ -429,7 +445,9 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                                                      __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
             for (uint32_t v = w0; v < u; ++v) {
-                const uint32_t i0 = c0 + v * kT, i = i0 + tid;
+                const uint32_t l = v * kT + tid;
+                if (l >= nlive) break;
+                const uint32_t i = c0 + list[l];
                 const uint32_t c = (uint32_t)(code >> (16 * v)) & 0xffffu;
                 uint32_t s = kNoSlot, f = 0;
                 if (c < kFlagged) {
@@ -438,7 +456,8 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 } else if (c == kAlone) {  // no room in the LDS table: a group of its own
                     const VertexIn<kKeys> in = load_vertex<kKeys>(fk, key, r, g, b, i);
                     uint32_t rnd[3] = {0, 0, 0};
-                    if constexpr (kKeys) random3(i0, rnd);
+                    if constexpr (kKeys)
+                        for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
                     uint64_t k;
                     int64_t q0, q1, q2;
                     vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
@@ -456,18 +475,27 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 } else {
                     f = c & 0xffu;
                 }
-                if (i < n) {
-                    if (kKeys || f) flags[i] = (uint8_t)f;
-                    slot_out[i] = s;
-                }
+                if (kKeys || f) flags[i] = (uint8_t)f;
+                slot_out[i] = s;
             }
             if (want) {
                 place[tid] = first_place;
                 taken[tid] = 0;
             }
-            if (tid < 2 * kMaxSteps && u == nsteps) created[tid] = 0;  // and nvalid, for the next chunk
-            if (tid == 0) misc[1] = next_chunk;
+            if (u == nsteps) {  // for the next chunk
+                if (tid < kMaxSteps) created[tid] = 0;
+                if (tid == 0) {
+                    if (ci >= gridDim.x) misc[1] = 2 * gridDim.x + drawn;
+                    misc[2] = 0;
+                }
+            }
             __syncthreads();
+            if (u == nsteps) {
+                const uint32_t after = ci < gridDim.x ? next : misc[1];
+                load_live(after, raw);
+                if (tid == 0) drawn = atomicAdd(ticket, 1u);
+                ci = after;
+            }
 #pragma unroll
             for (uint32_t v = 0; v < kFlush; ++v) {
                 const uint32_t j = v * kT + tid;
@@ -484,9 +512,9 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 lcnt[j] = 0;
             }
             w0 = u;
-            if (w0 == nsteps) ci = misc[1];
+            if (u == nsteps) live = live_bits(raw);
             __syncthreads();
-        }
+        } while (w0 < nsteps);
     }
     if (tid == 0 && misc[0]) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], misc[0]);
 }
@@ -505,11 +533,17 @@ struct Blend {
 // its table).  More than kCells cells take several passes over the records.
 // The exclusive owner then adds the sums to the cells and sets the occupancy
 // bits of its words.
+// Bound by its chain of latencies (counts, records, cells, the previous table's
+// slots) where bins are small and by LDS atomics and record reads where they are
+// large, so two workgroups of 512 threads share a CU, a thread's first cells are
+// requested before the records are summed, and records are read a batch ahead
+// (256 bins and one workgroup of 1024 threads a CU: 3840x2160x4 190 -> 134 us, 8M
+// incoherent keys 206 -> 145 us, 1920x1080x3 40 -> 38 us).
 // kBlend: it also computes the temporal values of the cells (which are final:
 // every record of a slot is in the slot's bin), as temporal_word does for one
 // bitmap word.
 template <bool kBlend = false, bool kHasPrev = false, bool kIntegrate = false>
-__global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl) {
+__global__ __launch_bounds__(kR) __attribute__((amdgpu_waves_per_eu(4, 4))) void reduce_kernel(Tab t, Buckets bk, Blend bl) {
     extern __shared__ unsigned long long lred[];
     unsigned long long *sum0 = lred, *sum1 = lred + kCells, *sum2 = lred + 2 * kCells;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(lred + 3 * kCells);
@@ -536,9 +570,9 @@ __global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl)
 #pragma unroll
     for (uint32_t x = 0; x < kMaxParts; ++x) {
         m += seg[x];
-        end[x] = m;
+        end[x] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
     }
-    auto record = [&](uint32_t j) -> uint4 {
+    auto record = [&](uint32_t j) -> const uint4 * {
         uint32_t x = 0, from = 0;
 #pragma unroll
         for (uint32_t y = 0; y + 1 < kMaxParts; ++y)
@@ -546,27 +580,30 @@ __global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl)
                 x = y + 1;
                 from = end[y];
             }
-        return bk.rec[((size_t)bin * bk.parts + x) * bk.part_cap + (j - from)];
+        return bk.rec + ((size_t)bin * bk.parts + x) * bk.part_cap + (j - from);
     };
-    auto mark = [&](const uint4 &q) {
-        const uint32_t loc = q.x & in_bin;
+    auto load_records = [&](uint32_t j0, uint4 (&q)[kHold]) {
+#pragma unroll
+        for (uint32_t u = 0; u < kHold; ++u)
+            if (j0 + u * kR + tid < m) q[u] = *record(j0 + u * kR + tid);
+    };
+    auto mark = [&](uint32_t word) {
+        const uint32_t loc = word & in_bin;
         atomicOr(&bits[loc >> 5], 1u << (loc & 31));
     };
     uint4 held[kHold];
+    load_records(0, held);
 #pragma unroll
     for (uint32_t u = 0; u < kHold; ++u)
-        if (u * kR + tid < m) held[u] = record(u * kR + tid);
+        if (u * kR + tid < m) mark(held[u].x);
+    for (uint32_t j0 = kHold * kR; j0 < m; j0 += kMark * kR) {
+        uint32_t word[kMark];
 #pragma unroll
-    for (uint32_t u = 0; u < kHold; ++u)
-        if (u * kR + tid < m) mark(held[u]);
-    for (uint32_t j0 = kHold * kR; j0 < m; j0 += kHold * kR) {
-        uint4 q[kHold];
+        for (uint32_t u = 0; u < kMark; ++u)
+            if (j0 + u * kR + tid < m) word[u] = record(j0 + u * kR + tid)->x;
 #pragma unroll
-        for (uint32_t u = 0; u < kHold; ++u)
-            if (j0 + u * kR + tid < m) q[u] = record(j0 + u * kR + tid);
-#pragma unroll
-        for (uint32_t u = 0; u < kHold; ++u)
-            if (j0 + u * kR + tid < m) mark(q[u]);
+        for (uint32_t u = 0; u < kMark; ++u)
+            if (j0 + u * kR + tid < m) mark(word[u]);
     }
     __syncthreads();
     // set bits before each word: a thread takes `per` consecutive words
@@ -612,6 +649,24 @@ __global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl)
             for (uint32_t v = bits[w]; v; v &= v - 1, ++at)
                 if (at - c0 < nc) list[at - c0] = w * 32 + (uint32_t)__builtin_ctz(v);
         __syncthreads();
+        // a thread's first cells are requested before the records are summed
+        struct CellIn {
+            uint4 lo, hi;
+            uint64_t key;
+        };
+        auto load_cells = [&](uint32_t k0, CellIn (&in)[kPair]) {
+#pragma unroll
+            for (int v = 0; v < kPair; ++v) {
+                const uint32_t k = k0 + v * kR + tid;
+                if (k >= nc) continue;
+                const uint4 *w4 = t.words_at(base + list[k]);  // 4 sixteen-byte words per slot record
+                in[v].lo = w4[0];
+                in[v].hi = w4[1];
+                if constexpr (kBlend && kHasPrev) in[v].key = (uint64_t)w4[2].x | (uint64_t)w4[2].y << 32;
+            }
+        };
+        CellIn in[kPair];
+        load_cells(0, in);
         auto add = [&](const uint4 &q) {
             const uint32_t loc = q.x & in_bin;
             const uint32_t k = before[loc >> 5] + (uint32_t)__popc(bits[loc >> 5] & ((1u << (loc & 31)) - 1u)) - c0;
@@ -633,45 +688,56 @@ __global__ __launch_bounds__(kR) void reduce_kernel(Tab t, Buckets bk, Blend bl)
             atomicAdd(&sum1[k], v1);
             atomicAdd(&sum2[k], v2);
         };
+        // the records after those held are one batch ahead of the sums
+        uint4 q[kHold];
 #pragma unroll
-        for (uint32_t u = 0; u < kHold; ++u)
-            if (u * kR + tid < m) add(held[u]);
-        for (uint32_t j0 = kHold * kR; j0 < m; j0 += kHold * kR) {
-            uint4 q[kHold];
-#pragma unroll
-            for (uint32_t u = 0; u < kHold; ++u)
-                if (j0 + u * kR + tid < m) q[u] = record(j0 + u * kR + tid);
+        for (uint32_t u = 0; u < kHold; ++u) q[u] = held[u];
+        for (uint32_t j0 = 0; j0 < m; j0 += kHold * kR) {
+            uint4 ahead[kHold];
+            load_records(j0 + kHold * kR, ahead);
 #pragma unroll
             for (uint32_t u = 0; u < kHold; ++u)
                 if (j0 + u * kR + tid < m) add(q[u]);
+#pragma unroll
+            for (uint32_t u = 0; u < kHold; ++u) q[u] = ahead[u];
         }
         __syncthreads();
-        for (uint32_t k = tid; k < nc; k += kR) {
-            const uint32_t sl[1] = {base + list[k]};
-            uint4 *w4 = t.words_at(sl[0]);  // 4 sixteen-byte words per slot record
-            const uint4 lo = w4[0], hi = w4[1];
-            pf_cell cl;
-            cl.fp = lo.x;
-            cl.count = lo.y + cnt[k];
-            const uint64_t s0 = ((uint64_t)lo.z | (uint64_t)lo.w << 32) + sum0[k];
-            const uint64_t s1 = ((uint64_t)hi.x | (uint64_t)hi.y << 32) + sum1[k];
-            const uint64_t s2 = ((uint64_t)hi.z | (uint64_t)hi.w << 32) + sum2[k];
-            uint64_t kw = 0;
-            if constexpr (kBlend && kHasPrev) kw = t.key_at(sl[0]);
-            w4[0] = make_uint4(cl.fp, cl.count, (uint32_t)s0, (uint32_t)(s0 >> 32));
-            w4[1] = make_uint4((uint32_t)s1, (uint32_t)(s1 >> 32), (uint32_t)s2, (uint32_t)(s2 >> 32));
-            if constexpr (kBlend) {
-                cl.sum[0] = (int64_t)s0;
-                cl.sum[1] = (int64_t)s1;
-                cl.sum[2] = (int64_t)s2;
-                const bool has[1] = {true};
-                const uint64_t key[1] = {kw};
-                const uint32_t fp[1] = {cl.fp}, n[1] = {cl.count};
-                uint32_t keep[1] = {kIntegrate ? min(cl.count, bl.cap) : cl.count};
-                float v[1][3] = {{t.average(cl, 0), t.average(cl, 1), t.average(cl, 2)}};
-                hits += blend_cells<kHasPrev, kIntegrate, 1, false>(t, bl.prev, sl, has, key, fp, v, n, keep, bl.alpha,
-                                                                    bl.beta, bl.cap);
+        for (uint32_t k0 = 0; k0 < nc; k0 += kPair * kR) {
+            if (k0) load_cells(k0, in);
+            uint32_t sl[kPair], fp[kPair], n[kPair], keep[kPair];
+            uint64_t key[kPair];
+            bool has[kPair];
+            float v[kPair][3];
+#pragma unroll
+            for (int w = 0; w < kPair; ++w) {
+                const uint32_t k = k0 + w * kR + tid;
+                has[w] = k < nc;
+                if (!has[w]) continue;
+                sl[w] = base + list[k];
+                pf_cell cl;
+                cl.fp = in[w].lo.x;
+                cl.count = in[w].lo.y + cnt[k];
+                const uint64_t s0 = ((uint64_t)in[w].lo.z | (uint64_t)in[w].lo.w << 32) + sum0[k];
+                const uint64_t s1 = ((uint64_t)in[w].hi.x | (uint64_t)in[w].hi.y << 32) + sum1[k];
+                const uint64_t s2 = ((uint64_t)in[w].hi.z | (uint64_t)in[w].hi.w << 32) + sum2[k];
+                uint4 *w4 = t.words_at(sl[w]);
+                w4[0] = make_uint4(cl.fp, cl.count, (uint32_t)s0, (uint32_t)(s0 >> 32));
+                w4[1] = make_uint4((uint32_t)s1, (uint32_t)(s1 >> 32), (uint32_t)s2, (uint32_t)(s2 >> 32));
+                if constexpr (kBlend) {
+                    cl.sum[0] = (int64_t)s0;
+                    cl.sum[1] = (int64_t)s1;
+                    cl.sum[2] = (int64_t)s2;
+                    if constexpr (kHasPrev) key[w] = in[w].key;
+                    fp[w] = cl.fp;
+                    n[w] = cl.count;
+                    keep[w] = kIntegrate ? min(cl.count, bl.cap) : cl.count;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) v[w][c] = t.average(cl, c);
+                }
             }
+            if constexpr (kBlend)
+                hits += blend_cells<kHasPrev, kIntegrate, kPair, false>(t, bl.prev, sl, has, key, fp, v, n, keep,
+                                                                        bl.alpha, bl.beta, bl.cap);
         }
     }
     if constexpr (kBlend && kHasPrev) {
@@ -719,7 +785,7 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
     bk.part_cap = p.part_cap;
     static bool attrs = false;  // dynamic LDS above 64 KB needs the attribute, set once per function
     if (!attrs) {
-        constexpr int kAggregateLds = kCap * 36 + kMaxBins * 8 + (4 + 2 * kMaxSteps) * 4;
+        constexpr int kAggregateLds = kCap * 36 + kMaxBins * 8 + (4 + kMaxSteps) * 4 + kMaxSteps * kT * 2;
         constexpr int kReduceLds = kCells * 32 + (8 << (kMaxLog2BinSlots - 5));
         static_assert(kAggregateLds <= 80 * 1024, "two workgroups of aggregate share a CU");
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false>),
@@ -734,7 +800,7 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
         attrs = true;
     }
     zero_kernel<<<1, kT, 0, st>>>(ticket, p.nzero);
-    aggregate_kernel<kKeys><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n, p.steps, bk,
+    aggregate_kernel<kKeys><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n, p.chunk, bk,
                                                                    ticket, fk);
     const Blend none{};
     const Blend &bl = blend ? *blend : none;

@@ -105,15 +105,16 @@ struct PcgJump {
 // floor of the binary32 quotient RN(x / h) that Algorithm 1 quantises, for
 // h = s 2^l, given r = RN(1/s) 2^-l.  t = RN(x r) is within 2.0001 u |t| of
 // the exact quotient y (u = 2^-24) and RN(y) within u |y| of y, so when no
-// integer lies within 4 u |t| of t, floor(RN(y)) = floor(t); otherwise (or
-// when t is not finite) the IEEE division decides.
-__device__ __forceinline__ float floor_quotient(float x, float h, float r) {
+// integer lies within 4 u |t| of t, floor(RN(y)) = floor(t).  x = 0 (every
+// vertex of an axis-aligned plane through the origin) has the quotient 0 where
+// t is 0 (r is finite, so h is not 0).  Returns false where the IEEE division
+// has to decide (or t is not finite).
+__device__ __forceinline__ bool floor_by_reciprocal(float x, float r, float &f) {
     const float t = x * r;
-    const float f = floorf(t);
+    f = floorf(t);
     const float frac = t - f;
     const float m = 2.38418579e-7f * fabsf(t);  // 4 u |t|
-    if (frac > m && 1.0f - frac > m) return f;
-    return floorf(x / h);
+    return (frac > m && 1.0f - frac > m) || (x == 0.0f && t == 0.0f);
 }
 
 // MurmurHash3 64-bit finaliser: the home index hash.

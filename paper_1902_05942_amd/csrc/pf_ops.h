@@ -46,15 +46,19 @@ __device__ __forceinline__ uint8_t vertex_key(const float x[3], const float nr[3
     const int lp = level_of_detail(cam[0], cam[1], cam[2], xp[0], xp[1], xp[2]);
     const float hp = ldexpf(s, lp);
     const float rp = ldexpf(inv_s, -lp);
-    bool inrange = true;
-    int32_t q[3];
+    float f[3];
+    bool exact = true;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const float f = floor_quotient(xp[c], hp, rp);
-        inrange = inrange && (f > -kCellIndexLimit) && (f < kCellIndexLimit);  // |x~| < 2^16
-        q[c] = inrange ? (int32_t)f : 0;
+    for (int c = 0; c < 3; ++c) exact = floor_by_reciprocal(xp[c], rp, f[c]) && exact;
+    if (!exact) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) f[c] = floorf(xp[c] / hp);
     }
+    bool inrange = true;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) inrange = inrange && fabsf(f[c]) < kCellIndexLimit;  // |x~| < 2^16
     if (!inrange) return PF_V_KEYRANGE;
+    const int32_t q[3] = {(int32_t)f[0], (int32_t)f[1], (int32_t)f[2]};
     const uint32_t code = normal_class(nr[0]) | (normal_class(nr[1]) << 2) | (normal_class(nr[2]) << 4);
     key = (uint64_t)(uint32_t)(q[0] + 65536) | ((uint64_t)(uint32_t)(q[1] + 65536) << 17) |
           ((uint64_t)(uint32_t)(q[2] + 65536) << 34) | ((uint64_t)(uint32_t)(lp + 16) << 51) | ((uint64_t)code << 56);
@@ -67,24 +71,24 @@ __device__ __forceinline__ uint8_t vertex_key(const float x[3], const float nr[3
 // (non-finite) or PF_V_RADRANGE (|c 2^F| >= 2^62).
 __device__ __forceinline__ uint8_t fixed_point(float c0, float c1, float c2, int frac_bits, int64_t &q0, int64_t &q1,
                                                int64_t &q2) {
+    const float s0 = ldexpf(c0, frac_bits), s1 = ldexpf(c1, frac_bits), s2 = ldexpf(c2, frac_bits);
+    const float lim32 = 2147483648.0f;  // 2^31
+    // the active lanes convert through int32 when all of them can (the usual
+    // magnitudes, nothing infinite or NaN): the same integers, a quarter of
+    // the instructions, and no other test is needed
+    if (__builtin_expect(__ballot(!(fabsf(s0) < lim32 && fabsf(s1) < lim32 && fabsf(s2) < lim32)) == 0, 1)) {
+        q0 = (int32_t)rintf(s0);
+        q1 = (int32_t)rintf(s1);
+        q2 = (int32_t)rintf(s2);
+        return 0;
+    }
     q0 = q1 = q2 = 0;
     if (!(isfinite(c0) && isfinite(c1) && isfinite(c2))) return PF_V_INVALID;
-    const float s0 = ldexpf(c0, frac_bits), s1 = ldexpf(c1, frac_bits), s2 = ldexpf(c2, frac_bits);
     const float lim = 4611686018427387904.0f;  // 2^62
     if (!(fabsf(s0) < lim && fabsf(s1) < lim && fabsf(s2) < lim)) return PF_V_RADRANGE;
-    // the active lanes convert through int32 when all of them can (the
-    // usual magnitudes): the same integers, a quarter of the instructions
-    const float r0 = rintf(s0), r1 = rintf(s1), r2 = rintf(s2);
-    const float lim32 = 2147483648.0f;  // 2^31
-    if (__builtin_expect(__ballot(!(fabsf(r0) < lim32 && fabsf(r1) < lim32 && fabsf(r2) < lim32)) == 0, 1)) {
-        q0 = (int32_t)r0;
-        q1 = (int32_t)r1;
-        q2 = (int32_t)r2;
-    } else {
-        q0 = (int64_t)r0;
-        q1 = (int64_t)r1;
-        q2 = (int64_t)r2;
-    }
+    q0 = (int64_t)rintf(s0);
+    q1 = (int64_t)rintf(s1);
+    q2 = (int64_t)rintf(s2);
     return 0;
 }
 
