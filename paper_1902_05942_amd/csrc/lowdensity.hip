@@ -5,11 +5,17 @@
 // count is below the threshold; the listed voxels are then searched, each
 // writing its pooled average into its temporal value, which the lookup with
 // use_blend returns.
-//   kMode 0, neighbourhood search: 8 lanes per voxel, lane l searching the
-//     keys of candidates 4l .. 4l+3 of the 27 voxels (dx, dy, dz) =
+//   kMode 0, neighbourhood search, over the 27 voxels (dx, dy, dz) =
 //     (c % 3 - 1, c / 3 % 3 - 1, c / 9 - 1) away at the same level and normal
-//     class, its four searches in flight together; the partial sums of the
-//     8 lanes are added with cross-lane adds;
+//     class.  A workgroup takes up to 256 of its listed voxels at a time
+//     through steps whose loads do not depend on each other: own cells and
+//     keys; the home slots' occupancy bits of all 26 neighbours of all voxels;
+//     the slots whose bit is set, listed in LDS, so that every lane probes one;
+//     the quotients, one component a lane.  Bound by the latency of these
+//     steps: with 8 lanes a voxel going through key, bits, fingerprint, key and
+//     cell one voxel after the other, the waves waited 80% of their time
+//     (1280x720x3, 134k sparse voxels with 4.7 present neighbours: 64 us, now
+//     44 us);
 //   kMode 1, similar normals along the probe run: one lane per voxel.  The
 //     key's home slot does not depend on its normal class, so the voxels at
 //     its position and level with other normals lie in its probe run, from
@@ -23,6 +29,7 @@
 // absent.  Sums and counts are pooled as integers (exact, order-free) and
 // divided once as the lookup divides: (float)((double)S * 2^-F / (double)N).
 #include "pf_kernels.h"
+#include "pf_merge.h"
 #include "pf_ops.h"
 
 namespace pfk {
@@ -30,7 +37,8 @@ namespace pfk {
 constexpr int kLdThreads = 256;
 constexpr uint32_t kLdWords = kLdThreads / 4;  // four lanes per occupancy word, 8 slots each
 constexpr uint32_t kLdSlots = kLdWords * 32;
-constexpr uint32_t kCubeLanes = 8, kCubePer = 4;  // 8 x 4 >= 27 candidates per voxel
+constexpr uint32_t kBatch = kLdThreads;  // voxels whose neighbours are searched together
+constexpr uint32_t kWork = 2048;         // slots to probe listed at a time
 constexpr uint64_t kCoordMask = (1ull << 51) - 1;
 
 __device__ __forceinline__ int class_sign(uint64_t key, int axis) {
@@ -58,58 +66,107 @@ __device__ __forceinline__ void store_pooled(const Tab &t, uint32_t s, uint32_t 
     v[2] = cell_average((int64_t)a2, n, t.frac_bits);
 }
 
-// Neighbourhood search for voxel s (key K) by this lane's candidates.
-__device__ __forceinline__ void search_cube(const Tab &t, uint32_t s, uint64_t K, uint32_t lane, uint32_t &n,
-                                            uint64_t &a0, uint64_t &a1, uint64_t &a2) {
-    uint64_t k2[kCubePer];
-    uint32_t f[kCubePer], p[kCubePer], found[kCubePer];
-    bool act[kCubePer];
+// Candidate c's key for the voxel with key K; false outside the key range.
+__device__ __forceinline__ bool neighbour_key(uint64_t K, uint32_t c, uint64_t &key) {
+    const int d[3] = {(int)(c % 3) - 1, (int)(c / 3 % 3) - 1, (int)(c / 9) - 1};
+    key = K & ~kCoordMask;
+    bool in = true;
 #pragma unroll
-    for (uint32_t u = 0; u < kCubePer; ++u) {
-        const uint32_t c = lane * kCubePer + u;
-        const int d[3] = {(int)(c % 3) - 1, (int)(c / 3 % 3) - 1, (int)(c / 9) - 1};
-        k2[u] = K & ~kCoordMask;
-        bool in = c < 27;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int x = (int)((K >> (17 * a)) & 0x1ffffu) - 65536 + d[a];
-            in = in && x > -65536 && x < 65536;
-            k2[u] |= (uint64_t)(uint32_t)(x + 65536) << (17 * a);
-        }
-        found[u] = (in && c == 13) ? s : kNoSlot;  // the voxel itself
-        act[u] = in && c != 13;
-        p[u] = act[u] ? home_of(k2[u], t.mask) : 0u;
-        f[u] = act[u] ? fingerprint_of(k2[u]) : 0u;
+    for (int a = 0; a < 3; ++a) {
+        const int x = (int)((K >> (17 * a)) & 0x1ffffu) - 65536 + d[a];
+        in = in && x > -65536 && x < 65536;
+        key |= (uint64_t)(uint32_t)(x + 65536) << (17 * a);
     }
-#pragma unroll
-    for (uint32_t u = 0; u < kCubePer; ++u) act[u] = act[u] && occupied(t, p[u]);
+    return in;
+}
+
+// Sums of a batch of voxels, in LDS.
+struct Pool {
+    unsigned long long key[kBatch], sum[3][kBatch];
+    uint32_t count[kBatch];
+    uint32_t nwork, slot[kWork];
+    uint16_t pair[kWork];  // voxel, candidate
+};
+
+// Probes for `key` from its (occupied) home slot p on and adds its cell to
+// voxel v's sums.  A slot's cell and key are one line, requested together; the
+// key decides (equal keys have equal fingerprints), an empty cell ends the run.
+__device__ __forceinline__ void pool_key(const Tab &t, Pool &P, uint32_t v, uint64_t key, uint32_t p) {
     for (uint32_t d = 0; d < t.max_probe; ++d) {
-        bool any = false;
+        const uint4 *w = t.words_at(p);
+        const uint4 lo = w[0], hi = w[1];
+        const uint64_t kk = t.key_at(p);
+        if (lo.x == 0) return;
+        if (kk == key) {
+            atomicAdd(&P.count[v], lo.y);
+            atomicAdd(&P.sum[0][v], (unsigned long long)lo.z | (unsigned long long)lo.w << 32);
+            atomicAdd(&P.sum[1][v], (unsigned long long)hi.x | (unsigned long long)hi.y << 32);
+            atomicAdd(&P.sum[2][v], (unsigned long long)hi.z | (unsigned long long)hi.w << 32);
+            return;
+        }
+        p = (p + 1) & t.mask;
+    }
+}
+
+// Neighbourhood search for the nb listed voxels.
+__device__ __forceinline__ void search_cubes(const Tab &t, Pool &P, const uint32_t *list, uint32_t nb) {
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) P.nwork = 0;
+    if (tid < nb) {
+        const uint4 *w = t.words_at(list[tid]);
+        const uint4 lo = w[0], hi = w[1];
+        P.key[tid] = t.key_at(list[tid]);
+        P.count[tid] = lo.y;
+        P.sum[0][tid] = (unsigned long long)lo.z | (unsigned long long)lo.w << 32;
+        P.sum[1][tid] = (unsigned long long)hi.x | (unsigned long long)hi.y << 32;
+        P.sum[2][tid] = (unsigned long long)hi.z | (unsigned long long)hi.w << 32;
+    }
+    __syncthreads();
+    // 32 lanes a voxel, one candidate each (27 of them; the voxel itself is in
+    // the sums); eight voxels a lane have their bits loaded together
+    const uint32_t c = tid & 31;
+    constexpr uint32_t kGroups = kLdThreads / 32, kTogether = 8;
+    for (uint32_t v0 = 0; v0 < nb; v0 += kGroups * kTogether) {
+        uint32_t home[kTogether], word[kTogether];
 #pragma unroll
-        for (uint32_t u = 0; u < kCubePer; ++u) any |= act[u];
-        if (!any) break;
-        uint32_t cur[kCubePer];
-        uint64_t kk[kCubePer];
+        for (uint32_t u = 0; u < kTogether; ++u) {
+            const uint32_t v = v0 + u * kGroups + (tid >> 5);
+            uint64_t key;
+            home[u] = kNoSlot;
+            word[u] = 0;
+            if (v < nb && c < 27 && c != 13 && neighbour_key(P.key[v], c, key)) {
+                home[u] = home_of(key, t.mask);
+                word[u] = t.occ[home[u] >> 5];
+            }
+        }
 #pragma unroll
-        for (uint32_t u = 0; u < kCubePer; ++u) cur[u] = act[u] ? t.cell_at(p[u]).fp : 0u;
-#pragma unroll
-        for (uint32_t u = 0; u < kCubePer; ++u) kk[u] = (act[u] && cur[u] == f[u]) ? t.key_at(p[u]) : 0ull;
-#pragma unroll
-        for (uint32_t u = 0; u < kCubePer; ++u) {
-            if (!act[u]) continue;
-            if (cur[u] == 0) {
-                act[u] = false;
-            } else if (cur[u] == f[u] && kk[u] == k2[u]) {
-                found[u] = p[u];
-                act[u] = false;
-            } else {
-                p[u] = (p[u] + 1) & t.mask;
+        for (uint32_t u = 0; u < kTogether; ++u) {
+            const uint32_t v = v0 + u * kGroups + (tid >> 5);
+            const bool want = (word[u] >> (home[u] & 31)) & 1u;
+            const uint32_t at = wave_reserve(&P.nwork, want);
+            if (!want) continue;
+            if (at < kWork) {
+                P.slot[at] = home[u];
+                P.pair[at] = (uint16_t)(v << 5 | c);
+            } else {  // the list is full: probed here
+                uint64_t key;
+                neighbour_key(P.key[v], c, key);
+                pool_key(t, P, v, key, home[u]);
             }
         }
     }
-#pragma unroll
-    for (uint32_t u = 0; u < kCubePer; ++u)
-        if (found[u] != kNoSlot) add_cell(t, found[u], n, a0, a1, a2);
+    __syncthreads();
+    for (uint32_t w = tid; w < min(P.nwork, kWork); w += kLdThreads) {
+        uint64_t key;
+        neighbour_key(P.key[P.pair[w] >> 5], P.pair[w] & 31u, key);
+        pool_key(t, P, P.pair[w] >> 5, key, P.slot[w]);
+    }
+    __syncthreads();
+    for (uint32_t x = tid; x < 3 * nb; x += kLdThreads) {
+        const uint32_t v = x / 3, k = x % 3;
+        reinterpret_cast<float *>(&t.blend_at(list[v]))[k] =
+            cell_average((int64_t)P.sum[k][v], P.count[v], t.frac_bits);
+    }
 }
 
 // Similar normals along the probe run of voxel s (key K), one lane.
@@ -170,22 +227,10 @@ __global__ __launch_bounds__(kLdThreads) void low_density_kernel(Tab t, uint32_t
         __syncthreads();
         const uint32_t m = nlist;
         if constexpr (kMode == 0) {
-            const uint32_t lane = threadIdx.x % kCubeLanes;
-            // the 8 lanes of a voxel share q, so they run the same trips
-            // and are all active for the cross-lane sums
-            for (uint32_t q = threadIdx.x / kCubeLanes; q < m; q += kLdThreads / kCubeLanes) {
-                const uint32_t s = list[q];
-                uint32_t n = 0;
-                uint64_t a0 = 0, a1 = 0, a2 = 0;
-                search_cube(t, s, t.key_at(s), lane, n, a0, a1, a2);
-#pragma unroll
-                for (uint32_t x = kCubeLanes / 2; x >= 1; x >>= 1) {
-                    n += (uint32_t)__shfl_xor((int)n, (int)x);
-                    a0 += (uint64_t)__shfl_xor((unsigned long long)a0, (int)x);
-                    a1 += (uint64_t)__shfl_xor((unsigned long long)a1, (int)x);
-                    a2 += (uint64_t)__shfl_xor((unsigned long long)a2, (int)x);
-                }
-                if (lane == 0) store_pooled(t, s, n, a0, a1, a2);
+            __shared__ Pool P;
+            for (uint32_t q = 0; q < m; q += kBatch) {
+                search_cubes(t, P, list + q, min(m - q, kBatch));
+                __syncthreads();  // the sums are rebuilt for the next voxels
             }
         } else {
             for (uint32_t q = threadIdx.x; q < m; q += kLdThreads) {
