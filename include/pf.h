@@ -200,7 +200,9 @@ pf_status pf_build_keys(const float *px, const float *py, const float *pz,
  * the lanes of each group of k consecutive threads of a 256-thread
  * workgroup that reach the same slot combine their contributions in LDS
  * first (they meet through 2k buckets indexed by the slot's low bits; a
- * lane whose bucket another slot took goes directly).
+ * lane whose bucket another slot took goes directly).  From 2^19 vertices on
+ * vertices that share a key are combined over up to 4096 valid vertices,
+ * whatever agg_width says.
  * slot_out (nullable): receives the slot of each vertex (0xffffffff if
  * flagged) so that pf_query_average can skip probing.
  * Several batches may be inserted before one lookup.

@@ -35,6 +35,7 @@
 // the insert costs, and a window of mostly distinct keys overflowed its LDS
 // table and sent its vertices to the table one by one.
 #include <mutex>
+#include <type_traits>
 
 #include "pf_kernels.h"
 #include "pf_merge.h"
@@ -51,6 +52,7 @@ constexpr uint32_t kFlush = 2;               // LDS entries per thread
 constexpr uint32_t kCap = 1920;              // LDS entries of a window
 constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
+constexpr uint32_t kMinWindowed = 1u << 19;  // vertices from which pf_insert_accumulate merges by windows
 constexpr uint32_t kMaxBins = 512, kMaxParts = 8;
 constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
 constexpr int kR = 512;                      // threads of reduce: two workgroups on a CU, all bins at once
@@ -92,6 +94,23 @@ struct Plan {
     uint32_t nzero;  // words from off_cnt on that start at zero: ticket, spill flags, bucket counts
 };
 
+// Steps of kT vertices spread over as many workgroups as there are, in chunks
+// of equal size; returns the steps.
+static uint32_t deal_chunks(uint32_t n, uint32_t &chunk, uint32_t &groups) {
+    const uint32_t nsteps = n ? (n + kT - 1) / kT : 1;
+    const uint32_t rounds = (nsteps + kMaxGroups * kMaxSteps - 1) / (kMaxGroups * kMaxSteps);
+    const uint32_t steps = (nsteps + kMaxGroups * rounds - 1) / (kMaxGroups * rounds);
+    chunk = steps * kT;
+    const uint32_t nchunks = (nsteps + steps - 1) / steps;
+    groups = nchunks < kMaxGroups ? nchunks : kMaxGroups;
+    return nsteps;
+}
+
+// LDS of aggregate for chunks of `chunk` vertices and nbins bins.
+static constexpr size_t aggregate_lds(uint32_t chunk, uint32_t nbins) {
+    return (size_t)kCap * 36 + (size_t)nbins * 8 + (4 + kMaxSteps) * 4 + (size_t)chunk * 2;
+}
+
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 Plan make_plan(uint32_t n, uint32_t log2_slots) {
@@ -110,14 +129,7 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     if (log2_bins > most) log2_bins = most;
     p.nbins = 1u << log2_bins;
     p.bin_shift = log2_slots - log2_bins;
-    // steps of kT vertices spread over as many workgroups as there are, in
-    // chunks of equal size
-    const uint32_t nsteps = n ? (n + kT - 1) / kT : 1;
-    const uint32_t rounds = (nsteps + kMaxGroups * kMaxSteps - 1) / (kMaxGroups * kMaxSteps);
-    const uint32_t steps = (nsteps + kMaxGroups * rounds - 1) / (kMaxGroups * rounds);
-    p.chunk = steps * kT;
-    const uint32_t nchunks = (nsteps + steps - 1) / steps;
-    p.groups = nchunks < kMaxGroups ? nchunks : kMaxGroups;
+    const uint32_t nsteps = deal_chunks(n, p.chunk, p.groups);
     // a bucket is split into one part per XCD (workgroups are dealt to the 8
     // XCDs in turn), so that a line of records is completed through one L2
     p.parts = nsteps >= 64 ? kMaxParts : 1;
@@ -126,7 +138,7 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     const uint64_t nparts = (uint64_t)p.nbins * p.parts;
     p.part_cap = (uint32_t)((4ull * n + nparts - 1) / nparts) + 32;
     p.nzero = 1 + p.nbins + p.nbins * p.parts;
-    p.lds_aggregate = (size_t)kCap * 36 + (size_t)p.nbins * 8 + (4 + kMaxSteps) * 4 + (size_t)p.chunk * 2;
+    p.lds_aggregate = aggregate_lds(p.chunk, p.nbins);
     const uint32_t words = p.bin_shift > 5 ? 1u << (p.bin_shift - 5) : 1u;
     p.lds_reduce = (size_t)kCells * 32 + (size_t)words * 8;
     p.off_cnt = 0;
@@ -135,9 +147,17 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     return p;
 }
 
-// Probe / claim like find_or_claim, without the occupancy bit (set by the
-// reduce pass, which owns the bitmap words of its bin), from probe d0 at
-// slot s onwards.
+// A cell just claimed: its key and (kOcc; else reduce sets it, which owns the
+// bitmap words of its bin) its occupancy bit.
+template <bool kOcc>
+__device__ __forceinline__ void claimed(const Tab &t, uint32_t s, uint64_t key) {
+    t.key_at(s) = key;
+    if constexpr (kOcc)
+        __hip_atomic_fetch_or(&t.occ[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Probe / claim like find_or_claim from probe d0 at slot s onwards.
+template <bool kOcc>
 __device__ __forceinline__ uint32_t claim_next(const Tab &t, uint64_t key, uint32_t f, uint32_t s, uint32_t d0) {
     for (uint32_t d = d0; d < t.max_probe; ++d) {
         uint32_t *pfp = &t.cell_at(s).fp;
@@ -146,7 +166,7 @@ __device__ __forceinline__ uint32_t claim_next(const Tab &t, uint64_t key, uint3
             uint32_t expected = 0;
             if (__hip_atomic_compare_exchange_strong(pfp, &expected, f, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT)) {
-                t.key_at(s) = key;
+                claimed<kOcc>(t, s, key);
                 return s;
             }
             cur = expected;
@@ -157,8 +177,9 @@ __device__ __forceinline__ uint32_t claim_next(const Tab &t, uint64_t key, uint3
     return kNoSlot;
 }
 
+template <bool kOcc>
 __device__ __forceinline__ uint32_t claim(const Tab &t, uint64_t key) {
-    return claim_next(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
+    return claim_next<kOcc>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
 // Whether a group needs records of kind 1, and how many.
@@ -234,17 +255,28 @@ __device__ __forceinline__ VertexIn<kKeys> load_vertex(const FusedKeys &fk, cons
     return in;
 }
 
-// Key, fixed-point contribution and flags of a vertex; rnd: its PCG32 outputs.
-template <bool kKeys>
+// Where a window's groups go: kBuckets, records for reduce; kAtomics, straight
+// to their cells by device atomics (no workspace), kFloatAtomics the same with
+// binary32 sums.
+enum Sink { kBuckets, kAtomics, kFloatAtomics };
+
+// Key, contribution (fixed point; kFloatAtomics: as it is) and flags of a
+// vertex; rnd: its PCG32 outputs.
+template <bool kKeys, typename V>
 __device__ __forceinline__ uint32_t vertex_value(const FusedKeys &fk, const VertexIn<kKeys> &in, const uint32_t rnd[3],
-                                                 int frac_bits, uint64_t &k, int64_t &q0, int64_t &q1, int64_t &q2) {
+                                                 int frac_bits, uint64_t &k, V &q0, V &q1, V &q2) {
     uint32_t f = 0;
     k = in.key;
     if constexpr (kKeys) {
         uint32_t fp, home;
         f = vertex_key(in.x, in.nr, true, fk.a.cam, fk.a.s, fk.a.inv_s, rnd, fk.a.mask, k, fp, home);
     }
-    if (f == 0) f = fixed_point(in.c[0], in.c[1], in.c[2], frac_bits, q0, q1, q2);
+    if (f == 0) {
+        if constexpr (std::is_same<V, float>::value)
+            f = float_contribution(in.c[0], in.c[1], in.c[2], q0, q1, q2);
+        else
+            f = fixed_point(in.c[0], in.c[1], in.c[2], frac_bits, q0, q1, q2);
+    }
     return f;
 }
 
@@ -266,7 +298,7 @@ constexpr uint32_t kAlone = 0xffffu, kFlagged = 0x8000u;
 // than kLimit entries in use), so coherent streams merge over 4096 vertices,
 // while streams of mostly distinct keys (small images, bounces, shuffled keys)
 // flush as often as the table needs.
-template <bool kKeys>
+template <bool kKeys, Sink kSink>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void aggregate_kernel(
     Tab t, const uint64_t *__restrict__ key, const float *__restrict__ r, const float *__restrict__ g,
     const float *__restrict__ b, uint8_t *__restrict__ flags, uint32_t *__restrict__ slot_out, uint32_t n,
@@ -280,8 +312,9 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     uint32_t *misc = place + bk.nbins;  // [0] overflowed vertices, [1] the next chunk, [2] valid vertices
     uint32_t *created = misc + 4;       // [kMaxSteps] LDS entries created by each step of the chunk
     uint16_t *list = reinterpret_cast<uint16_t *>(created + kMaxSteps);  // the chunk's valid vertices
+    using V = std::conditional_t<kSink == kFloatAtomics, float, int64_t>;
     const uint32_t tid = threadIdx.x;
-    const uint32_t part = blockIdx.x % bk.parts;
+    const uint32_t part = kSink == kBuckets ? blockIdx.x % bk.parts : 0u;
     for (uint32_t k = tid; k < bk.nbins; k += kT) taken[k] = 0;
     if (tid < 4 + kMaxSteps) misc[tid] = 0;
     for (uint32_t j = tid; j < kCap; j += kT) {
@@ -335,7 +368,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
             } else if (i < i1) {
                 if (kKeys) flags[i] = PF_V_INVALID;
                 if (kKeys && fk.key_out) fk.key_out[i] = 0;
-                slot_out[i] = kNoSlot;
+                if (kSink == kBuckets || slot_out) slot_out[i] = kNoSlot;
             }
         }
         __syncthreads();
@@ -355,16 +388,17 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                     if constexpr (kKeys)
                         for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
                     uint64_t k;
-                    int64_t q0, q1, q2;
+                    V q0, q1, q2;
                     c = vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
                     if (kKeys && fk.key_out) fk.key_out[i] = k;
                     if (c == 0) {
-                        const int e = lds_insert(lkey, kCap, k, fresh);
+                        // (a caller's key may be the empty entry's)
+                        const int e = !kKeys && k == kEmpty ? -1 : lds_insert(lkey, kCap, k, fresh);
                         if (e >= 0) {
                             atomicAdd(&lcnt[e], 1u);
-                            atomicAdd(&ls0[e], (unsigned long long)q0);
-                            atomicAdd(&ls1[e], (unsigned long long)q1);
-                            atomicAdd(&ls2[e], (unsigned long long)q2);
+                            lds_add(&ls0[e], q0);
+                            lds_add(&ls1[e], q1);
+                            lds_add(&ls2[e], q2);
                             c = (uint32_t)e;
                         } else {
                             c = kAlone;
@@ -424,16 +458,21 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 const uint32_t j = v * kT + tid;
                 slot[v] = kNoSlot;
                 if (gk[v] == kEmpty) continue;
-                if (won[v]) t.key_at(fs[v]) = gk[v];
+                if (won[v]) claimed<kSink != kBuckets>(t, fs[v], gk[v]);
                 // the home slot holds another key: probe on from the next
-                slot[v] = fcur[v] == ff[v] ? fs[v] : claim_next(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
+                slot[v] = fcur[v] == ff[v] ? fs[v]
+                                           : claim_next<kSink != kBuckets>(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
                 cnt[v] = lcnt[j];
                 lcnt[j] = slot[v];
-                if (slot[v] != kNoSlot)
+                if (slot[v] == kNoSlot) {
+                    atomicAdd(&misc[0], cnt[v]);
+                } else if constexpr (kSink == kBuckets) {
                     rank[v] = atomicAdd(&taken[slot[v] >> bk.bin_shift],
                                         1u + extra_records(cnt[v], ls0[j], ls1[j], ls2[j]));
-                else
-                    atomicAdd(&misc[0], cnt[v]);
+                } else {
+                    accumulate(t, slot[v], cnt[v], lds_value(&ls0[j], V()), lds_value(&ls1[j], V()),
+                               lds_value(&ls2[j], V()));
+                }
             }
             __syncthreads();
             // the window's places, one device atomic per bin; the vertices get
@@ -459,24 +498,26 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                     if constexpr (kKeys)
                         for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
                     uint64_t k;
-                    int64_t q0, q1, q2;
+                    V q0, q1, q2;
                     vertex_value<kKeys>(fk, in, rnd, t.frac_bits, k, q0, q1, q2);
-                    s = claim(t, k);
-                    if (s != kNoSlot) {
+                    s = claim<kSink != kBuckets>(t, k);
+                    if (s == kNoSlot) {
+                        f = PF_V_OVERFLOW;
+                        atomicAdd(&misc[0], 1u);
+                    } else if constexpr (kSink == kBuckets) {
                         const uint32_t extra = extra_records(1, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
                         const uint32_t pos =
                             __hip_atomic_fetch_add(&bk.cnt[(s >> bk.bin_shift) * bk.parts + part], 1u + extra,
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         put_records(bk, t, part, pos, extra, s, 1u, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
                     } else {
-                        f = PF_V_OVERFLOW;
-                        atomicAdd(&misc[0], 1u);
+                        accumulate(t, s, 1u, q0, q1, q2);
                     }
                 } else {
                     f = c & 0xffu;
                 }
                 if (kKeys || f) flags[i] = (uint8_t)f;
-                slot_out[i] = s;
+                if (kSink == kBuckets || slot_out) slot_out[i] = s;
             }
             if (want) {
                 place[tid] = first_place;
@@ -485,7 +526,10 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
             if (u == nsteps) {  // for the next chunk
                 if (tid < kMaxSteps) created[tid] = 0;
                 if (tid == 0) {
-                    if (ci >= gridDim.x) misc[1] = 2 * gridDim.x + drawn;
+                    if (kSink != kBuckets)
+                        misc[1] = ci + gridDim.x;  // no workspace, no ticket: chunks in turn
+                    else if (ci >= gridDim.x)
+                        misc[1] = 2 * gridDim.x + drawn;
                     misc[2] = 0;
                 }
             }
@@ -493,14 +537,14 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
             if (u == nsteps) {
                 const uint32_t after = ci < gridDim.x ? next : misc[1];
                 load_live(after, raw);
-                if (tid == 0) drawn = atomicAdd(ticket, 1u);
+                if (kSink == kBuckets && tid == 0) drawn = atomicAdd(ticket, 1u);
                 ci = after;
             }
 #pragma unroll
             for (uint32_t v = 0; v < kFlush; ++v) {
                 const uint32_t j = v * kT + tid;
                 if (gk[v] == kEmpty) continue;
-                if (slot[v] != kNoSlot) {
+                if (kSink == kBuckets && slot[v] != kNoSlot) {
                     const uint64_t s0 = ls0[j], s1 = ls1[j], s2 = ls2[j];
                     put_records(bk, t, part, place[slot[v] >> bk.bin_shift] + rank[v],
                                 extra_records(cnt[v], s0, s1, s2), slot[v], cnt[v], s0, s1, s2);
@@ -785,13 +829,13 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
     bk.part_cap = p.part_cap;
     static bool attrs = false;  // dynamic LDS above 64 KB needs the attribute, set once per function
     if (!attrs) {
-        constexpr int kAggregateLds = kCap * 36 + kMaxBins * 8 + (4 + kMaxSteps) * 4 + kMaxSteps * kT * 2;
+        constexpr int kAggregateLds = (int)aggregate_lds(kMaxSteps * kT, kMaxBins);
         constexpr int kReduceLds = kCells * 32 + (8 << (kMaxLog2BinSlots - 5));
         static_assert(kAggregateLds <= 80 * 1024, "two workgroups of aggregate share a CU");
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kBuckets>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<true>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<true, kBuckets>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
         for (const void *f : kReduceKernels)
             if (e == hipSuccess)
@@ -800,8 +844,8 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
         attrs = true;
     }
     zero_kernel<<<1, kT, 0, st>>>(ticket, p.nzero);
-    aggregate_kernel<kKeys><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n, p.chunk, bk,
-                                                                   ticket, fk);
+    aggregate_kernel<kKeys, kBuckets><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n,
+                                                                             p.chunk, bk, ticket, fk);
     const Blend none{};
     const Blend &bl = blend ? *blend : none;
     if (!blend)
@@ -818,6 +862,36 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
 }
 
 }  // namespace binned
+
+bool insert_by_windows(uint32_t n) { return n >= binned::kMinWindowed; }
+
+hipError_t launch_insert_windows(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
+                                 uint8_t *flags, uint32_t *slot_out, uint32_t n, hipStream_t st) {
+    using namespace binned;
+    constexpr int kLds = (int)aggregate_lds(kMaxSteps * kT, 0);
+    static bool attrs = false;  // as in run()
+    if (!attrs) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kAtomics>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kFloatAtomics>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        if (e != hipSuccess) return e;
+        attrs = true;
+    }
+    uint32_t chunk, groups;
+    deal_chunks(n, chunk, groups);
+    const size_t lds = aggregate_lds(chunk, 0);
+    const FusedKeys none{};
+    const Buckets no_buckets{};
+    if (t.fsum)
+        aggregate_kernel<false, kFloatAtomics><<<groups, kT, lds, st>>>(t, key, r, g, b, flags, slot_out, n, chunk,
+                                                                       no_buckets, nullptr, none);
+    else
+        aggregate_kernel<false, kAtomics><<<groups, kT, lds, st>>>(t, key, r, g, b, flags, slot_out, n, chunk,
+                                                                  no_buckets, nullptr, none);
+    return hipGetLastError();
+}
 
 hipError_t launch_insert_binned(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                                 uint8_t *flags, uint32_t *slot_out, uint32_t n, void *ws, hipStream_t st) {

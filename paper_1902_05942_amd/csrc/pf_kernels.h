@@ -28,6 +28,11 @@ hipError_t launch_build_keys(const float *px, const float *py, const float *pz, 
 size_t binned_workspace_bytes(uint32_t n, uint32_t log2_slots);
 hipError_t launch_insert_binned(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                                 uint8_t *flags, uint32_t *slot_out, uint32_t n, void *ws, hipStream_t st);
+// The insert by device atomics with vertices merged in windows first, for calls
+// of enough vertices (insert_by_windows).
+bool insert_by_windows(uint32_t n);
+hipError_t launch_insert_windows(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
+                                 uint8_t *flags, uint32_t *slot_out, uint32_t n, hipStream_t st);
 hipError_t launch_table_init(const Tab &t, hipStream_t st);
 hipError_t launch_clear(const Tab &t, hipStream_t st);
 hipError_t launch_insert(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,

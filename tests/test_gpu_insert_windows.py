@@ -14,7 +14,7 @@ from gpu_util import assert_bits_equal, table_contents
 pytestmark = pytest.mark.gpu
 
 
-def _insert_and_compare(key, rgb, m, frac_bits=24):
+def _insert_and_compare(key, rgb, m, frac_bits=24, agg=None):
     n = key.size
     probe = min(64, 1 << m)
     R = oracle.filter_keys(key, rgb[0], rgb[1], rgb[2], np.ones(n, np.uint8), m, probe, frac_bits)
@@ -27,7 +27,11 @@ def _insert_and_compare(key, rgb, m, frac_bits=24):
     cnt = torch.empty(n, dtype=torch.int32, device="cuda")
     ws = torch.empty(pf.insert_workspace_bytes(n, m), dtype=torch.uint8, device="cuda")
     out = [torch.empty(n, device="cuda") for _ in range(3)]
-    pf.insert_accumulate_binned(t, k, r, g, b, fl, slot, ws)
+    if agg is None:
+        pf.insert_accumulate_binned(t, k, r, g, b, fl, slot, ws)
+    else:
+        slot = slot if agg else None
+        pf.insert_accumulate(t, k, r, g, b, fl, slot, agg)
     pf.query_average(t, k, slot, r, g, b, fl, False, *out, cnt)
     torch.cuda.synchronize()
     assert R.table.order_free and not R.flags.any()
@@ -82,3 +86,40 @@ def test_full_bucket_and_several_passes(gpu):
     assert len(chosen) == cells
     rng = np.random.default_rng(3)
     _insert_and_compare(chosen[rng.integers(0, cells, n)], rng.random((3, n), dtype=np.float32), m)
+
+
+@pytest.mark.parametrize("n,distinct,m,agg", [
+    ((1 << 19) - 1, 1, 4, 64), (1 << 19, 1, 4, 64), (1 << 19, 200000, 20, 0), ((1 << 19) + 77, 1793, 17, 256)])
+def test_atomic_insert_by_windows(gpu, n, distinct, m, agg):
+    """The insert by device atomics on both sides of the size from which it
+    merges by windows; among its keys one with every bit set."""
+    rng = np.random.default_rng(n)
+    ids = np.concatenate([np.arange(distinct), rng.integers(0, distinct, n - distinct)])
+    rng.shuffle(ids)
+    key = _keys(ids)
+    key[ids == 0] = ~np.uint64(0)
+    _insert_and_compare(key, rng.random((3, n), dtype=np.float32) - np.float32(0.5), m, agg=agg)
+
+
+def test_atomic_insert_by_windows_overflows(gpu):
+    # 16 slots, 2 probes, 40 keys: whole groups overflow, and every vertex of a
+    # placed key is counted
+    n = 1 << 19
+    key = _keys(np.arange(n) % 40)
+    t = pf.Table(4, 2)
+    pf.table_init(t)
+    k = torch.from_numpy(key.view(np.int64)).cuda()
+    r = torch.ones(n, device="cuda")
+    fl = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    pf.insert_accumulate(t, k, r, r, r, fl, slot, 64)
+    torch.cuda.synchronize()
+    flags, slots = fl.cpu().numpy(), slot.cpu().numpy()
+    over = flags == pf.V_OVERFLOW
+    assert 0 < over.sum() < n and not flags[~over].any()
+    assert (slots[over] == -1).all() and (slots[~over] >= 0).all()
+    tc = table_contents(t)
+    placed = np.unique(key[~over])
+    assert np.array_equal(np.sort(tc["key"]), placed) and not np.isin(key[over], placed).any()
+    assert int(tc["count"].sum()) == int((~over).sum())
+    assert int(pf.read_stats(t)[pf.STAT_OVERFLOW]) == int(over.sum())
