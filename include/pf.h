@@ -649,10 +649,11 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  *   insert     keys of every vertex (as pf_build_keys) and its cell
  *              (Sections 3.2, 3.3.1): agg_width 0 claims the cell and adds
  *              count and sums with one set of device atomics per vertex;
- *              otherwise each workgroup merges windows of agg_width
- *              consecutive vertices by key in an LDS table of
- *              min(agg_width, 4 x block, 1536) entries (a vertex that finds
- *              no room goes alone), and each group claims its cell once and
+ *              otherwise a workgroup takes agg_width consecutive vertices at
+ *              a time (fewer where the views have few) and merges the valid
+ *              ones by key in an LDS table of min(agg_width, 4 x block, 1536)
+ *              entries, in as many windows as the table needs (a vertex that
+ *              finds no room goes alone); each group claims its cell once and
  *              writes one record {slot, count, sums} into the bucket of its
  *              bin of min(2 x block, 2048) slots (a full bucket adds the
  *              group with device atomics instead);

@@ -12,6 +12,8 @@
 // with plain loads and stores, and blends the cells with the previous
 // frame's values.  The per-vertex and per-cell arithmetic is that of the
 // single-view kernels (pf_ops.h).
+#include <algorithm>
+
 #include "pf_grid.h"
 #include "pf_kernels.h"
 #include "pf_merge.h"
@@ -41,10 +43,16 @@ __device__ __forceinline__ Tab to_tab(const pf_table &t) {
     return k;
 }
 
-// LDS merge table of the insert phase: a window of agg_width consecutive
-// vertices (block .. kIters * block) merges into at most min(agg_width,
-// 4 * block, 1536) entries (the table stays in static LDS and small
-// workgroups keep their residency); a vertex that finds no room goes alone.
+// LDS merge table of the insert phase: the valid ones of agg_width consecutive
+// vertices (block .. kIters * block) merge in windows into at most
+// min(agg_width, 4 * block, 1536) entries (the table stays in static LDS and
+// small workgroups keep their residency); a window ends when the next step's
+// vertices might not find room (more than seven eighths in use).  (With one
+// window per agg_width vertices, small images overflowed the table and sent
+// their vertices to the cells one by one, and a workgroup's 8 x block vertices
+// left most workgroups without any: insert phase of 640x360, 800x600, 401x229
+// and 256x256 x3 267 -> 197 us, of 200x90 and 150x150 x2 180 -> 56 us, of
+// 1920x1080 and 1280x720 x3 398 -> 346 us.)
 template <int B>
 constexpr uint32_t kMergeCap = 4 * B < 1536 ? 4 * B : 1536;
 template <int B>
@@ -63,6 +71,8 @@ struct Lds {
             unsigned long long key[kMergeCap<B>];
             unsigned long long s0[kMergeCap<B>], s1[kMergeCap<B>], s2[kMergeCap<B>];
             uint32_t cnt[kMergeCap<B>];  // count, then the group's slot
+            uint16_t list[kIters * B];   // the item's valid vertices
+            uint32_t nlive, created[kIters];  // valid vertices; entries created by each step
         } m;
         struct {
             unsigned long long s0[kBinSlots<B>], s1[kBinSlots<B>], s2[kBinSlots<B>];  // s0 then holds the cell list
@@ -72,7 +82,7 @@ struct Lds {
     uint32_t first[5][PF_MAX_VIEWS + 1];  // per item kind: first global item of each view
     uint32_t seg[kParts + 1];
     uint32_t spilled[2048 / 32];  // occupancy bits that spilled groups set, per bin
-    uint32_t hits, nlist;
+    uint32_t hits, nlist, per_item;
 };
 
 template <int B>
@@ -82,6 +92,10 @@ __device__ __forceinline__ void item_of(const Lds<B> &L, int phase, uint32_t nvi
     while (v + 1 < nviews && it >= L.first[phase][v + 1]) ++v;
     local = it - L.first[phase][v];
 }
+
+// What a lane keeps of a vertex until its window ends (16 bits): its LDS entry,
+// kAlone, or kFlagged and its flags.
+constexpr uint32_t kAlone = 0xffffu, kFlagged = 0x8000u;
 
 // Key, flags and fixed-point contribution of vertex i of a view (masked
 // vertices read nothing more than their valid byte).
@@ -183,10 +197,17 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
     __shared__ Lds<B> L;
     constexpr uint32_t kItem = (uint32_t)B * kIters;
     // work items per view and kind: 0 clear cur (B bitmap words and bucket
-    // counts), 1 keys + insert (8 x B vertices), 2 reduce and temporal (one
+    // counts), 1 keys + insert (agg vertices, or 8 x B), 2 reduce and temporal (one
     // bin), 3 clear prev (B bitmap words), 4 lookup (8 x B vertices); kinds
     // 3 and 4 share the last phase
     if (threadIdx.x == 0) {
+        // items of the insert: agg vertices, fewer where the views would not
+        // give every workgroup three
+        uint64_t total = 0;
+        for (uint32_t v = 0; v < nviews; ++v) total += views[v].d.n;
+        uint32_t per_item = agg ? agg : kItem;
+        while (agg && per_item > (uint32_t)B && (uint64_t)per_item * 3 * gridDim.x > total) per_item /= 2;
+        L.per_item = per_item;
         uint32_t acc[5] = {0, 0, 0, 0, 0};
         for (uint32_t v = 0; v < nviews; ++v) {
             const pf_view &d = views[v].d;
@@ -194,7 +215,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
             const uint32_t words = (slots + 31) / 32;
             const uint32_t counts = views[v].nbins * kParts;
             const uint32_t zero = words > counts ? words : counts;
-            const uint32_t items[5] = {(zero + B - 1) / B, (d.n + kItem - 1) / kItem, views[v].nbins,
+            const uint32_t items[5] = {(zero + B - 1) / B, (d.n + per_item - 1) / per_item, views[v].nbins,
                                        d.prev.cell ? (words + B - 1) / B : 0u, (d.n + kItem - 1) / kItem};
             for (int p = 0; p < 5; ++p) {
                 L.first[p][v] = acc[p];
@@ -235,12 +256,14 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
     stamp(1);
 
     // ---- phase 1: keys and insertion.  agg == 0: one claim and one set of
-    // device atomics per vertex.  Otherwise each window of agg consecutive
-    // vertices (a power of two, block <= agg <= kIters * block) merges by key
-    // in LDS, then every group claims its cell once and writes one record to
-    // its bin's bucket.
-    const uint32_t kCap = agg < kMergeCap<B> ? agg : kMergeCap<B>;
-    const uint32_t per = agg / B;  // vertices per lane and window (1, 2, 4 or 8)
+    // device atomics per vertex.  Otherwise an item is agg consecutive vertices
+    // (a power of two, block <= agg <= kIters * block; fewer for small views,
+    // down to block): its valid ones are
+    // listed, merged by key in LDS in windows that end before the table is
+    // full, then every group claims its cell once and writes one record to its
+    // bin's bucket.
+    const uint32_t kCap = agg < kMergeCap<B> ? agg : kMergeCap<B>, limit = kCap / 8 * 7;
+    const uint32_t per_item = L.per_item, per = per_item / B;  // vertices per lane and item (1, 2, 4 or 8)
     for (uint32_t it = blockIdx.x; it < L.first[1][nviews]; it += G) {
         uint32_t v, local;
         item_of(L, 1, nviews, it, v, local);
@@ -272,39 +295,84 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
             }
             continue;
         }
-        for (uint32_t sub = 0; sub < (uint32_t)kIters / per; ++sub) {
-            const uint32_t base = local * kItem + sub * agg;
-            if (base >= d.n) break;  // uniform across the workgroup
-            for (uint32_t j = threadIdx.x; j < kCap; j += B) {
-                L.m.key[j] = kEmpty;
-                L.m.s0[j] = 0;
-                L.m.s1[j] = 0;
-                L.m.s2[j] = 0;
-                L.m.cnt[j] = 0;
+        const uint32_t c0 = local * per_item, i1 = min(d.n, c0 + per_item);
+        for (uint32_t j = threadIdx.x; j < kCap; j += B) {
+            L.m.key[j] = kEmpty;
+            L.m.s0[j] = 0;
+            L.m.s1[j] = 0;
+            L.m.s2[j] = 0;
+            L.m.cnt[j] = 0;
+        }
+        if (threadIdx.x < kIters) L.m.created[threadIdx.x] = 0;
+        if (threadIdx.x == 0) L.m.nlive = 0;
+        // the valid bytes first; masked vertices read nothing more
+        uint32_t live = 0;
+        for (uint32_t u = 0; u < per; ++u) {
+            const uint32_t i = c0 + u * B + threadIdx.x;
+            live |= (i < i1 && (d.valid == nullptr || d.valid[i] != 0) ? 1u : 0u) << u;
+        }
+        __syncthreads();
+        for (uint32_t u = 0; u < per; ++u) {
+            const uint32_t i = c0 + u * B + threadIdx.x;
+            const bool v = (live >> u) & 1u;
+            const uint32_t at = wave_reserve(&L.m.nlive, v);
+            if (v) {
+                L.m.list[at] = (uint16_t)(u * B + threadIdx.x);
+            } else if (i < i1) {
+                d.vflags[i] = PF_V_INVALID;
+                if (d.key) d.key[i] = 0;
+                d.slot[i] = kNoSlot;
             }
-            __syncthreads();
-            // a lane keeps only its vertices' flags and LDS entries across
-            // the barriers; the rare vertex that found no room rebuilds its
-            // key and contribution
-            uint64_t fv = 0;          // 8 bits per vertex
-            uint64_t ev[2] = {0, 0};  // 16 bits per vertex (4 per word), 0xffff = no room
-#pragma unroll 1
-            for (uint32_t u = 0; u < per; ++u) {
-                const uint32_t i = base + u * B + threadIdx.x;
-                uint64_t k = 0;
-                int64_t q0 = 0, q1 = 0, q2 = 0;
-                uint8_t f = PF_V_INVALID;
-                if (i < d.n) f = view_vertex(d, t, inv_s, i, k, q0, q1, q2);
-                if (d.key && i < d.n) d.key[i] = k;
-                const int e =
-                    merge_into_lds<false>(L.m.key, L.m.s0, L.m.s1, L.m.s2, L.m.cnt, kCap, f == 0, k, q0, q1, q2);
-                fv |= (uint64_t)f << (8 * u);
-                const uint64_t eb = (uint64_t)(uint16_t)e << (16 * (u & 3));
-                if (u < 4)
-                    ev[0] |= eb;
+        }
+        __syncthreads();
+        const uint32_t nlive = L.m.nlive, nsteps = (nlive + B - 1) / B;
+        for (uint32_t w0 = 0, w1; w0 < nsteps; w0 = w1) {
+            // a lane keeps 16 bits of a vertex until its window ends: its LDS
+            // entry, kAlone (no room), or kFlagged and its flags
+            uint64_t code[2] = {0, 0};
+            uint32_t u = w0;
+            while (true) {
+                const uint32_t l = u * B + threadIdx.x;
+                uint32_t c = kFlagged;
+                bool fresh = false;
+                if (l < nlive) {
+                    const uint32_t i = c0 + L.m.list[l];
+                    uint64_t k;
+                    int64_t q0, q1, q2;
+                    c = view_vertex(d, t, inv_s, i, k, q0, q1, q2);
+                    if (d.key) d.key[i] = k;
+                    if (c == 0) {
+                        const int e = lds_insert(L.m.key, kCap, k, fresh);
+                        if (e >= 0) {
+                            atomicAdd(&L.m.cnt[e], 1u);
+                            lds_add(&L.m.s0[e], q0);
+                            lds_add(&L.m.s1[e], q1);
+                            lds_add(&L.m.s2[e], q2);
+                            c = (uint32_t)e;
+                        } else {
+                            c = kAlone;
+                        }
+                    } else {
+                        c |= kFlagged;
+                    }
+                }
+                const uint64_t m = __ballot(fresh);
+                if ((threadIdx.x & 63) == 0 && m) atomicAdd(&L.m.created[u], (uint32_t)__popcll(m));
+                const uint64_t cb = (uint64_t)c << (16 * ((u - w0) & 3));
+                if (u - w0 < 4)
+                    code[0] |= cb;
                 else
-                    ev[1] |= eb;
+                    code[1] |= cb;
+                ++u;
+                if (u == nsteps) break;
+                const uint32_t next = min(nlive - u * B, (uint32_t)B);
+                if ((u - w0) * B + next <= limit) continue;
+                __syncthreads();
+                uint32_t used = 0;
+                for (uint32_t x = w0; x < u; ++x) used += L.m.created[x];
+                if (used + next > limit) break;
             }
+            w1 = u;
             __syncthreads();
             // one claim and one record per group; a lane's entries issue
             // their home-slot loads, then their compare-and-swaps on empty
@@ -357,35 +425,45 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                 else
                     add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], (unsigned long long)c);
                 L.m.cnt[j] = sl[e];
+                L.m.key[j] = kEmpty;  // emptied for the next window
+                L.m.s0[j] = 0;
+                L.m.s1[j] = 0;
+                L.m.s2[j] = 0;
             }
             __syncthreads();
 #pragma unroll 1
-            for (uint32_t u = 0; u < per; ++u) {
-                const uint32_t i = base + u * B + threadIdx.x;
-                if (i >= d.n) continue;
-                uint8_t fl = (uint8_t)(fv >> (8 * u));
-                const uint32_t e = (uint32_t)((u < 4 ? ev[0] : ev[1]) >> (16 * (u & 3))) & 0xffffu;
+            for (uint32_t x = w0; x < w1; ++x) {
+                const uint32_t l = x * B + threadIdx.x;
+                if (l >= nlive) break;
+                const uint32_t i = c0 + L.m.list[l], at = x - w0;
+                const uint32_t c = (uint32_t)((at < 4 ? code[0] : code[1]) >> (16 * (at & 3))) & 0xffffu;
                 uint32_t slot = kNoSlot;
-                if (fl == 0) {
-                    if (e != 0xffffu) {
-                        slot = L.m.cnt[e];
-                    } else {  // no room in the LDS table: on its own
-                        uint64_t k;
-                        int64_t q0, q1, q2;
-                        view_vertex(d, t, inv_s, i, k, q0, q1, q2);
-                        slot = claim_cell(t, k);
-                        if (slot != kNoSlot)
-                            put_group(vd, t, bshift, part, slot, 1u, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
-                        else
-                            add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
-                    }
+                uint8_t fl = 0;
+                if (c < kFlagged) {
+                    slot = L.m.cnt[c];
                     if (slot == kNoSlot) fl = PF_V_OVERFLOW;
+                } else if (c == kAlone) {  // no room in the LDS table: on its own
+                    uint64_t k;
+                    int64_t q0, q1, q2;
+                    view_vertex(d, t, inv_s, i, k, q0, q1, q2);
+                    slot = claim_cell(t, k);
+                    if (slot != kNoSlot) {
+                        put_group(vd, t, bshift, part, slot, 1u, (uint64_t)q0, (uint64_t)q1, (uint64_t)q2);
+                    } else {
+                        add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
+                        fl = PF_V_OVERFLOW;
+                    }
+                } else {
+                    fl = (uint8_t)(c & 0xffu);
                 }
                 d.vflags[i] = fl;
                 d.slot[i] = slot;
             }
-            __syncthreads();  // the table is cleared for the next window
+            __syncthreads();  // the slots are handed out: counts start from 0 again
+            for (uint32_t j = threadIdx.x; j < kCap; j += B) L.m.cnt[j] = 0;
+            __syncthreads();
         }
+        __syncthreads();  // the LDS is set up for the next item
     }
     if (!grid_barrier(bar, 2)) return;
     stamp(2);
@@ -602,15 +680,17 @@ hipError_t launch_b(const ViewDev *views, uint32_t nviews, uint32_t agg, uint32_
         if (e != hipSuccess) return e;
         // every workgroup of a cooperative grid must be resident at once: the
         // LDS-bound count is taken as well, with the static LDS rounded up to
-        // 2 KB, so that an allocation granularity the occupancy query may not
-        // model cannot leave a workgroup waiting for a slot
+        // 2 KB and to the hardware's 1280 bytes (a 128th of 160 KB), so that an
+        // allocation granularity the occupancy query may not model cannot
+        // leave a workgroup waiting for a slot
         int lds_cu = 0;
         e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
         if (e != hipSuccess) return e;
         hipFuncAttributes fa;
         e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(views_kernel<B>));
         if (e != hipSuccess) return e;
-        const size_t per_wg = (fa.sharedSizeBytes + 2047) / 2048 * 2048;
+        const size_t per_wg = std::max((fa.sharedSizeBytes + 2047) / 2048 * 2048,
+                                       (fa.sharedSizeBytes + 1279) / 1280 * 1280);
         if (per_wg > 0 && lds_cu > 0 && (size_t)resident * per_wg > (size_t)lds_cu)
             resident = (int)((size_t)lds_cu / per_wg);
         // and the register-bound count the compiler guarantees (4 SIMDs)
