@@ -584,8 +584,7 @@ struct Blend {
 // (256 bins and one workgroup of 1024 threads a CU: 3840x2160x4 190 -> 134 us, 8M
 // incoherent keys 206 -> 145 us, 1920x1080x3 40 -> 38 us).
 // kBlend: it also computes the temporal values of the cells (which are final:
-// every record of a slot is in the slot's bin), as temporal_word does for one
-// bitmap word.
+// every record of a slot is in the slot's bin), as pf_temporal_update does.
 template <bool kBlend = false, bool kHasPrev = false, bool kIntegrate = false>
 __global__ __launch_bounds__(kR) __attribute__((amdgpu_waves_per_eu(4, 4))) void reduce_kernel(Tab t, Buckets bk, Blend bl) {
     extern __shared__ unsigned long long lred[];

@@ -39,23 +39,15 @@ __device__ __forceinline__ uint32_t history_slot(const Hist &h, uint64_t key) {
 template <bool kIntegrate>
 __global__ __launch_bounds__(kBlock) void history_blend_kernel(Tab cur, Hist h, float alpha, float beta,
                                                                uint32_t cap) {
-    const uint32_t nparts = cur.nwords() * 4;
-    const uint32_t stride = gridDim.x * kBlock;
+    __shared__ CellList L;
     uint32_t hits = 0;
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nparts; q += stride) {
-        uint32_t w = cur.occ[q >> 2] & (0xffu << (8 * (q & 3)));
-        while (w) {
-            const uint32_t s = (q >> 2) * 32 + __builtin_ctz(w);
-            w &= w - 1;
-            const uint4 *w4 = cur.words_at(s);  // cell and key in one record
-            const uint4 lo = w4[0], hi = w4[1], kw = w4[2];
-            const uint64_t key = (uint64_t)kw.x | (uint64_t)kw.y << 32;
-            pf_cell c;
-            c.fp = lo.x;
-            c.count = lo.y;
-            c.sum[0] = (int64_t)((uint64_t)lo.z | (uint64_t)lo.w << 32);
-            c.sum[1] = (int64_t)((uint64_t)hi.x | (uint64_t)hi.y << 32);
-            c.sum[2] = (int64_t)((uint64_t)hi.z | (uint64_t)hi.w << 32);
+    for (uint32_t rg = blockIdx.x; rg < list_ranges(cur); rg += gridDim.x) {
+        const uint32_t m = list_cells(cur, rg, L);
+        for (uint32_t q = threadIdx.x; q < m; q += kBlock) {
+            const uint32_t s = L.slot[q];
+            const CellWords cw = load_cell(cur, s);
+            const pf_cell &c = cw.cell;
+            const uint64_t key = cw.key;
             float v[3] = {cur.average(c, 0), cur.average(c, 1), cur.average(c, 2)};
             uint32_t keep = kIntegrate ? min(c.count, cap) : c.count;
             const uint32_t hs = history_slot(h, key);
@@ -85,6 +77,7 @@ __global__ __launch_bounds__(kBlock) void history_blend_kernel(Tab cur, Hist h, 
             }
             cur.blend_at(s) = make_float4(v[0], v[1], v[2], (float)keep);
         }
+        __syncthreads();
     }
     __shared__ uint32_t s_hits;
     if (threadIdx.x == 0) s_hits = 0;
@@ -108,13 +101,11 @@ __global__ __launch_bounds__(kBlock) void history_age_kernel(Hist h, uint32_t fr
 // voxel holding the slot's minimum writes its key, value and stamp.
 template <bool kOwn>
 __global__ __launch_bounds__(kBlock) void history_offer_kernel(Tab cur, Hist h, uint32_t frame) {
-    const uint32_t nparts = cur.nwords() * 4;
-    const uint32_t stride = gridDim.x * kBlock;
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nparts; q += stride) {
-        uint32_t w = cur.occ[q >> 2] & (0xffu << (8 * (q & 3)));
-        while (w) {
-            const uint32_t s = (q >> 2) * 32 + __builtin_ctz(w);
-            w &= w - 1;
+    __shared__ CellList L;
+    for (uint32_t rg = blockIdx.x; rg < list_ranges(cur); rg += gridDim.x) {
+        const uint32_t m = list_cells(cur, rg, L);
+        for (uint32_t q = threadIdx.x; q < m; q += kBlock) {
+            const uint32_t s = L.slot[q];
             const uint64_t key = cur.key_at(s);
             const float4 v = cur.blend_at(s);
             const uint64_t mine = history_word(key, 0, (uint32_t)v.w);
@@ -129,6 +120,7 @@ __global__ __launch_bounds__(kBlock) void history_offer_kernel(Tab cur, Hist h, 
                 h.stamp[hs] = frame;
             }
         }
+        __syncthreads();
     }
 }
 
@@ -148,8 +140,7 @@ hipError_t launch_history_init(const Hist &h, hipStream_t st) {
 
 hipError_t launch_temporal_history(const Tab &cur, const Hist &h, float alpha_old, int mode, uint32_t cap,
                                    uint32_t frame, hipStream_t st) {
-    const uint32_t parts = cur.nwords() * 4;
-    uint32_t blocks = (parts + kBlock - 1) / kBlock;
+    uint32_t blocks = (cur.nwords() + kListWords - 1) / kListWords;
     if (blocks > 16384) blocks = 16384;
     if (mode == 1)
         history_blend_kernel<true><<<blocks, kBlock, 0, st>>>(cur, h, 0.0f, 0.0f, cap);

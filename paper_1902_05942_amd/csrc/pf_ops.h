@@ -233,7 +233,6 @@ __device__ __forceinline__ void accumulate_group(const Tab &t, AggLds<kBlockT> &
     __syncthreads();  // the scratch may be reused right after
 }
 
-// Temporal values of the occupied cells recorded in occupancy word j of
 // Changes of resolution across frames (Section 3.4.2) for a key absent from
 // `prev`: its parent (level + 1, cell coordinates floor-divided by 2), whose
 // value is distributed to it with an eighth of the parent's samples (in
@@ -395,65 +394,47 @@ __device__ __forceinline__ uint32_t blend_cells(const Tab &cur, const Tab &prev,
     return hits;
 }
 
-// The temporal blend of the occupied cells of bitmap word j of `cur`
-// (Section 3.4.1), restricted to the bits of `part`; returns how many found
-// their key in `prev`.  The word's cells are taken kTB at a time, and each
-// step of their lookups in the previous table (cell and key, fingerprint
-// probe, key check, old value) is issued for all of them before any result
-// is used (blend_cells).  kIntegrate: temporal
-// integration, alpha = N_old / (N_old + N_new) per cell with the stored count
-// kept at most `cap`; else the moving average with a fixed alpha (the stored
-// count is this frame's).
-// kLevels: a key absent from prev is searched one level coarser and finer
-// (find_across_levels); hits still count exact keys only.
-template <bool kHasPrev, bool kIntegrate, int kTB = 4, bool kLevels = false>  // kTB: cells looked up together
-__device__ __forceinline__ uint32_t temporal_word(const Tab &cur, const Tab &prev, uint32_t j, float alpha,
-                                                  float beta, uint32_t cap, uint32_t part = 0xffffffffu) {
-    uint32_t hits = 0;
-    uint32_t w = cur.occ[j] & part;  // the slots of the word this lane takes
-    while (w) {
-        uint32_t s[kTB];
-        bool has[kTB];
-#pragma unroll
-        for (int k = 0; k < kTB; ++k) {
-            has[k] = w != 0;
-            s[k] = has[k] ? j * 32 + __builtin_ctz(w) : 0u;
-            w &= w - 1;
-        }
-        uint4 lo[kTB], hi[kTB];
-        uint64_t key[kTB];
-#pragma unroll
-        for (int k = 0; k < kTB; ++k) {
-            if (has[k]) {
-                lo[k] = cur.words_at(s[k])[0];
-                hi[k] = cur.words_at(s[k])[1];
-                if constexpr (kHasPrev) key[k] = cur.key_at(s[k]);
-            }
-        }
-        float v[kTB][3];
-        uint32_t cnt[kTB], keep[kTB];
-#pragma unroll
-        for (int k = 0; k < kTB; ++k) {
-            if (!has[k]) continue;
-            pf_cell c;
-            c.fp = lo[k].x;
-            c.count = lo[k].y;
-            c.sum[0] = (int64_t)((uint64_t)lo[k].z | (uint64_t)lo[k].w << 32);
-            c.sum[1] = (int64_t)((uint64_t)hi[k].x | (uint64_t)hi[k].y << 32);
-            c.sum[2] = (int64_t)((uint64_t)hi[k].z | (uint64_t)hi[k].w << 32);
-            cnt[k] = c.count;
-            keep[k] = kIntegrate ? min(c.count, cap) : c.count;
-            v[k][0] = cur.average(c, 0);
-            v[k][1] = cur.average(c, 1);
-            v[k][2] = cur.average(c, 2);
-        }
-        uint32_t fp[kTB];
-#pragma unroll
-        for (int k = 0; k < kTB; ++k) fp[k] = has[k] ? lo[k].x : 0u;
-        hits += blend_cells<kHasPrev, kIntegrate, kTB, kLevels>(cur, prev, s, has, key, fp, v, cnt, keep, alpha, beta,
-                                                                cap);
+// The occupied slots of a range of kListWords bitmap words, listed in LDS by a
+// workgroup of kBlock threads, so that a kernel over a table's cells has a cell
+// on every lane (a frame fills a few percent of its table) and each lane one
+// chain of dependent loads.
+constexpr uint32_t kListWords = kBlock / 4;  // four lanes a word, 8 slots each
+struct CellList {
+    uint32_t n, slot[kListWords * 32];
+};
+
+__device__ __forceinline__ uint32_t list_ranges(const Tab &t) { return (t.nwords() + kListWords - 1) / kListWords; }
+
+// Every thread of the workgroup calls; the last list is no longer read.
+__device__ __forceinline__ uint32_t list_cells(const Tab &t, uint32_t range, CellList &L) {
+    const uint32_t j = range * kListWords + (threadIdx.x >> 2), sh = 8 * (threadIdx.x & 3);
+    uint32_t w = j < t.nwords() ? (t.occ[j] >> sh) & 0xffu : 0u;
+    if (threadIdx.x == 0) L.n = 0;
+    __syncthreads();
+    if (w) {
+        uint32_t at = atomicAdd(&L.n, (uint32_t)__popc(w));
+        for (; w; w &= w - 1) L.slot[at++] = j * 32 + sh + (uint32_t)__builtin_ctz(w);
     }
-    return hits;
+    __syncthreads();
+    return L.n;
+}
+
+// A cell's words as the kernels over cells load them: one 64-byte record.
+struct CellWords {
+    pf_cell cell;
+    uint64_t key;
+};
+__device__ __forceinline__ CellWords load_cell(const Tab &t, uint32_t s) {
+    const uint4 *w4 = t.words_at(s);
+    const uint4 lo = w4[0], hi = w4[1], kw = w4[2];
+    CellWords c;
+    c.cell.fp = lo.x;
+    c.cell.count = lo.y;
+    c.cell.sum[0] = (int64_t)((uint64_t)lo.z | (uint64_t)lo.w << 32);
+    c.cell.sum[1] = (int64_t)((uint64_t)hi.x | (uint64_t)hi.y << 32);
+    c.cell.sum[2] = (int64_t)((uint64_t)hi.z | (uint64_t)hi.w << 32);
+    c.key = (uint64_t)kw.x | (uint64_t)kw.y << 32;
+    return c;
 }
 
 // The value a vertex's lookup returns: its cell's temporal value (blend)
