@@ -81,67 +81,60 @@ __device__ __forceinline__ uint16_t to_feature(double v) {
     return bf16((float)v);
 }
 
-// sin(pi t) and cos(pi t) in FP32 for the dyadic phase t = m 2^e (m odd,
-// |m| < 2^17, e <= 15).  Every step of the reduction is exact: t itself
-// (with e clamped to 1: every even integer phase gives 0 and 1, as 2 does),
-// 2t, its nearest integer k, and r = t - k/2 with |r| <= 1/4 (a multiple of
-// 2^e with at most 18 significant bits).  sin(pi r) and cos(pi r) come from
-// their Taylor series (through r^9 and r^10, truncation below 2^-28
-// relative at |r| = 1/4), coefficients rounded to FP32 and evaluated with
-// explicit fused multiply-adds; each value lies within 3 FP32 ulps of the
-// true one (2 observed over every phase), and the quadrant k mod 4 swaps
-// and negates them exactly.  Returns true when either value lies within
+// Positional-encoding pair j of a coordinate: sin and cos of pi t with the
+// exact phase t = (q + 1/2) 2^(lp - 10 + j), in FP32, rounded to BF16 (low half
+// sin, high half cos).  The phase is kept as an integer P = t 2^31 modulo 2^32,
+// a full turn: with m4 = 4 q + 2 and shift = min(lp + 19 + j, 31), P = m4 <<
+// shift holds every bit of t modulo 2 (shift is at least 3, and an integer
+// phase beyond it gives 0, as 2 does).  The nearest multiple of 2^30 is the
+// quadrant, the rest r (P's low 30 bits, signed) at most an eighth of a turn,
+// with 18 significant bits, so its conversion is exact.  sin(pi r) / r and
+// cos(pi r) are polynomials in r^2 fitted for the smallest relative error over
+// |r| <= 1/4 (2^-28.2 and 2^-24.6), coefficients rounded to FP32, evaluated
+// with explicit fused multiply-adds; over every phase the values lie within 1.7
+// FP32 ulps of the true ones, and the quadrant swaps and negates them exactly
+// (zeros come out as +0).  `tie` becomes true when either value lies within
 // kTieGuard bit patterns of a BF16 rounding midpoint: only there could the
-// FP64 value, rounded FP64 -> FP32 -> BF16, round to a different BF16 than
-// this FP32 value does (never for an integer phase, whose values are exact).
-constexpr uint32_t kTieGuard = 16;
-__device__ __forceinline__ bool near_bf16_tie(float y) {
-    const uint32_t lo = __float_as_uint(y) & 0xffffu;
-    return lo - (0x8000u - kTieGuard) <= 2u * kTieGuard;
-}
-__device__ __forceinline__ bool dyadic_sincospi(int32_t m, int e, float &so, float &co) {
-    const float t = ldexpf((float)m, e < 1 ? e : 1);
-    const float k = __builtin_rintf(2.0f * t);  // nearest multiple of 1/2, ties to even
-    const float r = fmaf(k, -0.5f, t);
-    const int kq = (int)k;
+// FP64 value, rounded FP64 -> FP32 -> BF16, round to a different BF16 (a
+// midpoint is the middle of a binade's patterns, so those around it are one ulp
+// apart, and the FP64 value rounded to FP32 is within 1.7 + 1/2 ulps).  No
+// branch: the lanes of a wavefront hold vertices of different levels.  FP32 ->
+// BF16 of both values is one conversion instruction: the values are 0, +-1 or
+// at least sin(pi 2^-27) in magnitude (the phase is an odd multiple of a power
+// of two not below 2^-27), never an FP32 denormal.
+// Bound by VALU issue: 31 instructions a pair (40 with the reduction in floating
+// point and Taylor polynomials of one degree more) of ~670 a 16-vertex tile
+// took inference of 272k vertices from 35.0 to 32.2 us, a training step from 16.5 to
+// 15.8.
+constexpr uint32_t kTieGuard = 4;
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pe_shift(int lp, int j) { return min((uint32_t)(lp + 19 + j), 31u); }
+__device__ __forceinline__ uint32_t pe_pair32(uint32_t m4, uint32_t shift, bool &tie) {
+    const uint32_t P = m4 << shift;
+    const float r = (float)((int32_t)(P << 2) >> 2) * 0x1p-31f;
+    const uint32_t Q = P + 0x20000000u;  // bits 31, 30: the quadrant
     const float r2 = r * r;
-    float p = fmaf(r2, 0x1.507834p-4f, -0x1.32d2ccp-1f);  // pi^9/9!, -pi^7/7!
-    p = fmaf(r2, p, 0x1.466bc6p+1f);                      // pi^5/5!
-    p = fmaf(r2, p, -0x1.4abbcep+2f);                     // -pi^3/3!
-    p = fmaf(r2, p, 0x1.921fb6p+1f);                      // pi
+    float p = fmaf(r2, -0x1.2d9302p-1f, 0x1.465e92p+1f);
+    p = fmaf(r2, p, -0x1.4abbbap+2f);
+    p = fmaf(r2, p, 0x1.921fb6p+1f);
     const float sr = r * p;
-    float c = fmaf(r2, -0x1.a6d1f2p-6f, 0x1.e1f506p-3f);  // -pi^10/10!, pi^8/8!
-    c = fmaf(r2, c, -0x1.55d3c8p+0f);                     // -pi^6/6!
-    c = fmaf(r2, c, 0x1.03c1f0p+2f);                      // pi^4/4!
-    c = fmaf(r2, c, -0x1.3bd3ccp+2f);                     // -pi^2/2!
+    float c = fmaf(r2, -0x1.4e844ap+0f, 0x1.03b090p+2f);
+    c = fmaf(r2, c, -0x1.3bd39cp+2f);
     const float cr = fmaf(r2, c, 1.0f);
-    const bool odd = (kq & 1) != 0, neg_s = (kq & 2) != 0, neg_c = ((kq + 1) & 2) != 0;
-    const float sv = odd ? cr : sr, cv = odd ? sr : cr;
-    so = (neg_s ? -sv : sv) + 0.0f;  // zeros as +0
-    co = (neg_c ? -cv : cv) + 0.0f;
-    return near_bf16_tie(so) || near_bf16_tie(co);
+    const bool odd = (Q & 0x40000000u) != 0;
+    const float sign_s = __uint_as_float((Q & 0x80000000u) | 0x3f800000u);
+    const float sign_c = __uint_as_float(((Q + 0x40000000u) & 0x80000000u) | 0x3f800000u);
+    const float sn = fmaf(odd ? cr : sr, sign_s, 0.0f), cs = fmaf(odd ? sr : cr, sign_c, 0.0f);
+    // both low halves, moved so that the guarded patterns are 0 .. 2 kTieGuard
+    const u16x2_t low = {(uint16_t)__float_as_uint(sn), (uint16_t)__float_as_uint(cs)};
+    const u16x2_t off = low - (uint16_t)(0x8000u - kTieGuard);
+    tie = min(off.x, off.y) <= 2 * kTieGuard;
+    return bf16x2(sn, cs);
 }
-
-// Positional-encoding pair j of coordinate c: sin and cos of pi t with the
-// exact phase t = (q + 1/2) 2^(lp - 10 + j) = (2q + 1) 2^e, e = lp - 11 + j,
-// from dyadic_sincospi, or, near a BF16 rounding midpoint, from one FP64
-// sincospi, so that both are the FP64 values rounded FP64 -> FP32 -> BF16.
-// No other branch: the lanes of a wavefront hold vertices of different
-// levels.  FP32 -> BF16 of both values is one conversion instruction: the
-// values are 0, +-1 or at least sin(pi 2^-27) in magnitude (the phase is an
-// odd multiple of 2^e, e >= -27, so it is never within 2^-27 of an
-// integer), never an FP32 denormal.
-__device__ __forceinline__ void pe_pair(int32_t qc, int lp, int j, uint16_t &sv, uint16_t &cv) {
-    float sn, cs;
-    if (dyadic_sincospi(2 * qc + 1, lp - 11 + j, sn, cs)) {
-        double s64, c64;
-        sincospi(ldexp((double)qc + 0.5, lp - 10 + j), &s64, &c64);  // exact phase
-        sn = (float)(s64 + 0.0);
-        cs = (float)(c64 + 0.0);
-    }
-    const uint32_t both = bf16x2(sn, cs);
-    sv = (uint16_t)both;
-    cv = (uint16_t)(both >> 16);
+__device__ __forceinline__ uint32_t pe_pair64(int32_t qc, int lp, int j) {
+    double s64, c64;
+    sincospi(ldexp((double)qc + 0.5, lp - 10 + j), &s64, &c64);  // exact phase
+    return bf16x2((float)(s64 + 0.0), (float)(c64 + 0.0));
 }
 
 // Feature f of a vertex (f in [0, 80)), FP64 then FP64 -> FP32 -> BF16, zeros as +0.
@@ -150,9 +143,10 @@ __device__ __forceinline__ uint16_t feature(int f, const int32_t q[3], int lp, c
     double v = 0.0;
     if (f < 72) {
         const int j = f / 6, r = f % 6, c = r % 3;
-        uint16_t sv, cv;
-        pe_pair(q[c], lp, j, sv, cv);
-        return r < 3 ? sv : cv;
+        bool tie;
+        uint32_t both = pe_pair32(4u * (uint32_t)q[c] + 2u, pe_shift(lp, j), tie);
+        if (tie) both = pe_pair64(q[c], lp, j);
+        return (uint16_t)(r < 3 ? both : both >> 16);
     } else if (f < 75) {
         v = (double)n[f - 72];
     } else if (f < 78) {
@@ -192,14 +186,33 @@ __device__ __forceinline__ int input_of_lane_value(int lg, int m) {
 template <typename Put>
 __device__ __forceinline__ void vertex_slots(int lg, const int32_t q[3], int lp, const float x[3], const float n[3],
                                              const float cam[3], Put put) {
+    // all pairs in FP32 first, unrolled so that their chains interleave; then
+    // the few near a rounding midpoint (0.03% of them) behind one branch.  Pair
+    // p = lg + 4 k has coordinate p % 3 = (lg + k) % 3 and frequency p / 3 =
+    // k + (lg + k) / 3: with the coordinates rotated by lg, k says which.
+    const int32_t rot[3] = {lg % 3 == 0 ? q[0] : (lg == 1 ? q[1] : q[2]), lg % 3 == 0 ? q[1] : (lg == 1 ? q[2] : q[0]),
+                            lg % 3 == 0 ? q[2] : (lg == 1 ? q[0] : q[1])};
+    uint32_t both[9], redo = 0;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {  // independent phases: unrolled so that their FP64 chains interleave
-        const int pi = lg + 4 * k, j = pi / 3, c = pi % 3;
-        const int32_t qc = c == 0 ? q[0] : (c == 1 ? q[1] : q[2]);  // selects: q stays in registers
-        uint16_t sv, cv;
-        pe_pair(qc, lp, j, sv, cv);
-        put(2 * k, sv);
-        put(2 * k + 1, cv);
+    for (int k = 0; k < 9; ++k) {
+        const int b = k % 3, j = k + k / 3 + (lg + b >= 3 ? 1 : 0);
+        bool tie;
+        both[k] = pe_pair32(4u * (uint32_t)rot[b] + 2u, pe_shift(lp, j), tie);
+        redo |= (tie ? 1u : 0u) << k;
+    }
+    if (__builtin_expect(redo != 0, 0)) {
+#pragma unroll 1
+        for (uint32_t w = redo; w; w &= w - 1) {
+            const int k = __builtin_ctz(w), pi = lg + 4 * k, c = pi % 3;
+            const uint32_t fixed = pe_pair64(c == 0 ? q[0] : (c == 1 ? q[1] : q[2]), lp, pi / 3);
+#pragma unroll
+            for (int x = 0; x < 9; ++x) both[x] = x == k ? fixed : both[x];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        put(2 * k, (uint16_t)both[k]);
+        put(2 * k + 1, (uint16_t)(both[k] >> 16));
     }
     // inputs 72 + lg and 76 + lg: the normal (72..74), the view direction
     // (75..77) and two zeros (78, 79); a lane needs at most one component of
