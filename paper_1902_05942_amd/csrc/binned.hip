@@ -52,6 +52,7 @@ constexpr uint32_t kFlush = 2;               // LDS entries per thread
 constexpr uint32_t kCap = 1920;              // LDS entries of a window
 constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
+constexpr uint32_t kSmall = 1u << 17;        // vertices up to which a call has one launch (and the blend's)
 constexpr uint32_t kMinWindowed = 1u << 19;  // vertices from which pf_insert_accumulate merges by windows
 constexpr uint32_t kMaxBins = 512, kMaxParts = 8;
 constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
@@ -147,39 +148,9 @@ Plan make_plan(uint32_t n, uint32_t log2_slots) {
     return p;
 }
 
-// A cell just claimed: its key and (kOcc; else reduce sets it, which owns the
-// bitmap words of its bin) its occupancy bit.
-template <bool kOcc>
-__device__ __forceinline__ void claimed(const Tab &t, uint32_t s, uint64_t key) {
-    t.key_at(s) = key;
-    if constexpr (kOcc)
-        __hip_atomic_fetch_or(&t.occ[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Probe / claim like find_or_claim from probe d0 at slot s onwards.
-template <bool kOcc>
-__device__ __forceinline__ uint32_t claim_next(const Tab &t, uint64_t key, uint32_t f, uint32_t s, uint32_t d0) {
-    for (uint32_t d = d0; d < t.max_probe; ++d) {
-        uint32_t *pfp = &t.cell_at(s).fp;
-        uint32_t cur = load_fp_probe(pfp);
-        if (cur == 0) {
-            uint32_t expected = 0;
-            if (__hip_atomic_compare_exchange_strong(pfp, &expected, f, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) {
-                claimed<kOcc>(t, s, key);
-                return s;
-            }
-            cur = expected;
-        }
-        if (cur == f) return s;
-        s = (s + 1) & t.mask;
-    }
-    return kNoSlot;
-}
-
 template <bool kOcc>
 __device__ __forceinline__ uint32_t claim(const Tab &t, uint64_t key) {
-    return claim_next<kOcc>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
+    return claim_from<kOcc>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
 // Whether a group needs records of kind 1, and how many.
@@ -461,7 +432,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 if (won[v]) claimed<kSink != kBuckets>(t, fs[v], gk[v]);
                 // the home slot holds another key: probe on from the next
                 slot[v] = fcur[v] == ff[v] ? fs[v]
-                                           : claim_next<kSink != kBuckets>(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
+                                           : claim_from<kSink != kBuckets>(t, gk[v], ff[v], (fs[v] + 1) & t.mask, 1);
                 cnt[v] = lcnt[j];
                 lcnt[j] = slot[v];
                 if (slot[v] == kNoSlot) {
@@ -561,6 +532,56 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
         } while (w0 < nsteps);
     }
     if (tid == 0 && misc[0]) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], misc[0]);
+}
+
+// The insert of a small call: a vertex per thread, its key (kKeys), its cell,
+// and device atomics after the threads of a workgroup that reach the same slot
+// have combined their contributions (pf_insert_accumulate with agg_width 256,
+// keys included).  Bound by its one chain of latencies: 64x64 vertices with the
+// blend's launch take 21 us of kernels against 35 through the buckets; the
+// whole frame's time meets at ~2^17 vertices (240x160x3 47 -> 44 us, 290x170x3
+// 51 -> 50, 330x200x3 44 -> 48).
+template <bool kKeys>
+__global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint64_t *__restrict__ key,
+                                                              const float *__restrict__ r, const float *__restrict__ g,
+                                                              const float *__restrict__ b, uint8_t *__restrict__ flags,
+                                                              uint32_t *__restrict__ slot_out, uint32_t n,
+                                                              FusedKeys fk) {
+    __shared__ AggLds<kBlock> L;
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    const bool in = i < n;
+    uint32_t f = PF_V_INVALID;
+    if constexpr (kKeys) {
+        if (in && (fk.valid == nullptr || fk.valid[i] != 0)) f = 0;
+    } else {
+        if (in) f = flags[i];
+    }
+    const uint32_t f0 = f;
+    uint64_t k = 0;
+    int64_t q0 = 0, q1 = 0, q2 = 0;
+    uint32_t slot = kNoSlot;
+    if (f == 0) {
+        const VertexIn<kKeys> vin = load_vertex<kKeys>(fk, key, r, g, b, i);
+        uint32_t rnd[3] = {0, 0, 0};
+        if constexpr (kKeys) {
+            const PcgJump jp(fk.a.seed, fk.a.idx_base);
+            for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
+        }
+        f = vertex_value<kKeys>(fk, vin, rnd, t.frac_bits, k, q0, q1, q2);
+        if (f == 0) {
+            slot = find_or_claim(t, k);
+            if (slot == kNoSlot) {
+                f = PF_V_OVERFLOW;
+                add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
+            }
+        }
+    }
+    if (in) {
+        if (kKeys && fk.key_out) fk.key_out[i] = k;
+        if (kKeys || f != f0) flags[i] = (uint8_t)f;
+        slot_out[i] = slot;
+    }
+    accumulate_group<kBlock, int64_t>(t, L, kBlock, slot, q0, q1, q2);
 }
 
 // The temporal blend done by reduce: the previous table (has_prev) and the
@@ -814,6 +835,13 @@ template <bool kKeys>
 static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                       uint8_t *flags, uint32_t *slot_out, uint32_t n, void *ws, const FusedKeys &fk,
                       const Blend *blend, bool has_prev, bool integrate, hipStream_t st) {
+    if (n <= kSmall) {
+        small_insert_kernel<kKeys><<<(n + kBlock - 1) / kBlock, kBlock, 0, st>>>(t, key, r, g, b, flags, slot_out, n,
+                                                                               fk);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !blend) return e;
+        return launch_temporal(t, has_prev ? &blend->prev : nullptr, blend->alpha, integrate ? 1 : 0, blend->cap, st);
+    }
     const uint32_t log2_slots = 32 - __builtin_clz(t.mask + 1) - 1;
     const Plan p = make_plan(n, log2_slots);
     char *base = reinterpret_cast<char *>((reinterpret_cast<uintptr_t>(ws) + 255) / 256 * 256);

@@ -132,30 +132,10 @@ __device__ __forceinline__ uint32_t bin_shift_of(uint32_t log2_slots) {
     return kBinShift<B> < log2_slots ? kBinShift<B> : log2_slots;
 }
 
-// Probe / claim like find_or_claim, without the occupancy bit (the reduce
-// phase sets the bits of the cells it receives records for), from probe d0
-// at slot s onwards.
-__device__ __forceinline__ uint32_t claim_cell_from(const Tab &t, uint64_t key, uint32_t f, uint32_t s, uint32_t d0) {
-    for (uint32_t d = d0; d < t.max_probe; ++d) {
-        uint32_t *pfp = &t.cell_at(s).fp;
-        uint32_t cur = load_fp_probe(pfp);
-        if (cur == 0) {
-            uint32_t expected = 0;
-            if (__hip_atomic_compare_exchange_strong(pfp, &expected, f, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) {
-                t.key_at(s) = key;
-                return s;
-            }
-            cur = expected;
-        }
-        if (cur == f) return s;
-        s = (s + 1) & t.mask;
-    }
-    return kNoSlot;
-}
-
+// Probe / claim without the occupancy bit (the reduce phase sets the bits of
+// the cells it receives records for).
 __device__ __forceinline__ uint32_t claim_cell(const Tab &t, uint64_t key) {
-    return claim_cell_from(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
+    return claim_from<false>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
 // One group's record {slot, count, sums} into its bin's bucket part for this
@@ -410,7 +390,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                 if (gk[e] == kEmpty) continue;
                 if (won[e]) t.key_at(fs[e]) = gk[e];
                 // the home slot holds another key: probe on from the next
-                sl[e] = fc[e] == ff[e] ? fs[e] : claim_cell_from(t, gk[e], ff[e], (fs[e] + 1) & t.mask, 1);
+                sl[e] = fc[e] == ff[e] ? fs[e] : claim_from<false>(t, gk[e], ff[e], (fs[e] + 1) & t.mask, 1);
                 if (sl[e] != kNoSlot)
                     pos[e] = __hip_atomic_fetch_add(&vd.cnt[(size_t)(sl[e] >> bshift) * kParts + part], 1u,
                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -1,5 +1,5 @@
-"""The binned insert where its windows, buckets and bins have their edges: steps
-of 1024 vertices, windows that fill the LDS table, groups whose count or sums
+"""The binned insert where its windows, buckets and bins have their edges: the
+size up to which a call is one launch, steps of 1024 vertices, windows that fill the LDS table, groups whose count or sums
 need more than one record, a bucket that runs full (its groups then go to their
 cells by device atomics) and bins of more cells than one pass sums.  All sums are
 integers: table, averages and counts equal the oracle's group-by bit for bit."""
@@ -54,7 +54,8 @@ def _keys(ids):
 
 @pytest.mark.parametrize("n,distinct,m", [
     (1, 1, 4), (63, 9, 5), (1023, 1023, 12), (1024, 1, 4), (1025, 700, 12), (4097, 4097, 14), (5000, 3, 6),
-    (64 * 1024, 30000, 17), (64 * 1024 + 1, 64 * 1024 + 1, 18), (525000, 1793, 17), (1 << 21, 900000, 22)])
+    (64 * 1024, 30000, 17), (1 << 17, 60000, 18), ((1 << 17) + 1, (1 << 17) + 1, 19), (140001, 3, 6), (150000, 1, 4),
+    (256 * 1024, 256 * 1024, 20), (525000, 1793, 17), (1 << 21, 900000, 22)])
 def test_edges_of_steps_windows_and_bins(gpu, n, distinct, m):
     rng = np.random.default_rng(n + m)
     ids = np.concatenate([np.arange(distinct), rng.integers(0, distinct, n - distinct)])
@@ -69,11 +70,11 @@ def test_edges_of_steps_windows_and_bins(gpu, n, distinct, m):
     (8, 1.0e13, 2000),     # sums near the top of 64 bits
     (24, 1.0, 4096)])      # one cell for a whole window
 def test_groups_of_more_than_one_record(gpu, frac_bits, scale, per):
-    n = 20000
+    n = 140000
     rng = np.random.default_rng(per)
     rgb = (rng.random((3, n), dtype=np.float32) * np.float32(scale)).astype(np.float32)
     rgb[1] = -rgb[1]
-    _insert_and_compare(_keys(np.arange(n) // per), rgb, 16, frac_bits)
+    _insert_and_compare(_keys(np.arange(n) // per), rgb, 19, frac_bits)
 
 
 def test_full_bucket_and_several_passes(gpu):
