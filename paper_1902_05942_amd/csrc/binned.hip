@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 }
             }
             // the group's rank among the window's records of its bin
-            uint32_t slot[kFlush], cnt[kFlush], rank[kFlush];
+            uint32_t slot[kFlush], cnt[kFlush] = {}, rank[kFlush];
 #pragma unroll
             for (uint32_t v = 0; v < kFlush; ++v) {
                 const uint32_t j = v * kT + tid;
@@ -440,9 +440,14 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                 } else if constexpr (kSink == kBuckets) {
                     rank[v] = atomicAdd(&taken[slot[v] >> bk.bin_shift],
                                         1u + extra_records(cnt[v], ls0[j], ls1[j], ls2[j]));
-                } else {
-                    accumulate(t, slot[v], cnt[v], lds_value(&ls0[j], V()), lds_value(&ls1[j], V()),
-                               lds_value(&ls2[j], V()));
+                }
+            }
+            if constexpr (kSink != kBuckets) {
+#pragma unroll
+                for (uint32_t v = 0; v < kFlush; ++v) {
+                    const uint32_t j = min(v * kT + tid, kCap - 1);
+                    accumulate_wave(t, slot[v], cnt[v], lds_value(&ls0[j], V()), lds_value(&ls1[j], V()),
+                                    lds_value(&ls2[j], V()));
                 }
             }
             __syncthreads();

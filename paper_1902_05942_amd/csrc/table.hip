@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(Tab t, const uint64_t *_
     if (in && fl != fl0) flags[i] = fl;
     if (in && slot_out) slot_out[i] = slot;
     if constexpr (!kAgg) {
-        if (slot != kNoSlot) accumulate(t, slot, 1, q0, q1, q2);
+        accumulate_wave(t, slot, 1, q0, q1, q2);
     } else {
         __shared__ AggLds<kBlock> L;
         accumulate_group<kBlock, V>(t, L, agg, slot, q0, q1, q2);
@@ -115,10 +115,11 @@ static void launch_insert_t(const Tab &t, const uint64_t *key, const float *r, c
 
 hipError_t launch_insert(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                          uint8_t *flags, uint32_t *slot_out, uint32_t n, uint32_t agg_width, hipStream_t st) {
-    // each group costs four device atomics (24 G/s), so fewer groups win once a
-    // call is large enough to fill the chip with 1024-thread workgroups: int64
-    // sums, agg_width 0 / 64, 1920x1080x3 vertices 648 / 380 -> 297 us, 1280x720x3
-    // 300 / 200 -> 182, 640x360x3 87 / 74 -> 73, 330x200x3 35 / 34 -> 39
+    // a group is a claim's line and one or two lines of atomics, so fewer groups
+    // win once a call fills the chip with 1024-thread workgroups: agg_width
+    // 0 / 64 -> windows, int64 sums, 1920x1080x3 vertices 243 / 182 -> 143 us,
+    // 1280x720x3 114 / 90 -> 88, 640x360x3 48 / 44 -> 50, 330x200x3 29 / 29 -> 30;
+    // binary32 sums 368 / 235 -> 198, 176 / 126 -> 121, 61 / 56 -> 53, 29 / 30 -> 32
     if (insert_by_windows(n)) return launch_insert_windows(t, key, r, g, b, flags, slot_out, n, st);
     if (t.fsum)
         launch_insert_t<float>(t, key, r, g, b, flags, slot_out, n, agg_width, st);

@@ -255,23 +255,24 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
         if (agg == 0) {
             for (int k = 0; k < kIters; ++k) {
                 const uint32_t i = local * kItem + k * B + threadIdx.x;
-                if (i >= d.n) break;
-                uint64_t key;
+                if (local * kItem + k * B >= d.n) break;
+                uint64_t key = 0;
                 int64_t q0 = 0, q1 = 0, q2 = 0;
                 uint32_t slot = kNoSlot;
-                uint8_t fl = view_vertex(d, t, inv_s, i, key, q0, q1, q2);
-                if (fl == 0) {
-                    slot = find_or_claim(t, key);
-                    if (slot == kNoSlot) {
-                        fl = PF_V_OVERFLOW;
-                        add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
-                    } else {
-                        accumulate(t, slot, 1, q0, q1, q2);
+                if (i < d.n) {
+                    uint8_t fl = view_vertex(d, t, inv_s, i, key, q0, q1, q2);
+                    if (fl == 0) {
+                        slot = find_or_claim(t, key);
+                        if (slot == kNoSlot) {
+                            fl = PF_V_OVERFLOW;
+                            add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
+                        }
                     }
+                    if (d.key) d.key[i] = key;
+                    d.vflags[i] = fl;
+                    d.slot[i] = slot;
                 }
-                if (d.key) d.key[i] = key;
-                d.vflags[i] = fl;
-                d.slot[i] = slot;
+                accumulate_wave(t, slot, 1, q0, q1, q2);
             }
             continue;
         }

@@ -124,3 +124,42 @@ def test_atomic_insert_by_windows_overflows(gpu):
     assert np.array_equal(np.sort(tc["key"]), placed) and not np.isin(key[over], placed).any()
     assert int(tc["count"].sum()) == int((~over).sum())
     assert int(pf.read_stats(t)[pf.STAT_OVERFLOW]) == int(over.sum())
+
+
+@pytest.mark.parametrize("agg", [0, 2, 64, 256])
+@pytest.mark.parametrize("n,distinct", [(1, 1), (15, 15), (65, 40), (300, 2), (5000, 4000)])
+def test_atomic_insert_of_partial_wavefronts(gpu, n, distinct, agg):
+    """Four lanes of a wavefront add the words of one cell: wavefronts that are
+    not full, cells with and without a contribution side by side, sums of both
+    signs (the fingerprint beside the count stays as it is)."""
+    rng = np.random.default_rng(n + agg)
+    ids = np.concatenate([np.arange(distinct), rng.integers(0, distinct, n - distinct)])
+    rng.shuffle(ids)
+    _insert_and_compare(_keys(ids), (rng.random((3, n)) * 300 - 150).astype(np.float32), 13, agg=agg)
+
+
+@pytest.mark.parametrize("n,agg", [(1, 0), (65, 0), (700, 0), (700, 64), (700, 256), ((1 << 19) + 3, 64)])
+def test_atomic_insert_of_binary32_sums(gpu, n, agg):
+    """Whole numbers whose sums stay below 2^24 are exact in any order; every
+    seventh vertex is flagged."""
+    rng = np.random.default_rng(n)
+    ids = rng.integers(0, max(1, n // 9), n)
+    rgb = rng.integers(-40, 41, (3, n)).astype(np.float32)
+    t = pf.Table(17, 64, sum_format=pf.SUMS_FLOAT32)
+    pf.table_init(t)
+    fl = (np.arange(n) % 7 == 6).astype(np.uint8)
+    out = [torch.empty(n, device="cuda") for _ in range(3)]
+    cnt = torch.empty(n, dtype=torch.int32, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    k, d_fl = torch.from_numpy(_keys(ids).view(np.int64)).cuda(), torch.from_numpy(fl).cuda()
+    r, g, b = (torch.from_numpy(x).cuda() for x in rgb)
+    pf.insert_accumulate(t, k, r, g, b, d_fl, slot, agg)
+    pf.query_average(t, k, slot, r, g, b, d_fl, False, *out, cnt)
+    torch.cuda.synchronize()
+    live = fl == 0
+    want_cnt = np.bincount(ids[live], minlength=ids.max() + 1)[ids]
+    assert np.array_equal(cnt.cpu().numpy()[live], want_cnt[live])
+    for c in range(3):
+        total = np.bincount(ids[live], weights=rgb[c][live].astype(np.float64), minlength=ids.max() + 1)[ids]
+        want = (total.astype(np.float32) / want_cnt.clip(1).astype(np.float32))
+        assert_bits_equal(out[c].cpu().numpy()[live], want[live], "average")
