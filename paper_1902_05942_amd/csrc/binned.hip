@@ -52,7 +52,7 @@ constexpr uint32_t kFlush = 2;               // LDS entries per thread
 constexpr uint32_t kCap = 1920;              // LDS entries of a window
 constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
-constexpr uint32_t kSmall = 1u << 17;        // vertices up to which a call has one launch (and the blend's)
+constexpr uint32_t kSmall = 5u << 16;        // vertices up to which a call has one launch (and the blend's)
 constexpr uint32_t kMinWindowed = 1u << 19;  // vertices from which pf_insert_accumulate merges by windows
 constexpr uint32_t kMaxBins = 512, kMaxParts = 8;
 constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
@@ -543,9 +543,10 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // and device atomics after the threads of a workgroup that reach the same slot
 // have combined their contributions (pf_insert_accumulate with agg_width 256,
 // keys included).  Bound by its one chain of latencies: 64x64 vertices with the
-// blend's launch take 21 us of kernels against 35 through the buckets; the
-// whole frame's time meets at ~2^17 vertices (240x160x3 47 -> 44 us, 290x170x3
-// 51 -> 50, 330x200x3 44 -> 48).
+// blend's launch take 16 us of kernels against 35 through the buckets; whole
+// frames by buckets -> by vertices: 290x170x3 49 -> 39 us, 401x229x3 48 -> 43,
+// 512x384x3 59 -> 58, 720x450x3 73 -> 73, but coherent ones 560x400x1 40 -> 42 and
+// 800x600x1 51 -> 60, so kSmall is 5 * 2^16.
 template <bool kKeys>
 __global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint64_t *__restrict__ key,
                                                               const float *__restrict__ r, const float *__restrict__ g,
@@ -574,7 +575,7 @@ __global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint6
         }
         f = vertex_value<kKeys>(fk, vin, rnd, t.frac_bits, k, q0, q1, q2);
         if (f == 0) {
-            slot = find_or_claim(t, k);
+            slot = find_or_claim<4>(t, k);
             if (slot == kNoSlot) {
                 f = PF_V_OVERFLOW;
                 add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);

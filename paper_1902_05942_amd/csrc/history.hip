@@ -140,7 +140,7 @@ hipError_t launch_history_init(const Hist &h, hipStream_t st) {
 
 hipError_t launch_temporal_history(const Tab &cur, const Hist &h, float alpha_old, int mode, uint32_t cap,
                                    uint32_t frame, hipStream_t st) {
-    uint32_t blocks = (cur.nwords() + kListWords - 1) / kListWords;
+    uint32_t blocks = list_ranges(cur);
     if (blocks > 16384) blocks = 16384;
     if (mode == 1)
         history_blend_kernel<true><<<blocks, kBlock, 0, st>>>(cur, h, 0.0f, 0.0f, cap);

@@ -181,34 +181,49 @@ __device__ __forceinline__ void claimed(const Tab &t, uint32_t s, uint64_t key) 
         __hip_atomic_fetch_or(&t.occ[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Probes from slot s, probe d0, for the fingerprint f or claims the first empty
+// Probes from slot s, probe d, for the fingerprint f or claims the first empty
 // cell.  Returns the slot or kNoSlot after max_probe slots.  A stale read of
 // 0 only leads to a compare-and-swap that returns the current value; a
-// non-zero fingerprint never changes within a kernel.  (Slots after the first
-// read four at a time moved more lines than the latencies they saved: insert of
-// 1920x1080x3 121 -> 135 us, 8M keys at load 0.5 460 -> 486 us.)
-template <bool kOcc>
-__device__ __forceinline__ uint32_t claim_from(const Tab &t, uint64_t key, uint32_t f, uint32_t s, uint32_t d0) {
-    for (uint32_t d = d0; d < t.max_probe; ++d) {
-        uint32_t *pfp = &t.cell_at(s).fp;
-        uint32_t cur = load_fp_probe(pfp);
-        if (cur == 0) {
-            uint32_t expected = 0;
-            if (__hip_atomic_compare_exchange_strong(pfp, &expected, f, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) {
-                claimed<kOcc>(t, s, key);
-                return s;
+// non-zero fingerprint never changes within a kernel.  After the first slot
+// kAhead are read at a time: in a small call, whose cost is its chain of
+// latencies, 4 (insert of 200x150x3 vertices, table 70% full, 25 -> 20 us,
+// 64x64 9.9 -> 9.3; 8: 21 and 10); in a large one the lines moved cost more
+// (1920x1080x3 121 -> 135 us, 8M keys at load 0.5 460 -> 486).
+template <bool kOcc, uint32_t kAhead = 1>
+__device__ __forceinline__ uint32_t claim_from(const Tab &t, uint64_t key, uint32_t f, uint32_t s, uint32_t d) {
+    while (d < t.max_probe) {
+        const uint32_t m = d == 0 ? 1u : min(kAhead, t.max_probe - d);
+        uint32_t cur[kAhead], at = m;
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u)
+            if (u < m) cur[u] = load_fp_probe(&t.cell_at((s + u) & t.mask).fp);
+        bool empty = false;
+#pragma unroll
+        for (uint32_t u = kAhead; u-- > 0;)  // the first that is empty or has the fingerprint
+            if (u < m && (cur[u] == 0 || cur[u] == f)) {
+                at = u;
+                empty = cur[u] == 0;
             }
-            cur = expected;  // claimed meanwhile by someone else
+        s = (s + at) & t.mask;
+        d += at;
+        if (at == m) continue;
+        if (!empty) return s;
+        uint32_t expected = 0;
+        if (__hip_atomic_compare_exchange_strong(&t.cell_at(s).fp, &expected, f, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)) {
+            claimed<kOcc>(t, s, key);
+            return s;
         }
-        if (cur == f) return s;
+        if (expected == f) return s;  // claimed meanwhile by someone else
         s = (s + 1) & t.mask;
+        ++d;
     }
     return kNoSlot;
 }
 
+template <uint32_t kAhead = 1>
 __device__ __forceinline__ uint32_t find_or_claim(const Tab &t, uint64_t key) {
-    return claim_from<true>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
+    return claim_from<true, kAhead>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
 // Probe without claiming (lookup after insertion).
@@ -482,21 +497,31 @@ __device__ __forceinline__ uint32_t blend_cells(const Tab &cur, const Tab &prev,
     return hits;
 }
 
-// The occupied slots of a range of kListWords bitmap words, listed in LDS by a
-// workgroup of kBlock threads, so that a kernel over a table's cells has a cell
-// on every lane (a frame fills a few percent of its table) and each lane one
-// chain of dependent loads.
-constexpr uint32_t kListWords = kBlock / 4;  // four lanes a word, 8 slots each
+// The occupied slots of a range of bitmap words, listed in LDS by a workgroup of
+// kBlock threads, so that a kernel over a table's cells has a cell on every lane
+// (a frame fills a few percent of its table) and each lane one chain of
+// dependent loads.  Four lanes a word, 8 slots each.
+constexpr uint32_t kListWords = kBlock / 4;  // words of a range, at most
 struct CellList {
     uint32_t n, slot[kListWords * 32];
 };
 
-__device__ __forceinline__ uint32_t list_ranges(const Tab &t) { return (t.nwords() + kListWords - 1) / kListWords; }
+// Words of a range: as many as leave 1024 ranges, so that small tables, which
+// fill up more, still give every CU a chain to wait on (temporal blend of a
+// 2^16-slot table 70% full 25 -> 10 us, 2^14 slots 9.8 -> 5.8; 64 words from 2^21
+// slots on: with 4096 ranges 1280x720x3 took 27 us against 18).
+__host__ __device__ inline uint32_t list_words(const Tab &t) {
+    const uint32_t w = t.nwords() / 1024u;
+    return w < 8 ? 8u : w > kListWords ? kListWords : w;
+}
+__host__ __device__ inline uint32_t list_ranges(const Tab &t) {
+    return (t.nwords() + list_words(t) - 1) / list_words(t);
+}
 
 // Every thread of the workgroup calls; the last list is no longer read.
 __device__ __forceinline__ uint32_t list_cells(const Tab &t, uint32_t range, CellList &L) {
-    const uint32_t j = range * kListWords + (threadIdx.x >> 2), sh = 8 * (threadIdx.x & 3);
-    uint32_t w = j < t.nwords() ? (t.occ[j] >> sh) & 0xffu : 0u;
+    const uint32_t nw = list_words(t), j = range * nw + (threadIdx.x >> 2), sh = 8 * (threadIdx.x & 3);
+    uint32_t w = (threadIdx.x >> 2) < nw && j < t.nwords() ? (t.occ[j] >> sh) & 0xffu : 0u;
     if (threadIdx.x == 0) L.n = 0;
     __syncthreads();
     if (w) {

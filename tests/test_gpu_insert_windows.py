@@ -54,8 +54,8 @@ def _keys(ids):
 
 @pytest.mark.parametrize("n,distinct,m", [
     (1, 1, 4), (63, 9, 5), (1023, 1023, 12), (1024, 1, 4), (1025, 700, 12), (4097, 4097, 14), (5000, 3, 6),
-    (64 * 1024, 30000, 17), (1 << 17, 60000, 18), ((1 << 17) + 1, (1 << 17) + 1, 19), (140001, 3, 6), (150000, 1, 4),
-    (256 * 1024, 256 * 1024, 20), (525000, 1793, 17), (1 << 21, 900000, 22)])
+    (64 * 1024, 30000, 17), (5 << 16, 60000, 18), ((5 << 16) + 1, (5 << 16) + 1, 20), (330001, 3, 6), (350000, 1, 4),
+    (512 * 1024, 512 * 1024, 20), (525000, 1793, 17), (1 << 21, 900000, 22)])
 def test_edges_of_steps_windows_and_bins(gpu, n, distinct, m):
     rng = np.random.default_rng(n + m)
     ids = np.concatenate([np.arange(distinct), rng.integers(0, distinct, n - distinct)])
@@ -70,11 +70,11 @@ def test_edges_of_steps_windows_and_bins(gpu, n, distinct, m):
     (8, 1.0e13, 2000),     # sums near the top of 64 bits
     (24, 1.0, 4096)])      # one cell for a whole window
 def test_groups_of_more_than_one_record(gpu, frac_bits, scale, per):
-    n = 140000
+    n = 330000
     rng = np.random.default_rng(per)
     rgb = (rng.random((3, n), dtype=np.float32) * np.float32(scale)).astype(np.float32)
     rgb[1] = -rgb[1]
-    _insert_and_compare(_keys(np.arange(n) // per), rgb, 19, frac_bits)
+    _insert_and_compare(_keys(np.arange(n) // per), rgb, 20, frac_bits)
 
 
 def test_full_bucket_and_several_passes(gpu):
@@ -163,3 +163,56 @@ def test_atomic_insert_of_binary32_sums(gpu, n, agg):
         total = np.bincount(ids[live], weights=rgb[c][live].astype(np.float64), minlength=ids.max() + 1)[ids]
         want = (total.astype(np.float32) / want_cnt.clip(1).astype(np.float32))
         assert_bits_equal(out[c].cpu().numpy()[live], want[live], "average")
+
+
+@pytest.mark.parametrize("m", [4, 7, 9, 13, 14, 18, 19, 21])
+def test_blend_visits_every_cell_once(gpu, m):
+    """Ranges of 8 to 64 bitmap words: with the same cells in the previous table
+    every one is found, and the blend of equal values returns them."""
+    n = (1 << m) // 2
+    key = _keys(np.arange(n))
+    k = torch.from_numpy(key.view(np.int64)).cuda()
+    c = torch.from_numpy(np.arange(n, dtype=np.float32) % 1024).cuda()  # halves and doubles of them are exact
+    fl = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    tabs = [pf.Table(m, 1 << min(m, 10)) for _ in range(2)]
+    for t in tabs:
+        pf.table_init(t)
+        pf.insert_accumulate(t, k, c, c, c, fl, None, 0)
+    pf.temporal_update(tabs[1], None, 0.5)
+    pf.temporal_update(tabs[0], tabs[1], 0.5)
+    out = [torch.empty(n, device="cuda") for _ in range(3)]
+    pf.query_average(tabs[0], k, None, c, c, c, fl, True, *out)
+    torch.cuda.synchronize()
+    assert not fl.any().item()
+    assert int(pf.read_stats(tabs[0])[pf.STAT_TEMPORAL_HIT]) == n
+    for o in out:
+        assert torch.equal(o, c)
+
+
+@pytest.mark.parametrize("probe", [1, 2, 3, 4, 5, 6, 9, 16])
+def test_small_call_claims_within_max_probe(gpu, probe):
+    """A small call reads the slots after the home slot four at a time: placed
+    keys lie less than max_probe slots from home with no empty slot before them,
+    and the others find all of their slots taken."""
+    m, n = 5, 96
+    key = _keys(np.arange(n) % 48 + 1000 * probe)
+    t = pf.Table(m, probe)
+    pf.table_init(t)
+    k = torch.from_numpy(key.view(np.int64)).cuda()
+    one = torch.ones(n, device="cuda")
+    fl = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    ws = torch.empty(pf.insert_workspace_bytes(n, m), dtype=torch.uint8, device="cuda")
+    pf.insert_accumulate_binned(t, k, one, one, one, fl, slot, ws)
+    torch.cuda.synchronize()
+    flags, slots = fl.cpu().numpy(), slot.cpu().numpy()
+    taken = table_contents(t)["occupied"].astype(bool)
+    home, _ = oracle.key_hashes(key, m)
+    for i in range(n):
+        window = (int(home[i]) + np.arange(probe)) % (1 << m)
+        if flags[i] == 0:
+            d = (int(slots[i]) - int(home[i])) % (1 << m)
+            assert d < probe and taken[window[:d + 1]].all()
+        else:
+            assert flags[i] == pf.V_OVERFLOW and slots[i] == -1 and taken[window].all()
+    assert (flags != 0).any() or probe == 16
