@@ -146,7 +146,9 @@ class FrameFilter:
         """Filters one frame; returns (r_out, g_out, b_out) (in place if out is (r, g, b)).
         mlp_timing: optional 4 events for the learned fallback's stages (MlpFallback.apply)."""
         n = px.numel()
-        key, vflags, slot = self.key[:n], self.vflags[:n], self.slot[:n]
+        key, vflags, slot = self.key, self.vflags, self.slot
+        if n != key.numel():
+            key, vflags, slot = key[:n], vflags[:n], slot[:n]
         cnt = self.count[:n] if (with_count or self.mlp is not None) else None
         cur = self.cur
         if not self._cur_clean:
