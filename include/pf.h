@@ -615,9 +615,8 @@ typedef struct pf_view {
 
 /* [host] Device workspace bytes of pf_filter_views for nviews views of n[v]
  * vertices and tables of 2^log2_slots[v] slots (host arrays), enough for
- * every workgroup size: barrier counters, the device copy of the
- * descriptors, and per view the records of its insert (32 bytes, about two
- * per vertex) with their bucket counts.  0 for bad arguments. */
+ * every workgroup size: barrier counters and the device copy of the
+ * descriptors.  0 for bad arguments. */
 size_t pf_views_workspace_bytes(const uint64_t *n, const uint32_t *log2_slots, uint32_t nviews);
 
 /* [host] Device workspace bytes of pf_filter_views_concurrent: the binned
@@ -645,7 +644,7 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  * resident workgroups of `block` threads), in four phases separated by
  * grid-wide barriers, the work items of all views spread over all
  * workgroups:
- *   clear      every view's `cur` and its bucket counts;
+ *   clear      every view's `cur`;
  *   insert     keys of every vertex (as pf_build_keys) and its cell
  *              (Sections 3.2, 3.3.1): agg_width 0 claims the cell and adds
  *              count and sums with one set of device atomics per vertex;
@@ -654,12 +653,9 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  *              ones by key in an LDS table of min(agg_width, 4 x block, 1536)
  *              entries, in as many windows as the table needs (a vertex that
  *              finds no room goes alone); each group claims its cell once and
- *              writes one record {slot, count, sums} into the bucket of its
- *              bin of min(2 x block, 2048) slots (a full bucket adds the
- *              group with device atomics instead);
- *   reduce     per bin, the records summed and added to the cells by one
- *              workgroup, then, when temporal is set, the temporal values of
- *              the bin's cells (as pf_temporal_update, mode 0, Section 3.4.1);
+ *              adds count and sums with one set of device atomics;
+ *   temporal   when temporal is set, the temporal values of the occupied cells
+ *              (as pf_temporal_update, mode 0, Section 3.4.1);
  *   lookup     every vertex (as pf_query_average with the slots), and,
  *              in the same phase, `prev` emptied (as pf_clear): the temporal
  *              blend has read it for the last time, so that a caller who
@@ -677,7 +673,7 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  * resident, so it stays 0); the next words hold the grid size and, after a
  * timed-out wait, the arrivals that were seen; words 4..13 hold five 64-bit
  * wall-clock readings of workgroup 0 (start, end of clear, of insert, of
- * reduce, of its own lookup), in ticks of pf_wall_clock_hz().
+ * the temporal phase, of its own lookup), in ticks of pf_wall_clock_hz().
  * Errors: PF_EINVAL (NULL, misaligned, inconsistent descriptor, a
  * PF_SUMS_FLOAT32 table, workspace too small), PF_ERANGE (nviews 0 or above
  * PF_MAX_VIEWS, block, agg_width, parameters), PF_ELAUNCH. */

@@ -295,7 +295,7 @@ class MultiViewFilter:
 
     def phase_us(self):
         """Microseconds of the last launch's phases as seen by workgroup 0:
-        clear, keys + insert, reduce with the temporal values, lookup."""
+        clear, keys + insert, temporal values, lookup."""
         w = self.ws[:64].view(torch.int32).cpu().numpy().view("uint32").astype("uint64")
         t = [int(w[4 + 2 * k]) | (int(w[5 + 2 * k]) << 32) for k in range(5)]
         hz = int(_lib.lib.pf_wall_clock_hz()) or 100_000_000

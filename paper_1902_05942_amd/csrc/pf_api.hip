@@ -588,7 +588,7 @@ size_t pf_views_workspace_bytes(const uint64_t *n, const uint32_t *log2_slots, u
     if (!n || !log2_slots || nviews == 0 || nviews > PF_MAX_VIEWS) return 0;
     for (uint32_t v = 0; v < nviews; ++v)
         if (n[v] > kMaxN || log2_slots[v] < 4 || log2_slots[v] > 30) return 0;
-    return pfk::views_workspace_bytes(n, log2_slots, nviews);
+    return pfk::views_workspace_bytes(nviews);
 }
 
 namespace {
@@ -757,15 +757,8 @@ pf_status pf_filter_views(const pf_view *views, uint32_t nviews, uint32_t block,
                 views[u].prev.cell == views[v].cur.cell)
                 return PF_EINVAL;
     }
-    uint64_t n[PF_MAX_VIEWS];
-    uint32_t lg[PF_MAX_VIEWS];
-    for (uint32_t v = 0; v < nviews; ++v) {
-        n[v] = views[v].n;
-        lg[v] = views[v].cur.log2_slots;
-    }
-    if (workspace_bytes < pfk::views_workspace_bytes(n, lg, nviews)) return PF_EINVAL;
-    return launched(pfk::launch_views(views, nviews, block, agg_width, grid_per_cu, workspace, workspace_bytes,
-                                      (hipStream_t)stream));
+    if (workspace_bytes < pfk::views_workspace_bytes(nviews)) return PF_EINVAL;
+    return launched(pfk::launch_views(views, nviews, block, agg_width, grid_per_cu, workspace, (hipStream_t)stream));
 }
 
 pf_status pf_microbench(int kind, void *buf, uint64_t bytes, uint32_t grain, uint32_t accesses_per_thread,

@@ -230,3 +230,32 @@ def test_views_without_temporal_blend_concurrent_equals_persistent(gpu):
                 assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (frame, v)
             for name in ("vflags", "count"):
                 assert torch.equal(filters[0].bufs[v][name][:n], filters[1].bufs[v][name][:n]), (frame, v, name)
+
+
+@pytest.mark.parametrize("block", [64, 256, 1024])
+@pytest.mark.parametrize("n,m", [(1, 7), (65, 9), (1030, 12), (9000, 13)])
+def test_small_ragged_views_equal_single_calls(gpu, block, n, m):
+    """Three frames of two small views in one launch against one call each: the
+    values, counts and flags are the same bits."""
+    rng = np.random.default_rng(n + block)
+    mv = pf.MultiViewFilter([(n, m), (n + 3, m + 1)], mode="persistent")
+    single = [pf.FrameFilter(k, lg, temporal=True, fused=True) for k, lg in ((n, m), (n + 3, m + 1))]
+    for frame in range(3):
+        frames = []
+        for k in (n, n + 3):
+            f = {c: torch.from_numpy(rng.random(k, dtype=np.float32) * np.float32(0.05)).cuda()
+                 for c in ("px", "py", "pz", "r", "g", "b")}
+            f.update(nx=torch.zeros(k, device="cuda"), ny=torch.zeros(k, device="cuda"),
+                     nz=torch.ones(k, device="cuda"), cam=(0.0, 0.0, 2.0), s=0.01, seed=17 + frame,
+                     valid=torch.from_numpy((rng.random(k) < 0.9).astype(np.uint8)).cuda())
+            frames.append(f)
+        got = mv.filter(frames, block=block, with_count=True)
+        assert mv.status() == 0
+        for v, (f, flt) in enumerate(zip(frames, single)):
+            a = {x: f[x] for x in ("px", "py", "pz", "nx", "ny", "nz", "valid", "r", "g", "b", "cam", "s", "seed")}
+            want = flt.filter(**a, with_count=True)
+            k = f["px"].numel()
+            assert torch.equal(mv.bufs[v]["vflags"][:k], flt.vflags[:k])
+            assert torch.equal(mv.bufs[v]["count"][:k], flt.count[:k])
+            for x, y in zip(got[v], want):
+                assert torch.equal(x.view(torch.int32), y.view(torch.int32))
