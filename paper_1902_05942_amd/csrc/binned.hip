@@ -1,6 +1,6 @@
 // Insert-accumulate without device atomics on the cell sums, for gfx950.
 //
-// Device atomics run at ~24 G/s on MI355X whatever the footprint, and a
+// Device atomics run at ~24 G lines/s on MI355X whatever the footprint, and a
 // random access of any kind moves a whole cache line, so the cost of the
 // insert is the number of per-cell operations it sends to memory.  This path
 // sends one per group of vertices that share a key within a window of up to
@@ -26,14 +26,14 @@
 // Integer sums make the result identical to the atomic insert.
 //
 // What it measured (MI355X; all launches of one call, the temporal blend in
-// reduce): 1920x1080x3 vertices (1.1M groups) 161 us, 3840x2160x4 (11M groups)
-// 815 us, 401x229x3 40 us, 64x64 35 us.  The counting sort it replaces (a
-// record of 32 bytes staged per workgroup, histograms scanned over the
-// workgroups, records scattered to their bins' ranges, LDS sums for every slot
-// of a bin, windows of a fixed 4096 vertices) took 234, 1544, 96 and 85 us:
-// incoherent vertices hardly merge, so the records' way through memory is what
-// the insert costs, and a window of mostly distinct keys overflowed its LDS
-// table and sent its vertices to the table one by one.
+// reduce): 1920x1080x3 vertices (1.1M groups) 163 us, 3840x2160x4 (11M groups)
+// 815 us.  The counting sort it replaces (a record of 32 bytes staged per
+// workgroup, histograms scanned over the workgroups, records scattered to their
+// bins' ranges, LDS sums for every slot of a bin, windows of a fixed 4096
+// vertices) took 234 and 1544 us: incoherent vertices hardly merge, so the
+// records' way through memory is what the insert costs, and a window of mostly
+// distinct keys overflowed its LDS table and sent its vertices to the table one
+// by one.  Small calls go another way (small_insert_kernel).
 #include <mutex>
 #include <type_traits>
 
@@ -610,8 +610,14 @@ struct Blend {
 // requested before the records are summed, and records are read a batch ahead
 // (256 bins and one workgroup of 1024 threads a CU: 3840x2160x4 190 -> 134 us, 8M
 // incoherent keys 206 -> 145 us, 1920x1080x3 40 -> 38 us).
+// A bin of more than kMaxPasses passes' cells (tables of 2^23 slots and more,
+// well filled) sends its records to the cells by device atomics instead, once:
+// 33M keys in a 2^25-slot table, all launches, passes / atomics at loads 0.15
+// (4.8 passes) 2526 / 2905 us, 0.2 (6.4) 3025 / 3053, 0.3 3813 / 3316, 0.5 4947 /
+// 3773, 0.7 5922 / 4111.
 // kBlend: it also computes the temporal values of the cells (which are final:
 // every record of a slot is in the slot's bin), as pf_temporal_update does.
+constexpr uint32_t kMaxPasses = 6;
 template <bool kBlend = false, bool kHasPrev = false, bool kIntegrate = false>
 __global__ __launch_bounds__(kR) __attribute__((amdgpu_waves_per_eu(4, 4))) void reduce_kernel(Tab t, Buckets bk, Blend bl) {
     extern __shared__ unsigned long long lred[];
@@ -702,6 +708,27 @@ __global__ __launch_bounds__(kR) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         // occupancy: the words of this bin belong to this workgroup
         if (v) t.occ[(base >> 5) + w] |= v;
     }
+    const bool direct = ncells > kMaxPasses * kCells;
+    if (direct) {
+        for (uint32_t j0 = 0; j0 < m; j0 += kR) {  // uniform: accumulate_wave is the wavefront's
+            uint32_t slot = kNoSlot, c = 0;
+            int64_t v[3] = {0, 0, 0};
+            if (j0 + tid < m) {
+                const uint4 q = *record(j0 + tid);
+                const bool high = q.x >> 31;
+                slot = base + (q.x & in_bin);
+                c = (q.x >> kSlotBits) & kCountMask;
+                c = high ? 64u * c : 1u + c;
+                const uint32_t w[3] = {q.y, q.z, q.w};
+                for (int k = 0; k < 3; ++k) v[k] = high ? (int64_t)((uint64_t)w[k] << 32) : (int64_t)(int32_t)w[k];
+            }
+            accumulate_wave(t, slot, c, v[0], v[1], v[2]);
+        }
+        if (!kBlend) return;
+        __threadfence();  // the cells are read below by other threads of the workgroup
+        __syncthreads();
+        __threadfence();
+    }
     uint32_t hits = 0;
     for (uint32_t c0 = 0; c0 < ncells; c0 += kCells) {
         const uint32_t nc = min(ncells - c0, kCells);
@@ -762,7 +789,7 @@ __global__ __launch_bounds__(kR) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         uint4 q[kHold];
 #pragma unroll
         for (uint32_t u = 0; u < kHold; ++u) q[u] = held[u];
-        for (uint32_t j0 = 0; j0 < m; j0 += kHold * kR) {
+        for (uint32_t j0 = 0; j0 < (direct ? 0u : m); j0 += kHold * kR) {
             uint4 ahead[kHold];
             load_records(j0 + kHold * kR, ahead);
 #pragma unroll

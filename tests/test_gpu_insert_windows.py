@@ -216,3 +216,40 @@ def test_small_call_claims_within_max_probe(gpu, probe):
         else:
             assert flags[i] == pf.V_OVERFLOW and slots[i] == -1 and taken[window].all()
     assert (flags != 0).any() or probe == 16
+
+
+def test_bins_of_more_cells_than_passes_pay(gpu):
+    # half of the table's bins hold ~13,300 cells each: their records go to the
+    # cells by device atomics
+    m = 24
+    cand = _keys(np.arange(1, 3400000))
+    home, _ = oracle.key_hashes(cand, m)
+    chosen = cand[home < np.uint32(1 << (m - 1))]
+    rng = np.random.default_rng(9)
+    key = np.concatenate([chosen, chosen[rng.integers(0, len(chosen), 200000)]])
+    rng.shuffle(key)
+    assert len(chosen) > 128 * 6 * 2048 and len(key) < 1 << 22
+    _insert_and_compare(key, (rng.random((3, len(key))) * 300 - 150).astype(np.float32), m)
+
+
+@pytest.mark.parametrize("max_samples", [None, 3])
+def test_blend_of_bins_of_many_cells(gpu, max_samples):
+    """3.5M vertices, nearly every one a cell of its own: the fused insert with
+    the blend against the atomic insert and the temporal pass."""
+    n, m = 3500000, 23
+    g = torch.Generator(device="cuda").manual_seed(4)
+    f = {c: torch.rand(n, device="cuda", generator=g) for c in ("px", "py", "pz", "r", "g", "b")}
+    f.update(nx=torch.zeros(n, device="cuda"), ny=torch.zeros(n, device="cuda"), nz=torch.ones(n, device="cuda"),
+             valid=torch.ones(n, dtype=torch.uint8, device="cuda"), cam=(0.0, 0.0, 3.0), s=0.0008)
+    fused = pf.FrameFilter(n, m, fused=True, max_samples=max_samples)
+    apart = pf.FrameFilter(n, m, agg_width=64, max_samples=max_samples)
+    for seed in (5, 5, 6):
+        a = fused.filter(**f, seed=seed, with_count=True)
+        b = apart.filter(**f, seed=seed, with_count=True)
+        used = int(pf.read_stats(fused.tables[1])[pf.STAT_USED])
+        assert used > 256 * 6 * 2048 and used == int(pf.read_stats(apart.tables[1])[pf.STAT_USED])
+        assert int(pf.read_stats(fused.tables[1])[pf.STAT_TEMPORAL_HIT]) == \
+            int(pf.read_stats(apart.tables[1])[pf.STAT_TEMPORAL_HIT])
+        assert not fused.vflags.any().item() and torch.equal(fused.count, apart.count)
+        for x, y in zip(a, b):
+            assert torch.equal(x.view(torch.int32), y.view(torch.int32))
