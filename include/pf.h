@@ -225,8 +225,9 @@ size_t pf_insert_workspace_bytes(uint64_t n, uint32_t log2_slots);
  * occupancy bits.  Compare-and-swap remains only for claiming new cells.  (A
  * bucket holds twice what evenly spread keys can fill; groups that find it
  * full go to their cells by device atomics.  Calls of up to 5 * 2^16 vertices
- * use no workspace: every vertex claims its cell and adds to it by device
- * atomics; with a temporal blend its pass over the table follows.)
+ * use no workspace: the vertices of a workgroup (256 to 1024) that share a key
+ * are merged in LDS and go to their cell by device atomics; with a temporal
+ * blend its pass over the table follows.)
  * slot_out is required.  workspace: pf_insert_workspace_bytes(n, log2_slots)
  * device bytes (caller-owned, no alignment needed).
  * Errors: PF_EINVAL (NULL, misaligned, workspace too small, a

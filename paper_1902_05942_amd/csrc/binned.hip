@@ -53,6 +53,7 @@ constexpr uint32_t kCap = 1920;              // LDS entries of a window
 constexpr uint32_t kLimit = kCap / 8 * 7;    // seven eighths full, a free entry is still a few probes away
 constexpr uint32_t kMaxLog2Slots = 25;
 constexpr uint32_t kSmall = 5u << 16;        // vertices up to which a call has one launch (and the blend's)
+constexpr uint32_t kSmallGroups = 192;       // workgroups of such a call before they get twice the threads
 constexpr uint32_t kMinWindowed = 1u << 19;  // vertices from which pf_insert_accumulate merges by windows
 constexpr uint32_t kMaxBins = 512, kMaxParts = 8;
 constexpr uint32_t kMaxLog2BinSlots = 17;    // the bin's bitmap and its prefix counts take 32 KB of LDS
@@ -539,22 +540,42 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     if (tid == 0 && misc[0]) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], misc[0]);
 }
 
-// The insert of a small call: a vertex per thread, its key (kKeys), its cell,
-// and device atomics after the threads of a workgroup that reach the same slot
-// have combined their contributions (pf_insert_accumulate with agg_width 256,
-// keys included).  Bound by its one chain of latencies: 64x64 vertices with the
-// blend's launch take 16 us of kernels against 35 through the buckets; whole
-// frames by buckets -> by vertices: 290x170x3 49 -> 39 us, 401x229x3 48 -> 43,
-// 512x384x3 59 -> 58, 720x450x3 73 -> 73, but coherent ones 560x400x1 40 -> 42 and
-// 800x600x1 51 -> 60, so kSmall is 5 * 2^16.
-template <bool kKeys>
-__global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint64_t *__restrict__ key,
-                                                              const float *__restrict__ r, const float *__restrict__ g,
-                                                              const float *__restrict__ b, uint8_t *__restrict__ flags,
-                                                              uint32_t *__restrict__ slot_out, uint32_t n,
-                                                              FusedKeys fk) {
-    __shared__ AggLds<kBlock> L;
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+// The insert of a small call: a vertex per thread; a workgroup's vertices merge
+// by key in an LDS table (keys included, kKeys), the thread that made a key's
+// entry claims its cell and adds the sums by device atomics.  Bound by its one
+// chain of latencies where cells are many, and by the visits of the workgroups
+// to the same few cells where voxels are coarse: a compare-and-swap and a line
+// of atomics each, and every workgroup meets the empty cell.  (With a claim per
+// vertex 300k vertices of one cell took 1100 us, this 16; whole frames of
+// 401x229x3 at cell size 0.01 / 1 / 10: 42.8 / 281 / 356 -> 42.7 / 38.7 / 39.9 us.)
+// So the threads a workgroup double at kSmallGroups workgroups (512 threads at
+// 401x229x3: 41.6 / 57 / 77 us; 1024 at 64x64: 27.6 against 20.4), and beyond
+// kSmallGroups of 1024 the slots after the home slot are read one at a time:
+// kAhead 4 saves a small call latency (200x150x3 43.4 -> 37.9 us) but reads the
+// lines that others are claiming (401x229x3 at cell size 10: 40 -> 56).
+// Whole frames by buckets -> this: 290x170x3 48 -> 38 us, 401x229x3 46 -> 43,
+// 430x250x3 49 -> 46, 570x570x1 39 -> 34, 400x400x2 44.5 -> 45, so kSmall is
+// 5 * 2^16.
+template <bool kKeys, uint32_t kSmallT, uint32_t kAhead>
+__global__ __launch_bounds__(kSmallT) void small_insert_kernel(Tab t, const uint64_t *__restrict__ key,
+                                                               const float *__restrict__ r,
+                                                               const float *__restrict__ g,
+                                                               const float *__restrict__ b,
+                                                               uint8_t *__restrict__ flags,
+                                                               uint32_t *__restrict__ slot_out, uint32_t n,
+                                                               FusedKeys fk) {
+    // LDS entries: never full; two workgroups of 1024 fit a CU
+    constexpr uint32_t kSmallCap = kSmallT < 1024 ? 2 * kSmallT : kSmallT / 2 * 3;
+    __shared__ unsigned long long lkey[kSmallCap], lsum[3][kSmallCap];
+    __shared__ uint32_t lcnt[kSmallCap], lslot[kSmallCap];
+    for (uint32_t j = threadIdx.x; j < kSmallCap; j += kSmallT) {
+        lkey[j] = kEmpty;
+        lsum[0][j] = 0;
+        lsum[1][j] = 0;
+        lsum[2][j] = 0;
+        lcnt[j] = 0;
+    }
+    const uint32_t i = blockIdx.x * kSmallT + threadIdx.x;
     const bool in = i < n;
     uint32_t f = PF_V_INVALID;
     if constexpr (kKeys) {
@@ -565,7 +586,6 @@ __global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint6
     const uint32_t f0 = f;
     uint64_t k = 0;
     int64_t q0 = 0, q1 = 0, q2 = 0;
-    uint32_t slot = kNoSlot;
     if (f == 0) {
         const VertexIn<kKeys> vin = load_vertex<kKeys>(fk, key, r, g, b, i);
         uint32_t rnd[3] = {0, 0, 0};
@@ -574,20 +594,44 @@ __global__ __launch_bounds__(kBlock) void small_insert_kernel(Tab t, const uint6
             for (int d = 0; d < 3; ++d) rnd[d] = jp.output(d, i);
         }
         f = vertex_value<kKeys>(fk, vin, rnd, t.frac_bits, k, q0, q1, q2);
-        if (f == 0) {
-            slot = find_or_claim<4>(t, k);
-            if (slot == kNoSlot) {
-                f = PF_V_OVERFLOW;
-                add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
-            }
+    }
+    __syncthreads();
+    int e = -1;
+    bool claims = false;  // this thread claims a cell: for its entry, or alone
+    uint32_t slot = kNoSlot;
+    if (f == 0) {
+        // (a caller's key may be the empty entry's)
+        if (kKeys || k != kEmpty) e = lds_insert(lkey, kSmallCap, k, claims);
+        if (e >= 0) {
+            atomicAdd(&lcnt[e], 1u);
+            lds_add(&lsum[0][e], q0);
+            lds_add(&lsum[1][e], q1);
+            lds_add(&lsum[2][e], q2);
+        } else {
+            claims = true;
         }
+        if (claims) slot = find_or_claim<kAhead>(t, k);
+        if (claims && e >= 0) lslot[e] = slot;
+    }
+    __syncthreads();
+    uint32_t cnt = 1;
+    if (e >= 0) {
+        cnt = lcnt[e];
+        q0 = (int64_t)lsum[0][e];
+        q1 = (int64_t)lsum[1][e];
+        q2 = (int64_t)lsum[2][e];
+        if (!claims) slot = lslot[e];
+    }
+    if (f == 0 && slot == kNoSlot) {
+        f = PF_V_OVERFLOW;
+        if (claims) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], (unsigned long long)cnt);
     }
     if (in) {
         if (kKeys && fk.key_out) fk.key_out[i] = k;
         if (kKeys || f != f0) flags[i] = (uint8_t)f;
         slot_out[i] = slot;
     }
-    accumulate_group<kBlock, int64_t>(t, L, kBlock, slot, q0, q1, q2);
+    accumulate_wave(t, claims ? slot : kNoSlot, cnt, q0, q1, q2);
 }
 
 // The temporal blend done by reduce: the previous table (has_prev) and the
@@ -869,8 +913,17 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
                       uint8_t *flags, uint32_t *slot_out, uint32_t n, void *ws, const FusedKeys &fk,
                       const Blend *blend, bool has_prev, bool integrate, hipStream_t st) {
     if (n <= kSmall) {
-        small_insert_kernel<kKeys><<<(n + kBlock - 1) / kBlock, kBlock, 0, st>>>(t, key, r, g, b, flags, slot_out, n,
-                                                                               fk);
+        const auto launch = [&](auto kernel, uint32_t threads) {
+            kernel<<<(n + threads - 1) / threads, threads, 0, st>>>(t, key, r, g, b, flags, slot_out, n, fk);
+        };
+        if (n <= kSmallGroups * 256)
+            launch(small_insert_kernel<kKeys, 256, 4>, 256);
+        else if (n <= kSmallGroups * 512)
+            launch(small_insert_kernel<kKeys, 512, 4>, 512);
+        else if (n <= kSmallGroups * 1024)
+            launch(small_insert_kernel<kKeys, 1024, 4>, 1024);
+        else
+            launch(small_insert_kernel<kKeys, 1024, 1>, 1024);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !blend) return e;
         return launch_temporal(t, has_prev ? &blend->prev : nullptr, blend->alpha, integrate ? 1 : 0, blend->cap, st);
