@@ -226,6 +226,25 @@ __device__ __forceinline__ uint32_t find_or_claim(const Tab &t, uint64_t key) {
     return claim_from<true, kAhead>(t, key, fingerprint_of(key), home_of(key, t.mask), 0);
 }
 
+// The same for a wavefront, neighbouring lanes with the same key claiming once;
+// all 64 lanes must call (want: the lane has a key).  At the start of a call
+// every lane finds its cell empty: without this a compare-and-swap each waits for
+// the others of its address (300k vertices of one cell, agg_width 64: 600 .. 1200
+// us, now 102; of 10000 cells in order 30 -> 12, in random order 33 -> 37; frames of
+// 640x360x3, agg_width 0 / 64, without windows 47 / 42 -> 44 / 41).
+__device__ __forceinline__ uint32_t find_or_claim_runs(const Tab &t, uint64_t key, bool want) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t wants = __ballot(want);
+    const uint64_t before = shfl64(key, (int)(lane ? lane - 1 : 0));
+    const bool head = want && (lane == 0 || !((wants >> (lane - 1)) & 1) || before != key);
+    const uint64_t heads = __ballot(head);
+    uint32_t slot = kNoSlot;
+    if (head) slot = find_or_claim(t, key);
+    const uint64_t upto = heads & (~0ull >> (63 - lane));
+    slot = (uint32_t)__shfl((int)slot, upto ? 63 - __builtin_clzll(upto) : 0);
+    return want ? slot : kNoSlot;
+}
+
 // Probe without claiming (lookup after insertion).
 __device__ __forceinline__ uint32_t find_slot(const Tab &t, uint64_t key) {
     const uint32_t f = fingerprint_of(key);

@@ -85,13 +85,10 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(Tab t, const uint64_t *_
         else
             fl = fixed_point(r[i], g[i], b[i], t.frac_bits, q0, q1, q2);
     }
-    uint32_t slot = kNoSlot;
-    if (fl == 0) {
-        slot = find_or_claim(t, key[i]);
-        if (slot == kNoSlot) {
-            fl = PF_V_OVERFLOW;
-            add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
-        }
+    const uint32_t slot = find_or_claim_runs(t, fl == 0 ? key[i] : 0ull, fl == 0);
+    if (fl == 0 && slot == kNoSlot) {
+        fl = PF_V_OVERFLOW;
+        add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
     }
     if (in && fl != fl0) flags[i] = fl;
     if (in && slot_out) slot_out[i] = slot;

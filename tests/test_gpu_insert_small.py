@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_1902_05942_amd as pf
-from gpu_util import check_frame_against_oracle, gpu_frame, to_dev
+from gpu_util import check_frame_against_oracle, gpu_frame, table_contents, to_dev
 from test_gpu_insert_windows import _insert_and_compare, _keys
 
 pytestmark = pytest.mark.gpu
@@ -98,3 +98,39 @@ def test_binned_insert_of_one_cell_is_not_slow(gpu, n):
     one, many = (times_of_cells(n, 20, cells, insert) for cells in (1, n))
     print(f"{n} vertices: one cell {one:.1f} us, each its own {many:.1f} us", flush=True)
     assert one < 3 * many
+
+
+@pytest.mark.parametrize("n", [50000, 300000])
+def test_atomic_insert_of_one_cell_is_not_slow(gpu, n):
+    """As above for the insert by device atomics, 64 lanes combined."""
+    def insert(t, k, c, fl, slot, ws):
+        pf.insert_accumulate(t, k, c, c, c, fl, slot, 64)
+
+    one, many = (times_of_cells(n, 20, cells, insert) for cells in (1, n))
+    print(f"{n} vertices: one cell {one:.1f} us, each its own {many:.1f} us", flush=True)
+    assert one < 3 * many
+
+
+@pytest.mark.parametrize("agg", [0, 64])
+@pytest.mark.parametrize("n,run", [(1, 1), (64, 64), (65, 5), (130, 63), (1000, 64), (4097, 200)])
+def test_atomic_insert_of_runs(gpu, agg, n, run):
+    """Neighbouring vertices with the same key claim once: runs within, across and
+    around wavefronts, cut by flagged vertices."""
+    ids = np.arange(n) // run
+    key = _keys(ids + 1)
+    flags = (np.arange(n) % 11 == 3).astype(np.uint8)
+    t = pf.Table(13, 64)
+    pf.table_init(t)
+    fl, slot = torch.from_numpy(flags).cuda(), torch.empty(n, dtype=torch.int32, device="cuda")
+    c = torch.from_numpy((np.arange(n) % 100 - 50).astype(np.float32)).cuda()
+    pf.insert_accumulate(t, torch.from_numpy(key.view(np.int64)).cuda(), c, c, c, fl, slot, agg)
+    live = flags == 0
+    assert np.array_equal(fl.cpu().numpy(), flags)
+    cells, counts = np.unique(key[live], return_counts=True)
+    tc = table_contents(t)
+    order = np.argsort(tc["key"])
+    assert np.array_equal(tc["key"][order], cells) and np.array_equal(tc["count"][order], counts)
+    at = slot.cpu().numpy()
+    assert (at[~live] == -1).all() and np.array_equal(t.keys().cpu().numpy().view(np.uint64)[at[live]], key[live])
+    want = [int((np.arange(n)[live & (key == k)] % 100 - 50).sum()) << 24 for k in cells]
+    assert np.array_equal(tc["sum"][order][:, 0], np.array(want, np.int64))
