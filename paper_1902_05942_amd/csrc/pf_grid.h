@@ -1,5 +1,5 @@
 // Grid-wide barrier for cooperative launches of resident workgroups on
-// gfx950 (used by the multi-view launch and the multi-step training launch).
+// gfx950 (used by the multi-view launch).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -37,6 +37,7 @@ __device__ __forceinline__ uint32_t poll(uint32_t *p) {
 // sets the status word and returns false (the workgroup then leaves).
 __device__ inline bool grid_barrier(const Barrier &bar, uint32_t epoch) {
     __shared__ uint32_t s_ok;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
