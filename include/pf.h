@@ -643,10 +643,11 @@ size_t pf_views_concurrent_workspace_bytes(const uint64_t *n, const uint32_t *lo
 pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint32_t nstreams, void *workspace,
                                      size_t workspace_bytes, void *stream);
 
-/* Filters nviews views in ONE persistent launch (a cooperative grid of
- * resident workgroups of `block` threads), in four phases separated by
- * grid-wide barriers, the work items of all views spread over all
- * workgroups:
+/* Filters nviews views in four phases, the work items of all views spread over
+ * all workgroups: three in ONE persistent launch (a cooperative grid of resident
+ * workgroups of `block` threads), separated by grid-wide barriers, and the
+ * lookup in a launch after it, which wants more wavefronts a compute unit than
+ * the insert's registers leave:
  *   clear      every view's `cur`;
  *   insert     keys of every vertex (as pf_build_keys) and its cell
  *              (Sections 3.2, 3.3.1): agg_width 0 claims the cell and adds
@@ -666,8 +667,8 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  *              the next launch's clear costs nothing.
  * Results equal those of the single-view calls (integer sums).
  * views: [host] array of nviews descriptors, validated on the host and
- * copied into the workspace before the call returns.  block in
- * {64, 128, 256, 512, 1024}; agg_width 0 or a power of two from block to
+ * copied into the workspace before the call returns.  block (of the persistent
+ * launch) in {64, 128, 256, 512, 1024}; agg_width 0 or a power of two from block to
  * 8 x block; grid_per_cu: workgroups per compute unit (0 = as many as fit).
  * workspace: pf_views_workspace_bytes(n, log2_slots, nviews) device bytes
  * (workspace_bytes gives its size), 256-byte aligned; its first uint32 is a
@@ -676,7 +677,8 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  * resident, so it stays 0); the next words hold the grid size and, after a
  * timed-out wait, the arrivals that were seen; words 4..13 hold five 64-bit
  * wall-clock readings of workgroup 0 (start, end of clear, of insert, of
- * the temporal phase, of its own lookup), in ticks of pf_wall_clock_hz().
+ * the temporal phase, of workgroup 0's own lookup), in ticks of
+ * pf_wall_clock_hz().
  * Errors: PF_EINVAL (NULL, misaligned, inconsistent descriptor, a
  * PF_SUMS_FLOAT32 table, workspace too small), PF_ERANGE (nviews 0 or above
  * PF_MAX_VIEWS, block, agg_width, parameters), PF_ELAUNCH. */

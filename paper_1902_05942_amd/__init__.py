@@ -218,7 +218,7 @@ class FrameFilter:
 
 
 class MultiViewFilter:
-    """Many views filtered per frame, by one persistent launch
+    """Many views filtered per frame, by one persistent launch and the lookup's
     (mode "persistent", pf_filter_views) or by every view's single-view calls
     spread over library streams (mode "concurrent",
     pf_filter_views_concurrent); the same results.

@@ -1,15 +1,16 @@
 // Many views in one persistent launch on gfx950.  A cooperative grid of
-// resident workgroups walks four phases -- clear, keys + insert, temporal blend,
-// lookup -- separated by grid-wide barriers.  Within a phase the work items of
-// all views (chunks of bitmap words, windows of vertices) are dealt to the
-// workgroups round-robin, so small and large views share the whole chip.  Each
-// group of vertices that share a key in a window claims its cell once and adds
-// to it by device atomics, a cell a line (accumulate_wave); the blend lists the
-// occupied cells.  (Records in buckets, a place each by a device atomic, summed
-// per bin of slots in a phase of their own, took more: insert + third phase of
-// 640x360, 800x600, 401x229 and 256x256 x3 277 us against 213, of 1920x1080 and
-// 1280x720 x3 483 against 425, of 200x90 and 150x150 x2 83 against 54.)  The per-vertex and per-cell arithmetic
-// is that of the single-view kernels (pf_ops.h).
+// resident workgroups walks three phases -- clear, keys + insert, temporal blend
+// -- separated by grid-wide barriers; the lookup follows as a launch of its own.
+// Within a phase the work items of all views (chunks of bitmap words, windows of
+// vertices) are dealt to the workgroups round-robin, so small and large views
+// share the whole chip.  Each group of vertices that share a key in a window
+// claims its cell once and adds to it by device atomics, a cell a line
+// (accumulate_wave); the blend lists the occupied cells.  (Records in buckets, a
+// place each by a device atomic, summed per bin of slots in a phase of their own,
+// took more: insert + third phase of 640x360, 800x600, 401x229 and 256x256 x3 277
+// us against 213, of 1920x1080 and 1280x720 x3 483 against 425, of 200x90 and
+// 150x150 x2 83 against 54.)  The per-vertex and per-cell arithmetic is that of the
+// single-view kernels (pf_ops.h).
 #include <algorithm>
 
 #include "pf_grid.h"
@@ -28,7 +29,6 @@ using grid::kSubCounters;
 using grid::poll;
 
 constexpr int kIters = 8;            // block-sized steps per work item
-constexpr int kLook = 8;             // of them in flight at a time in the lookup
 
 __device__ __forceinline__ Tab to_tab(const pf_table &t) {
     Tab k;
@@ -67,7 +67,7 @@ struct Lds {
         } m;
         uint32_t cells[8 * B];  // blend: the occupied slots of a range
     };
-    uint32_t first[5][PF_MAX_VIEWS + 1];  // per item kind: first global item of each view
+    uint32_t first[3][PF_MAX_VIEWS + 1];  // per item kind: first global item of each view
     uint32_t hits, nlist, per_item, per_range;
 };
 
@@ -127,9 +127,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
     __shared__ Lds<B> L;
     constexpr uint32_t kItem = (uint32_t)B * kIters;
     // work items per view and kind: 0 clear cur (B bitmap words), 1 keys + insert
-    // (agg vertices, or 8 x B), 2 temporal (a range of bitmap words), 3 clear prev
-    // (B bitmap words), 4 lookup (8 x B vertices); kinds 3 and 4 share the last
-    // phase
+    // (agg vertices, or 8 x B), 2 temporal (a range of bitmap words)
     if (threadIdx.x == 0) {
         // items of the insert: agg vertices, fewer where the views would not
         // give every workgroup three
@@ -145,19 +143,18 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
         uint32_t per_item = agg ? agg : kItem;
         while (agg && per_item > (uint32_t)B && (uint64_t)per_item * 3 * gridDim.x > total) per_item /= 2;
         L.per_item = per_item;
-        uint32_t acc[5] = {0, 0, 0, 0, 0};
+        uint32_t acc[3] = {0, 0, 0};
         for (uint32_t v = 0; v < nviews; ++v) {
             const pf_view &d = views[v];
             const uint32_t words = ((1u << d.cur.log2_slots) + 31) / 32;
-            const uint32_t items[5] = {(words + B - 1) / B, (d.n + per_item - 1) / per_item,
-                                       d.temporal ? (words + per_range - 1) / per_range : 0u,
-                                       d.prev.cell ? (words + B - 1) / B : 0u, (d.n + kItem - 1) / kItem};
-            for (int p = 0; p < 5; ++p) {
+            const uint32_t items[3] = {(words + B - 1) / B, (d.n + per_item - 1) / per_item,
+                                       d.temporal ? (words + per_range - 1) / per_range : 0u};
+            for (int p = 0; p < 3; ++p) {
                 L.first[p][v] = acc[p];
                 acc[p] += items[p];
             }
         }
-        for (int p = 0; p < 5; ++p) L.first[p][nviews] = acc[p];
+        for (int p = 0; p < 3; ++p) L.first[p][nviews] = acc[p];
     }
     // block 0 stamps the start and the end of every phase (wall clock, as
     // 64-bit values in status words 4..13) for the caller's diagnostics
@@ -429,55 +426,86 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
         __syncthreads();  // the list is read; the next range's follows
         if (threadIdx.x == 0 && L.hits) add_u64(&cur.stats[PF_STAT_PART_HIT + (blockIdx.x & 31)], L.hits);
     }
-    if (!grid_barrier(bar, 3)) return;
+    // no barrier after it: the lookup is a launch of its own, workgroup 0 stamps
+    // its own end
     stamp(3);
+}
 
-    // ---- phase 3: empty the previous tables (read for the last time by the
-    // temporal blend), then look up every vertex; the clear's items come
-    // first, so its scattered stores overlap the lookup's gathers
-    const uint32_t n_clear = L.first[3][nviews];
-    for (uint32_t it = blockIdx.x; it < n_clear + L.first[4][nviews]; it += G) {
-        uint32_t v, local;
-        if (it < n_clear) {
-            item_of(L, 3, nviews, it, v, local);
-            const Tab t = to_tab(views[v].prev);
-            const uint32_t j = local * B + threadIdx.x;
+// The last phase, a launch of its own: the previous tables emptied (read for the
+// last time by the blend), then every vertex looked up; the clear's items come
+// first, so its scattered stores overlap the lookup's gathers.  A plain gather,
+// bound by the lines in flight, that wants all the waves a compute unit holds: as
+// the last phase of views_kernel, whose registers are the insert's, it had half
+// of them (eight views of 59.5M vertices 750 -> 488 us; 540 when all phases shared
+// 64 registers).  The launch's start takes the place of a grid barrier: whole
+// calls of 640x360, 800x600, 401x229 and 256x256 x3 at 1024 lanes 327 -> 313 us, at
+// 256 404 -> 365, of 200x90 and 150x150 x2 130 -> 113.  Two vertices a lane: 1 or 4
+// are within 2%.
+constexpr int kLookT = 256, kLook = 2;  // threads; vertices a lane has in flight
+constexpr uint32_t kLookGroups = 8;     // workgroups a compute unit
+__global__ __launch_bounds__(kLookT) __attribute__((amdgpu_waves_per_eu(8))) void views_lookup_kernel(
+    const pf_view *__restrict__ views, uint32_t nviews, Barrier bar) {
+    if (bar.status[0]) return;  // a phase before gave up waiting
+    // lane v of every wavefront: where view v's items end among those of its kind
+    static_assert(PF_MAX_VIEWS <= 64, "a lane a view");
+    constexpr uint32_t kItem = kLookT * kLook;
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t end_clear = 0, end_look = 0;
+    if (lane < nviews) {
+        const pf_view &d = views[lane];
+        end_clear = d.prev.cell ? (((1u << d.cur.log2_slots) + 31) / 32 + kLookT - 1) / kLookT : 0u;
+        end_look = (d.n + kItem - 1) / kItem;
+    }
+    const uint32_t own_clear = end_clear, own_look = end_look;
+#pragma unroll
+    for (uint32_t off = 1; off < 64; off <<= 1) {
+        const uint32_t c = (uint32_t)__shfl_up((int)end_clear, off), l = (uint32_t)__shfl_up((int)end_look, off);
+        if (lane >= off) {
+            end_clear += c;
+            end_look += l;
+        }
+    }
+    const uint32_t n_clear = (uint32_t)__shfl((int)end_clear, 63), n_look = (uint32_t)__shfl((int)end_look, 63);
+    for (uint32_t it = blockIdx.x; it < n_clear + n_look; it += gridDim.x) {
+        const bool clears = it < n_clear;
+        const uint32_t k = clears ? it : it - n_clear;
+        const int v = __builtin_ctzll(__ballot((clears ? end_clear : end_look) > k));
+        const uint32_t local =
+            k - (uint32_t)(clears ? __shfl((int)(end_clear - own_clear), v) : __shfl((int)(end_look - own_look), v));
+        const pf_view &d = views[__builtin_amdgcn_readfirstlane(v)];
+        if (clears) {
+            const Tab t = to_tab(d.prev);
+            const uint32_t j = local * kLookT + threadIdx.x;
             if (j < t.nwords()) clear_word(t, j);
             continue;
         }
-        item_of(L, 4, nviews, it - n_clear, v, local);
-        const pf_view &d = views[v];
         const Tab t = to_tab(d.cur);
-        // eight vertices at a time: their slots (kNoSlot for flagged vertices),
-        // then every value they read, then the stores, so the loads of the
-        // eight are in flight together
-        for (int k0 = 0; k0 < kIters; k0 += kLook) {
-            uint32_t slot[kLook];
-            float4 val[kLook];
+        // the slots of a lane's vertices (kNoSlot for flagged ones), then every
+        // value they read, then the stores
+        uint32_t slot[kLook];
+        float4 val[kLook];
+        const uint32_t i0 = local * kItem + threadIdx.x;
 #pragma unroll
-            for (int u = 0; u < kLook; ++u) {
-                const uint32_t i = local * kItem + (k0 + u) * B + threadIdx.x;
-                slot[u] = i < d.n ? d.slot[i] : kNoSlot;
-            }
+        for (int u = 0; u < kLook; ++u) slot[u] = i0 + u * kLookT < d.n ? d.slot[i0 + u * kLookT] : kNoSlot;
 #pragma unroll
-            for (int u = 0; u < kLook; ++u) {
-                const uint32_t i = local * kItem + (k0 + u) * B + threadIdx.x;
-                if (i >= d.n) continue;
-                val[u] = lookup_value(t, slot[u], i, d.r, d.g, d.b, d.temporal != 0);
-            }
+        for (int u = 0; u < kLook; ++u)
+            if (i0 + u * kLookT < d.n)
+                val[u] = lookup_value(t, slot[u], i0 + u * kLookT, d.r, d.g, d.b, d.temporal != 0);
 #pragma unroll
-            for (int u = 0; u < kLook; ++u) {
-                const uint32_t i = local * kItem + (k0 + u) * B + threadIdx.x;
-                if (i >= d.n) continue;
-                d.r_out[i] = val[u].x;
-                d.g_out[i] = val[u].y;
-                d.b_out[i] = val[u].z;
-                if (d.count_out) d.count_out[i] = slot[u] == kNoSlot ? 0u : (uint32_t)val[u].w;
-            }
+        for (int u = 0; u < kLook; ++u) {
+            const uint32_t i = i0 + u * kLookT;
+            if (i >= d.n) continue;
+            d.r_out[i] = val[u].x;
+            d.g_out[i] = val[u].y;
+            d.b_out[i] = val[u].z;
+            if (d.count_out) d.count_out[i] = slot[u] == kNoSlot ? 0u : (uint32_t)val[u].w;
         }
     }
-    // the lookup has no barrier after it: block 0 stamps its own end
-    stamp(4);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // its own end
+        const uint64_t w = wall_clock64();
+        bar.status[12] = (uint32_t)w;
+        bar.status[13] = (uint32_t)(w >> 32);
+    }
 }
 
 __global__ void views_reset_kernel(uint32_t *ws, uint32_t words) {
@@ -535,8 +563,11 @@ hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_
     const uint32_t per = (per_cu == 0 || per_cu > (uint32_t)resident) ? (uint32_t)resident : per_cu;
     uint32_t grid = per * (uint32_t)cus;
     void *args[] = {(void *)&views, (void *)&nviews, (void *)&agg, (void *)&bar};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B>), dim3(grid), dim3(B), args, 0,
-                                      st);
+    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B>), dim3(grid), dim3(B),
+                                                    args, 0, st);
+    if (e != hipSuccess) return e;
+    views_lookup_kernel<<<(uint32_t)cus * kLookGroups, kLookT, 0, st>>>(views, nviews, bar);
+    return hipGetLastError();
 }
 
 }  // namespace views
