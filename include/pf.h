@@ -654,7 +654,7 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  *              count and sums with one set of device atomics per vertex;
  *              otherwise a workgroup takes agg_width consecutive vertices at
  *              a time (fewer where the views have few) and merges the valid
- *              ones by key in an LDS table of min(agg_width, 4 x block, 1536)
+ *              ones by key in an LDS table of min(agg_width, 3.75 x block, 1536)
  *              entries, in as many windows as the table needs (a vertex that
  *              finds no room goes alone); each group claims its cell once and
  *              adds count and sums with one set of device atomics;

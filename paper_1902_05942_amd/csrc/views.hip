@@ -52,7 +52,9 @@ __device__ __forceinline__ Tab to_tab(const pf_table &t) {
 // left most workgroups without any: insert phase of 640x360, 800x600, 401x229
 // and 256x256 x3 267 -> 197 us, of 200x90 and 150x150 x2 180 -> 56 us.)
 template <int B>
-constexpr uint32_t kMergeCap = 4 * B < 1536 ? 4 * B : 1536;
+constexpr uint32_t kMergeCap = 15 * B / 4 < 1536 ? 15 * B / 4 : 1536;
+template <int B>
+constexpr uint32_t kGroups = B == 64 ? 13 : B == 128 ? 8 : B == 256 ? 4 : 2;  // workgroups a compute unit's LDS holds
 template <int B>
 constexpr uint32_t kEntries = (kMergeCap<B> + B - 1) / B;  // merge-table entries per lane
 template <int B>
@@ -70,6 +72,12 @@ struct Lds {
     uint32_t first[3][PF_MAX_VIEWS + 1];  // per item kind: first global item of each view
     uint32_t hits, nlist, per_item, per_range;
 };
+
+// LDS is allotted in pieces of 1280 bytes; the launch rounds up to 2 KB as well
+template <int B>
+constexpr bool kFits = (sizeof(Lds<B>) + 16 + 2047) / 2048 * 2048 * kGroups<B> <= 160 << 10 &&
+                       (sizeof(Lds<B>) + 16 + 1279) / 1280 * 1280 * kGroups<B> <= 160 << 10;
+static_assert(kFits<64> && kFits<128> && kFits<256> && kFits<512> && kFits<1024>, "workgroups lost to LDS");
 
 template <int B>
 __device__ __forceinline__ void item_of(const Lds<B> &L, int phase, uint32_t nviews, uint32_t it, uint32_t &v,

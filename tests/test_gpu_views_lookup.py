@@ -1,6 +1,6 @@
 """The lookup after the persistent multi-view launch: every lane of a wavefront
 holds one view's items, so the most views a call takes, of sizes around its items
-of 512 vertices and 8192 slots."""
+of 512 vertices and 8192 slots; and the launch's resident workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -40,3 +40,18 @@ def test_many_views_equal_single_calls(gpu, nviews, temporal):
                 assert not mv.tables[v][0].occupancy().any().item()
     phases = mv.phase_us()
     assert all(0 <= x < 1e6 for x in phases), phases
+
+
+@pytest.mark.parametrize("block,groups", [(64, 13), (128, 8), (256, 4), (512, 2)])
+def test_resident_workgroups(gpu, block, groups):
+    """LDS bounds the persistent launch: 160 KB hold this many workgroups of each
+    size (16 waves a compute unit from 128 lanes on)."""
+    n = 3000
+    mv = pf.MultiViewFilter([(n, 13)], mode="persistent")
+    f = {c: torch.rand(n, device="cuda") for c in ("px", "py", "pz", "r", "g", "b")}
+    f.update(nx=torch.zeros(n, device="cuda"), ny=torch.zeros(n, device="cuda"), nz=torch.ones(n, device="cuda"),
+             cam=(0.0, 0.0, 2.0), s=0.01, seed=1, valid=torch.ones(n, dtype=torch.uint8, device="cuda"))
+    mv.filter([f], block=block)
+    assert mv.status() == 0
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert mv.status_words()[1] == groups * cus
