@@ -654,10 +654,11 @@ pf_status pf_filter_views_concurrent(const pf_view *views, uint32_t nviews, uint
  *              count and sums with one set of device atomics per vertex;
  *              otherwise a workgroup takes agg_width consecutive vertices at
  *              a time (fewer where the views have few) and merges the valid
- *              ones by key in an LDS table of min(agg_width, 3.75 x block, 1536)
- *              entries, in as many windows as the table needs (a vertex that
- *              finds no room goes alone); each group claims its cell once and
- *              adds count and sums with one set of device atomics;
+ *              ones by key in an LDS table of min(3.375 x block, 1536) entries (a
+ *              vertex that finds no room goes alone); each entry claims its
+ *              cell once and adds count and sums with one set of device
+ *              atomics when the table is full or the workgroup goes on to
+ *              another view;
  *   temporal   when temporal is set, the temporal values of the occupied cells
  *              (as pf_temporal_update, mode 0, Section 3.4.1);
  *   lookup     every vertex (as pf_query_average with the slots), and,

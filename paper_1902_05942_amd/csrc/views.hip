@@ -43,16 +43,21 @@ __device__ __forceinline__ Tab to_tab(const pf_table &t) {
 }
 
 // LDS merge table of the insert phase: the valid ones of agg_width consecutive
-// vertices (block .. kIters * block) merge in windows into at most
-// min(agg_width, 4 * block, 1536) entries (the table stays in static LDS and
-// small workgroups keep their residency); a window ends when the next step's
-// vertices might not find room (more than seven eighths in use).  (With one
-// window per agg_width vertices, small images overflowed the table and sent
-// their vertices to the cells one by one, and a workgroup's 8 x block vertices
-// left most workgroups without any: insert phase of 640x360, 800x600, 401x229
-// and 256x256 x3 267 -> 197 us, of 200x90 and 150x150 x2 180 -> 56 us.)
+// vertices (block .. kIters * block) merge into at most min(3.375 * block, 1536)
+// entries (with the list of valid vertices, kGroups<block> workgroups of them fill
+// a compute unit's LDS; at 4 * block entries and without slots one less did, 12
+// waves instead of 16 at 256 lanes).  An entry claims its cell when its window
+// ends and keeps its sums while the workgroup's next items are of the same view,
+// until another step might not find room (more than seven eighths in use): where
+// voxels are coarse a workgroup goes to a cell once, not once an item (views of
+// 1920x1080 and 1280x720 x3 at cell size 10, 256/256 and 1024/4096: 2500 and 536 ->
+// 564 and 347 us; at 0.01 667 and 553 -> 686 and 553).  (With one window per
+// agg_width vertices, small images overflowed the table and sent their vertices to
+// the cells one by one, and a workgroup's 8 x block vertices left most workgroups
+// without any: insert phase of 640x360, 800x600, 401x229 and 256x256 x3 267 -> 197
+// us, of 200x90 and 150x150 x2 180 -> 56 us.)
 template <int B>
-constexpr uint32_t kMergeCap = 15 * B / 4 < 1536 ? 15 * B / 4 : 1536;
+constexpr uint32_t kMergeCap = 27 * B / 8 < 1536 ? 27 * B / 8 : 1536;
 template <int B>
 constexpr uint32_t kGroups = B == 64 ? 13 : B == 128 ? 8 : B == 256 ? 4 : 2;  // workgroups a compute unit's LDS holds
 template <int B>
@@ -63,7 +68,7 @@ struct Lds {
         struct {
             unsigned long long key[kMergeCap<B>];
             unsigned long long s0[kMergeCap<B>], s1[kMergeCap<B>], s2[kMergeCap<B>];
-            uint32_t cnt[kMergeCap<B>];  // count, then the group's slot
+            uint32_t cnt[kMergeCap<B>], slot[kMergeCap<B>];
             uint16_t list[kIters * B];   // the item's valid vertices
             uint32_t nlive, created[kIters];  // valid vertices; entries created by each step
         } m;
@@ -90,6 +95,7 @@ __device__ __forceinline__ void item_of(const Lds<B> &L, int phase, uint32_t nvi
 // What a lane keeps of a vertex until its window ends (16 bits): its LDS entry,
 // kAlone, or kFlagged and its flags.
 constexpr uint32_t kAlone = 0xffffu, kFlagged = 0x8000u;
+constexpr uint32_t kUnclaimed = 0xfffffffeu;  // slot of an entry whose cell has not been claimed
 
 // Key, flags and fixed-point contribution of vertex i of a view (masked
 // vertices read nothing more than their valid byte).
@@ -195,11 +201,40 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
     // ---- phase 1: keys and insertion.  agg == 0: one claim and one set of
     // device atomics per vertex.  Otherwise an item is agg consecutive vertices
     // (a power of two, block <= agg <= kIters * block; fewer for small views,
-    // down to block): its valid ones are
-    // listed, merged by key in LDS in windows that end before the table is
-    // full, then every group claims its cell once and adds to it.
-    const uint32_t kCap = agg < kMergeCap<B> ? agg : kMergeCap<B>, limit = kCap / 8 * 7;
+    // down to block): its valid ones are listed and merged by key in LDS in
+    // windows that end before the table is full; a window's new entries claim
+    // their cells, a full table's go to them.
+    constexpr uint32_t kCap = kMergeCap<B>, limit = kCap / 8 * 7;
     const uint32_t per_item = L.per_item, per = per_item / B;  // vertices per lane and item (1, 2, 4 or 8)
+    const uint32_t tid = threadIdx.x;
+    uint32_t used = 0, table_of = 0;  // entries in use, and the view they are of
+    auto empty_entry = [&](uint32_t j) {
+        L.m.key[j] = kEmpty;
+        L.m.s0[j] = 0;
+        L.m.s1[j] = 0;
+        L.m.s2[j] = 0;
+        L.m.cnt[j] = 0;
+    };
+    if (agg)
+        for (uint32_t j = tid; j < kCap; j += B) empty_entry(j);
+    // an entry's sums to its cell; every lane of a wavefront calls
+    auto add_entry = [&](const Tab &t, uint32_t j, uint32_t jl, bool has, uint32_t slot) {
+        const uint32_t c = L.m.cnt[jl];
+        accumulate_wave(t, slot, c, (int64_t)L.m.s0[jl], (int64_t)L.m.s1[jl], (int64_t)L.m.s2[jl]);
+        if (!has) return;
+        if (slot == kNoSlot) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], (unsigned long long)c);
+        empty_entry(j);
+    };
+    // all entries (their cells are claimed)
+    auto flush = [&](const Tab &t) {
+#pragma unroll
+        for (uint32_t e = 0; e < kEntries<B>; ++e) {
+            const uint32_t j = e * B + tid, jl = min(j, kCap - 1);
+            const bool has = j < kCap && L.m.key[jl] != kEmpty;
+            add_entry(t, j, jl, has, has ? L.m.slot[jl] : kNoSlot);
+        }
+        used = 0;
+    };
     for (uint32_t it = blockIdx.x; it < L.first[1][nviews]; it += G) {
         uint32_t v, local;
         item_of(L, 1, nviews, it, v, local);
@@ -231,28 +266,21 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
             continue;
         }
         const uint32_t c0 = local * per_item, i1 = min(d.n, c0 + per_item);
-        for (uint32_t j = threadIdx.x; j < kCap; j += B) {
-            L.m.key[j] = kEmpty;
-            L.m.s0[j] = 0;
-            L.m.s1[j] = 0;
-            L.m.s2[j] = 0;
-            L.m.cnt[j] = 0;
-        }
-        if (threadIdx.x < kIters) L.m.created[threadIdx.x] = 0;
-        if (threadIdx.x == 0) L.m.nlive = 0;
+        if (tid < kIters) L.m.created[tid] = 0;
+        if (tid == 0) L.m.nlive = 0;
         // the valid bytes first; masked vertices read nothing more
         uint32_t live = 0;
         for (uint32_t u = 0; u < per; ++u) {
-            const uint32_t i = c0 + u * B + threadIdx.x;
+            const uint32_t i = c0 + u * B + tid;
             live |= (i < i1 && (d.valid == nullptr || d.valid[i] != 0) ? 1u : 0u) << u;
         }
         __syncthreads();
         for (uint32_t u = 0; u < per; ++u) {
-            const uint32_t i = c0 + u * B + threadIdx.x;
+            const uint32_t i = c0 + u * B + tid;
             const bool v = (live >> u) & 1u;
             const uint32_t at = wave_reserve(&L.m.nlive, v);
             if (v) {
-                L.m.list[at] = (uint16_t)(u * B + threadIdx.x);
+                L.m.list[at] = (uint16_t)(u * B + tid);
             } else if (i < i1) {
                 d.vflags[i] = PF_V_INVALID;
                 if (d.key) d.key[i] = 0;
@@ -261,13 +289,18 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
         }
         __syncthreads();
         const uint32_t nlive = L.m.nlive, nsteps = (nlive + B - 1) / B;
+        if (used && nsteps && v != table_of) {
+            flush(to_tab(views[table_of].cur));
+            __syncthreads();
+        }
+        if (nsteps) table_of = v;
         for (uint32_t w0 = 0, w1; w0 < nsteps; w0 = w1) {
             // a lane keeps 16 bits of a vertex until its window ends: its LDS
             // entry, kAlone (no room), or kFlagged and its flags
             uint64_t code[2] = {0, 0};
             uint32_t u = w0;
             while (true) {
-                const uint32_t l = u * B + threadIdx.x;
+                const uint32_t l = u * B + tid;
                 uint32_t c = kFlagged;
                 bool fresh = false;
                 if (l < nlive) {
@@ -279,6 +312,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                     if (c == 0) {
                         const int e = lds_insert(L.m.key, kCap, k, fresh);
                         if (e >= 0) {
+                            if (fresh) L.m.slot[e] = kUnclaimed;
                             atomicAdd(&L.m.cnt[e], 1u);
                             lds_add(&L.m.s0[e], q0);
                             lds_add(&L.m.s1[e], q1);
@@ -292,7 +326,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                     }
                 }
                 const uint64_t m = __ballot(fresh);
-                if ((threadIdx.x & 63) == 0 && m) atomicAdd(&L.m.created[u], (uint32_t)__popcll(m));
+                if ((tid & 63) == 0 && m) atomicAdd(&L.m.created[u], (uint32_t)__popcll(m));
                 const uint64_t cb = (uint64_t)c << (16 * ((u - w0) & 3));
                 if (u - w0 < 4)
                     code[0] |= cb;
@@ -301,26 +335,29 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                 ++u;
                 if (u == nsteps) break;
                 const uint32_t next = min(nlive - u * B, (uint32_t)B);
-                if ((u - w0) * B + next <= limit) continue;
+                if (used + (u - w0) * B + next <= limit) continue;
                 __syncthreads();
-                uint32_t used = 0;
-                for (uint32_t x = w0; x < u; ++x) used += L.m.created[x];
-                if (used + next > limit) break;
+                uint32_t now = used;
+                for (uint32_t x = w0; x < u; ++x) now += L.m.created[x];
+                if (now + next > limit) break;
             }
             w1 = u;
             __syncthreads();
-            // one claim per group; a lane's entries issue their home-slot
+            for (uint32_t x = w0; x < w1; ++x) used += L.m.created[x];
+            const bool full = w1 < nsteps || used + B > limit;  // no room for another step
+            // one claim per new entry; a lane's entries issue their home-slot
             // loads, then their compare-and-swaps on empty home slots, before
             // any result is used
             uint64_t gk[kEntries<B>];
-            uint32_t fs[kEntries<B>], ff[kEntries<B>], fc[kEntries<B>];
+            uint32_t sl[kEntries<B>], fs[kEntries<B>], ff[kEntries<B>], fc[kEntries<B>];
             bool won[kEntries<B>];
 #pragma unroll
             for (uint32_t e = 0; e < kEntries<B>; ++e) {
-                const uint32_t j = e * B + threadIdx.x;
-                gk[e] = j < kCap ? L.m.key[j] : kEmpty;
+                const uint32_t j = e * B + tid, jl = min(j, kCap - 1);
+                gk[e] = j < kCap ? L.m.key[jl] : kEmpty;
+                sl[e] = gk[e] != kEmpty ? L.m.slot[jl] : kNoSlot;
                 fs[e] = ff[e] = fc[e] = 0;
-                if (gk[e] != kEmpty) {
+                if (sl[e] == kUnclaimed) {
                     fs[e] = home_of(gk[e], t.mask);
                     ff[e] = fingerprint_of(gk[e]);
                     fc[e] = load_fp_probe(&t.cell_at(fs[e]).fp);
@@ -329,7 +366,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
 #pragma unroll
             for (uint32_t e = 0; e < kEntries<B>; ++e) {
                 won[e] = false;
-                if (gk[e] != kEmpty && fc[e] == 0) {
+                if (sl[e] == kUnclaimed && fc[e] == 0) {
                     uint32_t expected = 0;
                     won[e] = __hip_atomic_compare_exchange_strong(&t.cell_at(fs[e]).fp, &expected, ff[e],
                                                                   __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -338,35 +375,28 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                 }
             }
 #pragma unroll
-            for (uint32_t e = 0; e < kEntries<B>; ++e) {  // uniform: accumulate_wave is the wavefront's
-                const uint32_t j = e * B + threadIdx.x, jl = min(j, kCap - 1);
-                uint32_t sl = kNoSlot;
-                if (gk[e] != kEmpty) {
+            for (uint32_t e = 0; e < kEntries<B>; ++e) {
+                const uint32_t j = e * B + tid, jl = min(j, kCap - 1);
+                if (sl[e] == kUnclaimed) {
                     if (won[e]) claimed<true>(t, fs[e], gk[e]);
                     // the home slot holds another key: probe on from the next
-                    sl = fc[e] == ff[e] ? fs[e] : claim_from<true>(t, gk[e], ff[e], (fs[e] + 1) & t.mask, 1);
+                    sl[e] = fc[e] == ff[e] ? fs[e] : claim_from<true>(t, gk[e], ff[e], (fs[e] + 1) & t.mask, 1);
+                    L.m.slot[j] = sl[e];
                 }
-                const uint32_t c = L.m.cnt[jl];
-                accumulate_wave(t, sl, c, (int64_t)L.m.s0[jl], (int64_t)L.m.s1[jl], (int64_t)L.m.s2[jl]);
-                if (gk[e] == kEmpty) continue;
-                if (sl == kNoSlot) add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], (unsigned long long)c);
-                L.m.cnt[j] = sl;
-                L.m.key[j] = kEmpty;  // emptied for the next window
-                L.m.s0[j] = 0;
-                L.m.s1[j] = 0;
-                L.m.s2[j] = 0;
+                if (full) add_entry(t, j, jl, gk[e] != kEmpty, sl[e]);  // uniform
             }
+            if (full) used = 0;
             __syncthreads();
 #pragma unroll 1
             for (uint32_t x = w0; x < w1; ++x) {
-                const uint32_t l = x * B + threadIdx.x;
+                const uint32_t l = x * B + tid;
                 if (l >= nlive) break;
                 const uint32_t i = c0 + L.m.list[l], at = x - w0;
                 const uint32_t c = (uint32_t)((at < 4 ? code[0] : code[1]) >> (16 * (at & 3))) & 0xffffu;
                 uint32_t slot = kNoSlot;
                 uint8_t fl = 0;
                 if (c < kFlagged) {
-                    slot = L.m.cnt[c];
+                    slot = L.m.slot[c];
                     if (slot == kNoSlot) fl = PF_V_OVERFLOW;
                 } else if (c == kAlone) {  // no room in the LDS table: on its own
                     uint64_t k;
@@ -385,12 +415,10 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd
                 d.vflags[i] = fl;
                 d.slot[i] = slot;
             }
-            __syncthreads();  // the slots are handed out: counts start from 0 again
-            for (uint32_t j = threadIdx.x; j < kCap; j += B) L.m.cnt[j] = 0;
-            __syncthreads();
+            __syncthreads();  // the slots are read: the next window's follow
         }
-        __syncthreads();  // the LDS is set up for the next item
     }
+    if (used) flush(to_tab(views[table_of].cur));
     if (!grid_barrier(bar, 2)) return;
     stamp(2);
 
