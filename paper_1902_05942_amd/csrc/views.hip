@@ -127,16 +127,19 @@ __device__ __forceinline__ void clear_word(const Tab &t, uint32_t j) {
     }
 }
 
-// At least kWavesPerSimd waves of this kernel fit a SIMD (the compiler
-// keeps the registers within that), which bounds the resident workgroups
-// from below independently of the occupancy query.  (With 8, so that two
-// workgroups of 1024 lanes share a compute unit, their 64 registers a lane
-// spilled 58: phases of 640x360, 800x600, 401x229 and 256x256 x3 11 + 190 + 63
-// + 12 us against 7 + 167 + 45 + 22.)
-constexpr int kWavesPerSimd = 4;
+// At least kWaves waves of this kernel fit a SIMD (the compiler keeps the
+// registers within that), which bounds the resident workgroups from below
+// independently of the occupancy query.  8, so that two workgroups of 1024 lanes
+// share a compute unit and one's barriers hide behind the other, costs 17 spilled
+// registers; it pays once the views give every workgroup many items (kMany
+// vertices in all): 1024 lanes, widths 1024 / 4096, 4 -> 8 waves: eight views of
+// 59.5M vertices 3326 / 2681 -> 3218 / 2482 us, 24.9M 1288 / 1066 -> 1285 / 1006, 18.7M
+// 1095 / 917 -> 1106 / 880, 11.1M 671 / 567 -> 689 / 562, 9M 608 / 555 -> 633 / 565, 2.6M
+// 325 / 308 -> 343 / 344.  (Smaller workgroups are bound by their LDS.)
+constexpr uint64_t kMany = 1ull << 24;
 
-template <int B>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd))) void views_kernel(
+template <int B, int kWaves>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kWaves))) void views_kernel(
     const pf_view *__restrict__ views, uint32_t nviews, uint32_t agg, Barrier bar) {
     __shared__ Lds<B> L;
     constexpr uint32_t kItem = (uint32_t)B * kIters;
@@ -552,7 +555,7 @@ __global__ void views_reset_kernel(uint32_t *ws, uint32_t words) {
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 static size_t descriptors_at() { return align256(sizeof(uint32_t) * kCounterStride * (2 * kSubCounters + 2)); }
 
-template <int B>
+template <int B, int kWaves = 4>
 hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_t per_cu, uint32_t *ws,
                     hipStream_t st) {
     static int resident = 0;  // workgroups per CU for this block size (queried once)
@@ -563,7 +566,7 @@ hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_
         if (e != hipSuccess) return e;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, reinterpret_cast<const void *>(views_kernel<B>), B,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, reinterpret_cast<const void *>(views_kernel<B, kWaves>), B,
                                                          0);
         if (e != hipSuccess) return e;
         // every workgroup of a cooperative grid must be resident at once: the
@@ -575,14 +578,14 @@ hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_
         e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
         if (e != hipSuccess) return e;
         hipFuncAttributes fa;
-        e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(views_kernel<B>));
+        e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(views_kernel<B, kWaves>));
         if (e != hipSuccess) return e;
         const size_t per_wg = std::max((fa.sharedSizeBytes + 2047) / 2048 * 2048,
                                        (fa.sharedSizeBytes + 1279) / 1280 * 1280);
         if (per_wg > 0 && lds_cu > 0 && (size_t)resident * per_wg > (size_t)lds_cu)
             resident = (int)((size_t)lds_cu / per_wg);
         // and the register-bound count the compiler guarantees (4 SIMDs)
-        const int by_waves = 4 * kWavesPerSimd * 64 / B > 0 ? 4 * kWavesPerSimd * 64 / B : 1;
+        constexpr int by_waves = 4 * kWaves * 64 / B;
         if (resident > by_waves) resident = by_waves;
         if (resident < 1) return hipErrorInvalidConfiguration;
     }
@@ -599,7 +602,7 @@ hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_
     const uint32_t per = (per_cu == 0 || per_cu > (uint32_t)resident) ? (uint32_t)resident : per_cu;
     uint32_t grid = per * (uint32_t)cus;
     void *args[] = {(void *)&views, (void *)&nviews, (void *)&agg, (void *)&bar};
-    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B>), dim3(grid), dim3(B),
+    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B, kWaves>), dim3(grid), dim3(B),
                                                     args, 0, st);
     if (e != hipSuccess) return e;
     views_lookup_kernel<<<(uint32_t)cus * kLookGroups, kLookT, 0, st>>>(views, nviews, bar);
@@ -618,12 +621,16 @@ hipError_t launch_views(const pf_view *host_views, uint32_t nviews, uint32_t blo
     hipError_t e = hipMemcpyAsync(dev, host_views, nviews * sizeof(pf_view), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     uint32_t *ws = reinterpret_cast<uint32_t *>(workspace);
+    uint64_t total = 0;
+    for (uint32_t v = 0; v < nviews; ++v) total += host_views[v].n;
     switch (block) {
         case 64: return views::launch_b<64>(dev, nviews, agg, per_cu, ws, st);
         case 128: return views::launch_b<128>(dev, nviews, agg, per_cu, ws, st);
         case 256: return views::launch_b<256>(dev, nviews, agg, per_cu, ws, st);
         case 512: return views::launch_b<512>(dev, nviews, agg, per_cu, ws, st);
-        case 1024: return views::launch_b<1024>(dev, nviews, agg, per_cu, ws, st);
+        case 1024:
+            return total >= views::kMany ? views::launch_b<1024, 8>(dev, nviews, agg, per_cu, ws, st)
+                                         : views::launch_b<1024>(dev, nviews, agg, per_cu, ws, st);
         default: return hipErrorInvalidConfiguration;
     }
 }

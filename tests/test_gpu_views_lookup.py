@@ -44,12 +44,13 @@ def test_many_views_equal_single_calls(gpu, nviews, temporal):
     assert all(0 <= x < 1e6 for x in phases), phases
 
 
-@pytest.mark.parametrize("block,groups", [(64, 13), (128, 8), (256, 4), (512, 2)])
-def test_resident_workgroups(gpu, block, groups):
+@pytest.mark.parametrize("block,groups,n", [(64, 13, 3000), (128, 8, 3000), (256, 4, 3000), (512, 2, 3000),
+                                            (1024, 1, (1 << 24) - 1), (1024, 2, 1 << 24)])
+def test_resident_workgroups(gpu, block, groups, n):
     """LDS bounds the persistent launch: 160 KB hold this many workgroups of each
-    size (16 waves a compute unit from 128 lanes on)."""
-    n = 3000
-    mv = pf.MultiViewFilter([(n, 13)], mode="persistent")
+    size (16 waves a compute unit from 128 lanes on); of 1024 lanes two share a
+    compute unit from 2^24 vertices on."""
+    mv = pf.MultiViewFilter([(n, 13)], mode="persistent", keys=False)
     f = {c: torch.rand(n, device="cuda") for c in ("px", "py", "pz", "r", "g", "b")}
     f.update(nx=torch.zeros(n, device="cuda"), ny=torch.zeros(n, device="cuda"), nz=torch.ones(n, device="cuda"),
              cam=(0.0, 0.0, 2.0), s=0.01, seed=1, valid=torch.ones(n, dtype=torch.uint8, device="cuda"))
