@@ -39,6 +39,7 @@
 
 #include "pf_kernels.h"
 #include "pf_merge.h"
+#include "pf_once.h"
 #include "pf_ops.h"
 
 namespace pfk {
@@ -898,14 +899,6 @@ size_t binned_workspace_bytes(uint32_t n, uint32_t log2_slots) {
 
 namespace binned {
 
-// the reduce kernels of every blend variant, for their LDS attribute
-static const void *const kReduceKernels[] = {
-    reinterpret_cast<const void *>(reduce_kernel<false, false, false>),
-    reinterpret_cast<const void *>(reduce_kernel<true, false, false>),
-    reinterpret_cast<const void *>(reduce_kernel<true, true, false>),
-    reinterpret_cast<const void *>(reduce_kernel<true, false, true>),
-    reinterpret_cast<const void *>(reduce_kernel<true, true, true>)};
-
 // blend: NULL for the insert alone; else the temporal blend in reduce
 // (has_prev: blend->prev is a table; integrate: temporal integration).
 template <bool kKeys>
@@ -940,22 +933,16 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
     bk.nbins = p.nbins;
     bk.parts = p.parts;
     bk.part_cap = p.part_cap;
-    static bool attrs = false;  // dynamic LDS above 64 KB needs the attribute, set once per function
-    if (!attrs) {
-        constexpr int kAggregateLds = (int)aggregate_lds(kMaxSteps * kT, kMaxBins);
-        constexpr int kReduceLds = kCells * 32 + (8 << (kMaxLog2BinSlots - 5));
-        static_assert(kAggregateLds <= 80 * 1024, "two workgroups of aggregate share a CU");
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kBuckets>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<true, kBuckets>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kAggregateLds);
-        for (const void *f : kReduceKernels)
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kReduceLds);
-        if (e != hipSuccess) return e;
-        attrs = true;
-    }
+    constexpr size_t kAggregateLds = aggregate_lds(kMaxSteps * kT, kMaxBins);
+    constexpr size_t kReduceLds = kCells * 32 + (8 << (kMaxLog2BinSlots - 5));
+    static_assert(kAggregateLds <= 80 * 1024, "two workgroups of aggregate share a CU");
+    static LargeLds aggregate, reduce;
+    hipError_t e = aggregate.allow(kAggregateLds, aggregate_kernel<kKeys, kBuckets>);
+    if (e == hipSuccess)
+        e = reduce.allow(kReduceLds, reduce_kernel<false, false, false>, reduce_kernel<true, false, false>,
+                         reduce_kernel<true, true, false>, reduce_kernel<true, false, true>,
+                         reduce_kernel<true, true, true>);
+    if (e != hipSuccess) return e;
     zero_kernel<<<1, kT, 0, st>>>(ticket, p.nzero);
     aggregate_kernel<kKeys, kBuckets><<<p.groups, kT, p.lds_aggregate, st>>>(t, key, r, g, b, flags, slot_out, n,
                                                                              p.chunk, bk, ticket, fk);
@@ -981,17 +968,10 @@ bool insert_by_windows(uint32_t n) { return n >= binned::kMinWindowed; }
 hipError_t launch_insert_windows(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                                  uint8_t *flags, uint32_t *slot_out, uint32_t n, hipStream_t st) {
     using namespace binned;
-    constexpr int kLds = (int)aggregate_lds(kMaxSteps * kT, 0);
-    static bool attrs = false;  // as in run()
-    if (!attrs) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kAtomics>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(aggregate_kernel<false, kFloatAtomics>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-        if (e != hipSuccess) return e;
-        attrs = true;
-    }
+    static LargeLds large;
+    const hipError_t e = large.allow(aggregate_lds(kMaxSteps * kT, 0), aggregate_kernel<false, kAtomics>,
+                                     aggregate_kernel<false, kFloatAtomics>);
+    if (e != hipSuccess) return e;
     uint32_t chunk, groups;
     deal_chunks(n, chunk, groups);
     const size_t lds = aggregate_lds(chunk, 0);

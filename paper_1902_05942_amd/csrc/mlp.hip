@@ -7,6 +7,7 @@
 //   C/D:       lane l holds D[4 (l / 16) + 0..3][l % 16].
 #include "pf_device.h"
 #include "pf_kernels.h"
+#include "pf_once.h"
 
 namespace pfk {
 
@@ -971,13 +972,9 @@ hipError_t launch_mlp_train(const MlpArgs &a, const Tab &t, const GeoArgs &g, co
     A.gscale = (float)(2.0 / (3.0 * (double)batch));
     const uint32_t nblocks = batch / mlp::kBS;
     const size_t lds = sizeof(mlp::TrainLds);
-    static bool lds_set = false;  // the attribute is per function: set it once
-    if (!lds_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mlp::train_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        lds_set = true;
-    }
+    static LargeLds large;
+    const hipError_t e = large.allow(lds, mlp::train_kernel);
+    if (e != hipSuccess) return e;
     mlp::train_kernel<<<nblocks, mlp::kThreads, lds, st>>>(A, a.wb, a.w, a.partial);
     const double c1 = 1.0 / (1.0 - pow(0.9, (double)step));
     const double c2 = 1.0 / (1.0 - pow(0.999, (double)step));
@@ -1015,19 +1012,15 @@ hipError_t launch_mlp_infer(const MlpArgs &a, const GeoArgs &g, const uint32_t *
     G.nz = g.nz;
     for (int c = 0; c < 3; ++c) G.cam[c] = g.cam[c];
     const size_t lds = sizeof(mlp::InferLds);
-    static bool lds_set = false;  // the attribute is per function: set it once
-    if (!lds_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mlp::infer_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        lds_set = true;
-    }
+    static LargeLds large;
+    hipError_t e = large.allow(lds, mlp::infer_kernel);
+    if (e != hipSuccess) return e;
     // no more workgroups than are resident at once: the waves stride over
     // the tiles, and a second round of workgroups would start only when the
     // first has finished (per device, asked once)
     static uint32_t resident[64] = {};
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (resident[dev] == 0) {

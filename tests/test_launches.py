@@ -24,3 +24,38 @@ def test_views_lookup_is_a_launch_of_its_own(tmp_path):
     names = [line.split()[2] for line in out if line]
     assert kinds == ["launch", "cooperative", "launch"]
     assert "views_kernel" in names[1] and "lookup" in names[2]
+
+
+def test_large_lds_is_allowed_on_every_device(tmp_path):
+    """More than 64 KB of dynamic LDS is an attribute of a kernel on a device: a
+    process that goes on to a second device sets it there too."""
+    out = record(tmp_path, """
+    t = table(22)
+    class pf_mlp(ctypes.Structure):
+        _fields_ = [(n, vp) for n in ("w", "m", "v", "wb", "partial", "loss")] + [("max_batch", u32), ("pad", u32)]
+    class pf_geometry(ctypes.Structure):
+        _fields_ = [(n, vp) for n in ("key", "px", "py", "pz", "nx", "ny", "nz")] + [("cam", f32 * 3), ("pad", u32)]
+    net, geo = pf_mlp(), pf_geometry(*p[:7])
+    assert L.pf_mlp_carve(vp(0x500000000000), u32(1024), ctypes.byref(net)) == 0
+    for device in (0, 1):
+        R.rec_set_device(device)
+        for _ in range(2):
+            assert L.pf_insert_accumulate(ctypes.byref(t), *p[:6], u64(1 << 21), u32(0), None) == 0
+            assert L.pf_insert_accumulate_binned(ctypes.byref(t), *p[:6], u64(1 << 21), p[6],
+                                                 ctypes.c_size_t(1 << 40), None) == 0
+            assert L.pf_mlp_train_step(ctypes.byref(net), ctypes.byref(t), ctypes.byref(geo), p[7], p[8], p[9],
+                                       u32(1024), u64(1), u32(1), f32(0.1), None) == 0
+            assert L.pf_mlp_infer(ctypes.byref(net), ctypes.byref(geo), p[7], p[8], u64(1000), *p[9:12], None) == 0
+    print(launches())
+    """)
+    rows = [line.split() for line in out.splitlines() if line]
+    large = {(row[1], row[2]) for row in rows if row[0] == "launch" and int(row[5]) > 64 << 10}
+    assert {device for device, _ in large} == {"0", "1"} and len(large) >= 8
+    for row in rows:
+        if row[0] == "attribute":
+            large.discard((row[1], row[2]))
+        elif row[0] == "launch":
+            assert (row[1], row[2]) not in large, f"{row[2]} on device {row[1]} before its attribute"
+    assert not large
+    attributes = [row for row in rows if row[0] == "attribute"]
+    assert len(attributes) == len({tuple(row) for row in attributes}), "set once"
