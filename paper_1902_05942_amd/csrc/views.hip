@@ -16,6 +16,7 @@
 #include "pf_grid.h"
 #include "pf_kernels.h"
 #include "pf_merge.h"
+#include "pf_once.h"
 #include "pf_ops.h"
 
 namespace pfk {
@@ -555,26 +556,30 @@ __global__ void views_reset_kernel(uint32_t *ws, uint32_t words) {
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 static size_t descriptors_at() { return align256(sizeof(uint32_t) * kCounterStride * (2 * kSubCounters + 2)); }
 
+// A device's compute units, the workgroups of a kernel that are resident on each
+// at once, and its wall clock's rate: asked for once per device.
+struct Shape {
+    uint32_t cus, resident;
+    uint64_t ticks_per_s;
+};
+
 template <int B, int kWaves = 4>
 hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_t per_cu, uint32_t *ws,
                     hipStream_t st) {
-    static int resident = 0;  // workgroups per CU for this block size (queried once)
-    static int cus = 0;
-    if (resident == 0) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+    static PerDevice<Shape> shapes;
+    Shape sh;
+    const hipError_t q = shapes.get(sh, [](int dev, Shape &out) {
+        int resident = 0, cus = 0, lds_cu = 0, khz = 0;
+        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, reinterpret_cast<const void *>(views_kernel<B, kWaves>), B,
-                                                         0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident,
+                                                         reinterpret_cast<const void *>(views_kernel<B, kWaves>), B, 0);
         if (e != hipSuccess) return e;
         // every workgroup of a cooperative grid must be resident at once: the
         // LDS-bound count is taken as well, with the static LDS rounded up to
         // 2 KB and to the hardware's 1280 bytes (a 128th of 160 KB), so that an
         // allocation granularity the occupancy query may not model cannot
         // leave a workgroup waiting for a slot
-        int lds_cu = 0;
         e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
         if (e != hipSuccess) return e;
         hipFuncAttributes fa;
@@ -588,24 +593,23 @@ hipError_t launch_b(const pf_view *views, uint32_t nviews, uint32_t agg, uint32_
         constexpr int by_waves = 4 * kWaves * 64 / B;
         if (resident > by_waves) resident = by_waves;
         if (resident < 1) return hipErrorInvalidConfiguration;
-    }
-    static uint64_t ticks_per_s = 0;
-    if (ticks_per_s == 0) {
-        int dev = 0, khz = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
+        e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
         if (e != hipSuccess) return e;
-        ticks_per_s = (uint64_t)(khz > 0 ? khz : 100000) * 1000ull;
-    }
-    const Barrier bar = grid::barrier_at(ws, 2 * ticks_per_s);  // a phase never takes seconds
+        out.resident = (uint32_t)resident;
+        out.cus = (uint32_t)cus;
+        out.ticks_per_s = (uint64_t)(khz > 0 ? khz : 100000) * 1000ull;
+        return hipSuccess;
+    });
+    if (q != hipSuccess) return q;
+    const Barrier bar = grid::barrier_at(ws, 2 * sh.ticks_per_s);  // a phase never takes seconds
     views_reset_kernel<<<1, 256, 0, st>>>(ws, grid::kWords);
-    const uint32_t per = (per_cu == 0 || per_cu > (uint32_t)resident) ? (uint32_t)resident : per_cu;
-    uint32_t grid = per * (uint32_t)cus;
+    const uint32_t per = (per_cu == 0 || per_cu > sh.resident) ? sh.resident : per_cu;
+    const uint32_t grid = per * sh.cus;
     void *args[] = {(void *)&views, (void *)&nviews, (void *)&agg, (void *)&bar};
-    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B, kWaves>), dim3(grid), dim3(B),
-                                                    args, 0, st);
+    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(views_kernel<B, kWaves>), dim3(grid),
+                                                    dim3(B), args, 0, st);
     if (e != hipSuccess) return e;
-    views_lookup_kernel<<<(uint32_t)cus * kLookGroups, kLookT, 0, st>>>(views, nviews, bar);
+    views_lookup_kernel<<<sh.cus * kLookGroups, kLookT, 0, st>>>(views, nviews, bar);
     return hipGetLastError();
 }
 

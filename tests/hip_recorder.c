@@ -4,17 +4,19 @@
  * definitions are found first; no kernel runs. */
 #define __HIP_PLATFORM_AMD__ 1
 #include <hip/hip_runtime_api.h>
+#include <pthread.h>
 #include <stdio.h>
 #include <string.h>
+#include <unistd.h>
 
 static int device;
 static char text[1 << 16];
 static size_t used;
 static struct { const void *fn; const char *name; } kernels[512];
 static int nkernels;
-static dim3 cfg_grid, cfg_block;
-static size_t cfg_lds;
-static hipStream_t cfg_stream;
+static __thread dim3 cfg_grid, cfg_block;
+static __thread size_t cfg_lds;
+static __thread hipStream_t cfg_stream;
 
 void rec_set_device(int d) { device = d; }
 void rec_clear(void) { used = 0; text[0] = 0; }
@@ -25,8 +27,11 @@ static const char *name_of(const void *fn) {
         if (kernels[k].fn == fn) return kernels[k].name;
     return "?";
 }
+static pthread_mutex_t lock = PTHREAD_MUTEX_INITIALIZER;
 static void note(const char *what, const void *fn, unsigned a, unsigned b, size_t c) {
+    pthread_mutex_lock(&lock);
     used += (size_t)snprintf(text + used, sizeof(text) - used, "%s %d %s %u %u %zu\n", what, device, name_of(fn), a, b, c);
+    pthread_mutex_unlock(&lock);
 }
 
 void **__hipRegisterFatBinary(const void *data) { static void *module; (void)data; return &module; }
@@ -64,7 +69,9 @@ hipError_t hipFuncSetAttribute(const void *fn, hipFuncAttribute attr, int value)
 }
 hipError_t hipFuncGetAttributes(struct hipFuncAttributes *attr, const void *fn) {
     (void)fn;
+    usleep(200000);  /* long enough for another thread to come by */
     memset(attr, 0, sizeof(*attr));
+    attr->sharedSizeBytes = 60000;
     return hipSuccess;
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *fn, int threads, size_t lds) {
@@ -73,8 +80,7 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *fn, 
     return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t attr, int dev) {
-    (void)dev;
-    *value = attr == hipDeviceAttributeMultiprocessorCount                  ? 256
+    *value = attr == hipDeviceAttributeMultiprocessorCount                  ? 256 >> dev
              : attr == hipDeviceAttributeMaxSharedMemoryPerMultiprocessor ? 160 << 10
                                                                           : 100000;
     return hipSuccess;

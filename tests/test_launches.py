@@ -59,3 +59,33 @@ def test_large_lds_is_allowed_on_every_device(tmp_path):
     assert not large
     attributes = [row for row in rows if row[0] == "attribute"]
     assert len(attributes) == len({tuple(row) for row in attributes}), "set once"
+
+
+def test_views_grid_is_the_devices_own(tmp_path):
+    """The recorder's devices have 256 and 128 compute units, whose LDS holds two
+    workgroups each."""
+    out = record(tmp_path, VIEWS + """
+for device in (0, 1, 0):
+    R.rec_set_device(device)
+    print(filter_views([100000], 512, 512))
+""")
+    grids = [int(line.split()[3]) for line in out.splitlines() if line.startswith("cooperative")]
+    assert grids == [512, 256, 512]
+
+
+def test_views_grid_of_threads_that_call_together(tmp_path):
+    """A second thread must not launch with what the first has only half found out:
+    a cooperative grid that is not resident at once would wait for itself."""
+    out = record(tmp_path, VIEWS + """
+import threading, time
+launches = lambda: None
+a = threading.Thread(target=filter_views, args=([100000], 64, 64))
+a.start()
+time.sleep(0.05)
+b = threading.Thread(target=filter_views, args=([100000], 64, 64))
+b.start()
+a.join(), b.join()
+print(R.rec_text().decode())
+""")
+    grids = [int(line.split()[3]) for line in out.splitlines() if line.startswith("cooperative")]
+    assert grids == [512, 512]
