@@ -2,17 +2,21 @@
 
 Times pf_filter_views for every (workgroup size, aggregation width) pair on
 the caller's actual views and frames, keeps the fastest, and caches the
-choice in a JSON file keyed by the device (name, compute units) and the
-views' shapes; tune_streams times pf_filter_views_concurrent for 1 .. 3
+choice in a JSON file keyed by the device (name, compute units), the views'
+shapes and the built library (another build's kernels may favour another pair); tune_streams times pf_filter_views_concurrent for 1 .. 3
 library streams.  Every configuration computes identical results; only the
 time differs.
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 
 import torch
+
+from ._lib import LIB_PATH
 
 BLOCKS = (64, 128, 256, 512, 1024)
 # aggregation width as a multiple of the workgroup size: 0 = device atomics
@@ -30,10 +34,16 @@ def cache_path() -> str:
     return os.environ.get("PF_AUTOTUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "pf_autotune.json"))
 
 
+@functools.lru_cache(maxsize=None)
+def library_digest() -> str:
+    with open(LIB_PATH, "rb") as fh:
+        return hashlib.sha256(fh.read()).hexdigest()[:16]
+
+
 def signature(frames) -> str:
     props = torch.cuda.get_device_properties(torch.cuda.current_device())
     shapes = ",".join(str(f["px"].numel()) for f in frames)
-    return f"{props.name}|{props.multi_processor_count}|{shapes}"
+    return f"{props.name}|{props.multi_processor_count}|{shapes}|{library_digest()}"
 
 
 def time_config(mvf, frames, block, agg, reps=5) -> float:
