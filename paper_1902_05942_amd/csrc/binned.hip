@@ -1,10 +1,12 @@
-// Insert-accumulate without device atomics on the cell sums, for gfx950.
+// Insert-accumulate with the cell sums added in LDS by the workgroup that owns
+// them, for gfx950.
 //
 // Device atomics run at ~24 G lines/s on MI355X whatever the footprint, and a
 // random access of any kind moves a whole cache line, so the cost of the
 // insert is the number of per-cell operations it sends to memory.  This path
 // sends one per group of vertices that share a key within a window of up to
-// 4096 consecutive vertices, and no atomic at all for the sums:
+// 4096 consecutive vertices, and no device atomic for the sums (but where a bucket
+// runs full, or a bin holds more cells than six passes sum):
 //   aggregate  per window: the vertices are merged by key in an LDS hash table
 //              (count and fixed-point sums added with LDS atomics; the LDS
 //              serialises the lanes of a coherent run on one entry more cheaply
@@ -33,7 +35,7 @@
 // vertices) took 234 and 1544 us: incoherent vertices hardly merge, so the
 // records' way through memory is what the insert costs, and a window of mostly
 // distinct keys overflowed its LDS table and sent its vertices to the table one
-// by one.  Small calls go another way (small_insert_kernel).
+// by one.  Small calls go another way (small_insert_kernel: device atomics).
 #include <mutex>
 #include <type_traits>
 
@@ -116,6 +118,8 @@ static constexpr size_t aggregate_lds(uint32_t chunk, uint32_t nbins) {
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// (Calls of up to kSmall vertices launch nothing of it; their workspace's size is
+// still this plan's, so that a call is refused or accepted as before.)
 Plan make_plan(uint32_t n, uint32_t log2_slots) {
     Plan p;
     // a bin per 1024 vertices up to 256 (a window of ~1500 groups then takes
@@ -655,9 +659,10 @@ struct Blend {
 // requested before the records are summed, and records are read a batch ahead
 // (256 bins and one workgroup of 1024 threads a CU: 3840x2160x4 190 -> 134 us, 8M
 // incoherent keys 206 -> 145 us, 1920x1080x3 40 -> 38 us).
-// A bin of more than kMaxPasses passes' cells (tables of 2^23 slots and more,
-// well filled) sends its records to the cells by device atomics instead, once:
-// 33M keys in a 2^25-slot table, all launches, passes / atomics at loads 0.15
+// A bin of more than kMaxPasses passes' cells (bins of 2^14 slots and more, well
+// filled: tables from 2^22 slots on, 2^23 above 2^22 vertices) sends its records to
+// the cells by device atomics instead, once: 33M keys in a 2^25-slot table, the
+// insert's launches alone, passes / atomics at loads 0.15
 // (4.8 passes) 2526 / 2905 us, 0.2 (6.4) 3025 / 3053, 0.3 3813 / 3316, 0.5 4947 /
 // 3773, 0.7 5922 / 4111.
 // kBlend: it also computes the temporal values of the cells (which are final:

@@ -113,10 +113,14 @@ static void launch_insert_t(const Tab &t, const uint64_t *key, const float *r, c
 hipError_t launch_insert(const Tab &t, const uint64_t *key, const float *r, const float *g, const float *b,
                          uint8_t *flags, uint32_t *slot_out, uint32_t n, uint32_t agg_width, hipStream_t st) {
     // a group is a claim's line and one or two lines of atomics, so fewer groups
-    // win once a call fills the chip with 1024-thread workgroups: agg_width
-    // 0 / 64 -> windows, int64 sums, 1920x1080x3 vertices 243 / 182 -> 143 us,
-    // 1280x720x3 114 / 90 -> 88, 640x360x3 48 / 44 -> 50, 330x200x3 29 / 29 -> 30;
-    // binary32 sums 368 / 235 -> 198, 176 / 126 -> 121, 61 / 56 -> 53, 29 / 30 -> 32
+    // win where vertices cohere, once a call fills the chip with 1024-thread
+    // workgroups.  agg_width 0 / 64 -> windows, frames, int64 sums: 540x330x3 39 / 37
+    // -> 37 us, 640x360x3 44 / 41 -> 43, 1024x768x1 61 / 43 -> 35, 1280x720x1 69 / 47 ->
+    // 40, 800x450x3 56 / 49 -> 55, 960x540x3 71 / 61 -> 62, 1280x720x3 106 / 83 -> 78;
+    // binary32 sums 47 / 41 -> 42, 56 / 49 -> 48, 99 / 56 -> 48, 108 / 63 -> 54, 76 / 63 ->
+    // 63, 102 / 80 -> 81, 161 / 116 -> 112.  Keys in random order lose a twentieth at any
+    // size (2.8M, int64: 192 -> 200) and a fifth just above the line (534k: 63 -> 77,
+    // two steps a workgroup on half the chip).
     if (insert_by_windows(n)) return launch_insert_windows(t, key, r, g, b, flags, slot_out, n, st);
     if (t.fsum)
         launch_insert_t<float>(t, key, r, g, b, flags, slot_out, n, agg_width, st);
