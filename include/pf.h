@@ -226,7 +226,7 @@ size_t pf_insert_workspace_bytes(uint64_t n, uint32_t log2_slots);
  * bucket holds twice what evenly spread keys can fill; groups that find it
  * full go to their cells by device atomics, as do the records of a bin of more
  * than 12288 cells.  Calls of up to 5 * 2^16 vertices leave the workspace as it
- * is: the vertices of a workgroup (256 to 1024) that share a key are merged in
+ * is: the vertices of a workgroup (128 to 1024) that share a key are merged in
  * LDS and go to their cell by device atomics; with a temporal blend its pass
  * over the table follows.)
  * slot_out is required.  workspace: pf_insert_workspace_bytes(n, log2_slots)

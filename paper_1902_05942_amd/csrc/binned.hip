@@ -553,8 +553,9 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // of atomics each, and every workgroup meets the empty cell.  (With a claim per
 // vertex 300k vertices of one cell took 1100 us, this 16; whole frames of
 // 401x229x3 at cell size 0.01 / 1 / 10: 42.8 / 281 / 356 -> 42.7 / 38.7 / 39.9 us.)
-// So the threads a workgroup double at kSmallGroups workgroups (512 threads at
-// 401x229x3: 41.6 / 57 / 77 us; 1024 at 64x64: 27.6 against 20.4), and beyond
+// So the threads a workgroup double at kSmallGroups workgroups, from 128 on (512
+// threads at 401x229x3: 41.6 / 57 / 77 us; 64x64 by 128 / 256 / 512 / 1024 threads
+// 20.2 / 20.5 / 22.3 / 27.6, as by a claim per vertex), and beyond
 // kSmallGroups of 1024 the slots after the home slot are read one at a time:
 // kAhead 4 saves a small call latency (200x150x3 43.4 -> 37.9 us) but reads the
 // lines that others are claiming (401x229x3 at cell size 10: 40 -> 56).
@@ -914,7 +915,9 @@ static hipError_t run(const Tab &t, const uint64_t *key, const float *r, const f
         const auto launch = [&](auto kernel, uint32_t threads) {
             kernel<<<(n + threads - 1) / threads, threads, 0, st>>>(t, key, r, g, b, flags, slot_out, n, fk);
         };
-        if (n <= kSmallGroups * 256)
+        if (n <= kSmallGroups * 128)
+            launch(small_insert_kernel<kKeys, 128, 4>, 128);
+        else if (n <= kSmallGroups * 256)
             launch(small_insert_kernel<kKeys, 256, 4>, 256);
         else if (n <= kSmallGroups * 512)
             launch(small_insert_kernel<kKeys, 512, 4>, 512);

@@ -1,5 +1,5 @@
 """The insert of small calls (up to 5 * 2^16 vertices): its workgroups grow at 192
-of 256, 512 and 1024 threads and merge vertices by key in LDS.  Table, flags,
+of 128, 256, 512 and 1024 threads and merge vertices by key in LDS.  Table, flags,
 counts and averages equal the oracle's bit for bit; a call whose vertices share
 few cells must not wait for every vertex's own claim."""
 import numpy as np
@@ -14,7 +14,7 @@ from test_gpu_insert_windows import _insert_and_compare, _keys
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [255, 257, 192 * 256, 192 * 256 + 1, 192 * 512, 192 * 512 + 1, 192 * 1024,
+@pytest.mark.parametrize("n", [127, 129, 192 * 128, 192 * 128 + 1, 192 * 256, 192 * 256 + 1, 192 * 512, 192 * 512 + 1, 192 * 1024,
                                192 * 1024 + 1, 5 << 16])
 @pytest.mark.parametrize("distinct", [1, 3, 0])
 def test_edges_of_workgroup_sizes(gpu, n, distinct):
