@@ -79,13 +79,15 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(Tab t, const uint64_t *_
     uint8_t fl = in ? flags[i] : (uint8_t)PF_V_INVALID;
     const uint8_t fl0 = fl;
     V q0 = 0, q1 = 0, q2 = 0;
+    uint64_t k = 0;
     if (fl == 0) {
+        k = key[i];  // requested with the contribution
         if constexpr (std::is_same<V, float>::value)
             fl = float_contribution(r[i], g[i], b[i], q0, q1, q2);
         else
             fl = fixed_point(r[i], g[i], b[i], t.frac_bits, q0, q1, q2);
     }
-    const uint32_t slot = find_or_claim_runs(t, fl == 0 ? key[i] : 0ull, fl == 0);
+    const uint32_t slot = find_or_claim_runs(t, k, fl == 0);
     if (fl == 0 && slot == kNoSlot) {
         fl = PF_V_OVERFLOW;
         add_u64(&t.stats[PF_STAT_PART_OVF + (blockIdx.x & 15)], 1ull);
