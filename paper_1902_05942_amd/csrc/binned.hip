@@ -662,10 +662,10 @@ struct Blend {
 // incoherent keys 206 -> 145 us, 1920x1080x3 40 -> 38 us).
 // A bin of more than kMaxPasses passes' cells (bins of 2^14 slots and more, well
 // filled: tables from 2^22 slots on, 2^23 above 2^22 vertices) sends its records to
-// the cells by device atomics instead, once: 33M keys in a 2^25-slot table, the
-// insert's launches alone, passes / atomics at loads 0.15
-// (4.8 passes) 2526 / 2905 us, 0.2 (6.4) 3025 / 3053, 0.3 3813 / 3316, 0.5 4947 /
-// 3773, 0.7 5922 / 4111.
+// the cells by device atomics instead, once.  33M keys drawn from load x 2^25 cells
+// (at load 0.5 86% of them occur; with every cell present 0.5 / 0.7 take 3994 / 5050
+// us), 2^25 slots, all launches, passes / atomics at loads 0.15 (4.8 passes) 2526 /
+// 2905 us, 0.2 (6.4) 3025 / 3053, 0.3 3813 / 3316, 0.5 4947 / 3773, 0.7 5922 / 4111.
 // kBlend: it also computes the temporal values of the cells (which are final:
 // every record of a slot is in the slot's bin), as pf_temporal_update does.
 constexpr uint32_t kMaxPasses = 6;
